@@ -922,7 +922,7 @@ __global__ __launch_bounds__(256) void k_constraints_lds(const double *__restric
     __shared__ double red[4][256];
     const int64_t lb = xcd_logical_block(blockIdx.x, gridDim.x);
     const int p = (int)(lb / 3);
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x;
     double h2 = 0.0, m2 = 0.0, cnt = 0.0, bad = 0.0;
     if (p < npatch) {  // uniform over the work-group
         const int sl = (int)(lb % 3);
@@ -945,7 +945,8 @@ __global__ __launch_bounds__(256) void k_constraints_lds(const double *__restric
         double q[NV], dq[3][NDIFF];
         const int ra[CONS_NB] = {SD, SD + 1, SD + 2, SD + 3, SD + 4, SD + 5, SD + 6, SD + 7,
                                  SD + 8, SD + 9, SD + 10, SD + 11, SD + 12, SD + 13};
-        lds_round(qb, lds, sl, ra, w, lane, hs);
+        const Stager sg = lds_stager(qb, sl, hs);
+        lds_round(lds, ra, sg);
         if (act)
 #pragma unroll
             for (int j = 0; j < CONS_NB; ++j) {
@@ -955,7 +956,7 @@ __global__ __launch_bounds__(256) void k_constraints_lds(const double *__restric
             }
         const int rb[CONS_NB] = {SD + 14, SD + 15, SD + 16, SD + 17, SP, SP + 1, SP + 2,
                                  SAT, SAT + 1, SAT + 2, SAT + 3, SAT + 4, SAT + 5, SK};
-        lds_issue(qb, lds, sl, rb, w, lane, hs);
+        lds_issue(lds, rb, sg);
         // the remaining slots pointwise (every slot takes part in the finiteness count), in
         // flight together with the second round's copies; an idle lane reads cell 242's values
 #pragma unroll
@@ -1199,7 +1200,7 @@ __global__ __launch_bounds__(256) void k_reconstruct_lds(double *__restrict__ Q,
     if (p >= npatch) return;  // uniform over the work-group
     const int sl = (int)(lb % 3);
     const PatchGeom g = geom[p];
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x;
     const bool act = tid < 243;
     const int cc = act ? tid : 242;
     const int x = cc % 9 + 3, y = (cc / 9) % 9 + 3, zl = cc / 81;
@@ -1223,7 +1224,7 @@ __global__ __launch_bounds__(256) void k_reconstruct_lds(double *__restrict__ Q,
     int64_t pd[3];
     push_offsets(nbr, p, x, y, z, o, pd, paxes);
     const int slots[SPHI + 1] = {0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10};
-    lds_round(qb, lds, sl, slots, w, lane, hs);
+    lds_round(lds, slots, lds_stager(qb, sl, hs));
     if (act) reconstruct_from_lds<0, SPHI + 1>(C, qb, o, pd);
 }
 

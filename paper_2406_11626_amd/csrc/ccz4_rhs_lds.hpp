@@ -39,7 +39,6 @@ constexpr int LPAIRS = LROW / 2;                  // 16-byte copies per staged r
 constexpr int LPLANE = NBX * LROW;                // one staged plane, 15 rows
 constexpr int LDS_OWN = 3 * LPLANE;               // the slab's planes
 constexpr int LDS_OWN_PAIRS = 3 * NBX * LPAIRS;   // 360 or 405 copies
-constexpr int LDS_OWN_CHUNKS = (LDS_OWN_PAIRS + 63) / 64;
 constexpr int LDS_HROW = 10;                      // halo row: x = 2..11 (16-byte aligned pairs)
 constexpr int LDS_HALO = 6 * 9 * LDS_HROW;        // 540 doubles
 constexpr int LDS_SLOT = LDS_OWN + LDS_HALO;      // 1260 (1350) doubles
@@ -47,11 +46,6 @@ constexpr int LDS_NBUF = 15;
 constexpr int LDS_DOUBLES = LDS_NBUF * LDS_SLOT;  // 151200 bytes
 
 typedef __attribute__((address_space(3))) void lds_void_t;
-
-// cache-policy bits of the staging copies (0: the default policy)
-#ifndef CCZ4_STAGE_CPOL
-#define CCZ4_STAGE_CPOL 0
-#endif
 
 // Where the y and z face halos of a patch are read from: d[2 (a - 1) + (side > 0)] (a = 1, 2) is
 // added to the element index of a halo cell of the face of axis a on that side.  0 reads the
@@ -64,49 +58,68 @@ struct HaloSrc {
     int64_t d[4];
 };
 
-// Issue the direct global->LDS copies of slot v of slab sl into buffer b (does not wait).
-// Own planes: 45 rows of LPAIRS pairs in 64-lane chunks (with an 18-double pitch the ninth pair of
-// a row repeats its eighth), the rows y <= 2 and y >= 12 from the y faces'
-// sources; halo rows: 270 pairs in five chunks, pair e being plane e / 45 (0..2 below, 3..5
-// above), row (e / 5) % 9, columns 2 + 2 (e % 5), planes outside the patch from the z faces'
-// sources.
-__device__ __forceinline__ void lds_stage_slot(const double *__restrict__ qp, double *lds, int sl, int v, int b,
-                                               int w, int lane, const HaloSrc &hs)
+// The staging copies of one lane.  A slot's LDS_PAIRS 16-byte pairs (own planes first: 45 rows of
+// LPAIRS pairs, where with an 18-double pitch the ninth pair of a row repeats its eighth; then the
+// halo rows: pair e being plane e / 45 (0..2 below, 3..5 above), row (e / 5) % 9, columns
+// 2 + 2 (e % 5)) are contiguous in LDS, so wave w copies chunks w, w + 4, w + 8 of 64 pairs.  The
+// source addresses of a lane's copies are the same in every slot up to the slot stride: they are
+// formed once per work-group instead of once per copy (which took about 25 integer instructions a
+// copy, 4000 of the 10,900 vector instructions of a right-hand side per wave).
+constexpr int LDS_PAIRS = LDS_SLOT / 2;
+constexpr int LDS_COPIES = (LDS_PAIRS + 255) / 256;  // per lane; the last only where pair < LDS_PAIRS
+static_assert(LDS_COPIES == 3, "three copies per lane and slot");
+
+struct Stager {
+    const double *src[LDS_COPIES];  // the lane's sources in slot 0
+    bool last;                      // the lane takes part in its wave's last chunk
+    int wave;                       // uniform
+};
+
+// slab sl of the patch at qp; the rows y <= 2 and y >= 12 come from the y faces' sources, planes
+// outside the patch from the z faces' sources
+__device__ __forceinline__ Stager lds_stager(const double *__restrict__ qp, int sl, const HaloSrc &hs)
 {
-    const double *box = qp + v * CS;
-    double *dst = lds + b * LDS_SLOT;
-    const double *own = box + (3 + 3 * sl) * ZS;
-    const int w0 = (w + b) & 3;
-    for (int ch = w0; ch < LDS_OWN_CHUNKS; ch += 4)
-        if (ch * 64 + lane < LDS_OWN_PAIRS) {
-            const int q = ch * 64 + lane, r = q / LPAIRS, j = q % LPAIRS, y = r % 15;
-            const int e = r * XS + 2 * (j < 8 ? j : 7);
-            // selects, not an index into hs.d: a lane-dependent index would put the array in memory
-            const int64_t d = y <= 2 ? hs.d[0] : (y >= 12 ? hs.d[1] : 0);
-            __builtin_amdgcn_global_load_lds((const void *)(own + e + d), (lds_void_t *)(dst + ch * 128), 16, 0, CCZ4_STAGE_CPOL);
-        }
-    const int w1 = (w + b + 2) & 3;
-    for (int ch = w1; ch < 5; ch += 4) {
-        const int e = ch * 64 + lane;
-        if (e < 270) {
-            const int hp = e / 45, row = (e / 5) % 9, pr = e % 5;
+    Stager g;
+    g.wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+#pragma unroll
+    for (int i = 0; i < LDS_COPIES; ++i) {
+        const int q = min(i * 256 + (int)threadIdx.x, LDS_PAIRS - 1);
+        int e;
+        int64_t d;  // selects, not an index into hs.d: a lane-dependent index would put the array in memory
+        if (q < LDS_OWN_PAIRS) {
+            const int r = q / LPAIRS, j = q % LPAIRS, y = r % 15;
+            e = (3 + 3 * sl) * ZS + r * XS + 2 * (j < 8 ? j : 7);
+            d = y <= 2 ? hs.d[0] : (y >= 12 ? hs.d[1] : 0);
+        } else {
+            const int h = q - LDS_OWN_PAIRS, hp = h / 45, row = (h / 5) % 9, pr = h % 5;
             const int z = hp < 3 ? 3 * sl + hp : 3 * sl + 3 + hp;
-            const int64_t zd = z <= 2 ? hs.d[2] : (z >= 12 ? hs.d[3] : 0);
-            __builtin_amdgcn_global_load_lds((const void *)(box + (z * ZS + (row + 3) * YS + 2 + 2 * pr) + zd),
-                                             (lds_void_t *)(dst + LDS_OWN + ch * 128), 16, 0, CCZ4_STAGE_CPOL);
+            e = z * ZS + (row + 3) * YS + 2 + 2 * pr;
+            d = z <= 2 ? hs.d[2] : (z >= 12 ? hs.d[3] : 0);
         }
+        g.src[i] = qp + e + d;
     }
+    g.last = (LDS_COPIES - 1) * 256 + (int)threadIdx.x < LDS_PAIRS;
+    return g;
 }
 
-// Issue the copies of a round's N slots into buffers 0..N-1 once every wave is done with the
-// previous round's buffers; returns without waiting for them.
+// Issue the direct global->LDS copies of a round's N slots into buffers 0..N-1 once every wave is
+// done with the previous round's buffers; returns without waiting for them.
 template <int N>
-__device__ __forceinline__ void lds_issue(const double *__restrict__ qp, double *lds, int sl, const int (&slots)[N],
-                                          int w, int lane, const HaloSrc &hs)
+__device__ __forceinline__ void lds_issue(double *lds, const int (&slots)[N], const Stager &g)
 {
     __syncthreads();
+    double *dst = lds + g.wave * 128;
 #pragma unroll
-    for (int j = 0; j < N; ++j) lds_stage_slot(qp, lds, sl, slots[j], j, w, lane, hs);
+    for (int j = 0; j < N; ++j)
+#pragma unroll
+        for (int i = 0; i < LDS_COPIES - 1; ++i)
+            __builtin_amdgcn_global_load_lds((const void *)(g.src[i] + slots[j] * CS),
+                                             (lds_void_t *)(dst + j * LDS_SLOT + i * 512), 16, 0, 0);
+    if (g.last)
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            __builtin_amdgcn_global_load_lds((const void *)(g.src[LDS_COPIES - 1] + slots[j] * CS),
+                                             (lds_void_t *)(dst + j * LDS_SLOT + (LDS_COPIES - 1) * 512), 16, 0, 0);
 }
 
 // Wait for every outstanding memory operation of the lane and make the staged slots visible to
@@ -119,10 +132,9 @@ __device__ __forceinline__ void lds_wait()
 
 // Stage the N slots of a round and wait for them.
 template <int N>
-__device__ __forceinline__ void lds_round(const double *__restrict__ qp, double *lds, int sl, const int (&slots)[N],
-                                          int w, int lane, const HaloSrc &hs)
+__device__ __forceinline__ void lds_round(double *lds, const int (&slots)[N], const Stager &g)
 {
-    lds_issue(qp, lds, sl, slots, w, lane, hs);
+    lds_issue(lds, slots, g);
     lds_wait();
 }
 
@@ -459,7 +471,7 @@ template <typename T, int LOP, typename Sink>
 __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, double *lds, int sl, bool act, int o0,
                                              const LdsCell &C0, const RhsParams &p, Sink &snk, const HaloSrc &hs)
 {
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+    const Stager sg = lds_stager(qp, sl, hs);
     const bool gdrv = p.shift != 0;
     const T sfac = gdrv ? T(1) : T(0);
     const T cc = cvt<T>(p.c);
@@ -487,7 +499,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
     {
         const int r1[15] = {SAT, SAT + 1, SAT + 2, SAT + 3, SAT + 4, SAT + 5, SB, SB + 1, SB + 2,
                             SB + 3, SB + 4, SB + 5, SB + 6, SB + 7, SB + 8};
-        lds_round(qp, lds, sl, r1, w, lane, hs);
+        lds_round(lds, r1, sg);
     }
     if (act) {
         {  // B: advection + KO, GB^i = gt^kl d_(k B_l)^i, sdBtr_k = d_(k B_l)^l, and the shift
@@ -619,7 +631,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
     {
         const int r2[15] = {SD, SD + 1, SD + 2, SD + 3, SD + 4, SD + 5, SD + 6, SD + 7,
                             SD + 8, SD + 9, SD + 10, SD + 11, SD + 12, SD + 13, SD + 14};
-        lds_round(qp, lds, sl, r2, w, lane, hs);
+        lds_round(lds, r2, sg);
     }
     if (act) {
         const LdsCell C = fresh(C0);
@@ -649,7 +661,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
                             SGHAT, SGHAT + 1, SGHAT + 2, SK, STHETA};
         double qa[15], qb[15];
         if (act) snk.load(R2_OUT, qa, qb);
-        lds_issue(qp, lds, sl, r3, w, lane, hs);
+        lds_issue(lds, r3, sg);
         __builtin_amdgcn_s_waitcnt(0);  // the sink's loads and this wave's copies have landed
         if (act) snk.store(R2_OUT, ro2, qa, qb);
     }
@@ -991,7 +1003,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
                             SALPHA, SBETA, SBETA + 1, SBETA + 2, SPHI};
         double qa[20], qb[20];
         if (act) snk.load(R3_OUT, qa, qb);
-        lds_issue(qp, lds, sl, r4, w, lane, hs);
+        lds_issue(lds, r4, sg);
         __builtin_amdgcn_s_waitcnt(0);  // the sink's loads and this wave's copies have landed
         if (act) snk.store(R3_OUT, ro3, qa, qb);
     }
