@@ -629,7 +629,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CCZ4_RHS_WP
     snk.s = s;
     snk.so = prm.formulation;
     snk.dt = dt;
-    snk.oc = acc_cell((int)(lb % 3), (int)threadIdx.x);
+    snk.oc = acc_cell((int)(lb % 3), slab_lane((int)threadIdx.x / 81, ((int)threadIdx.x / 9) % 9, (int)threadIdx.x % 9));
     push_offsets(nbr, p, c % 9 + 3, (c / 9) % 9 + 3, c / 81 + 3, cr.o, snk.pd, paxes);
     rhs_cell_phased<T>(cr, prm, snk);
 }
@@ -639,10 +639,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CCZ4_RHS_WP
 __device__ __forceinline__ void lds_cell_setup(double *lds, int sl, const PatchGeom &g, const RhsParams &prm,
                                                LdsCell &C, int &o, bool &act)
 {
-    const int tid = threadIdx.x;
-    act = tid < 243;
-    const int cc = act ? tid : 242;
-    const int x = cc % 9 + 3, y = (cc / 9) % 9 + 3, zl = cc / 81;
+    int x, y, zl;
+    act = slab_cell((int)threadIdx.x, x, y, zl);
     C.s = lds;
     lds_cell_offsets(C, x, y, zl);
 #pragma unroll
@@ -760,8 +758,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     ss.dt = dt;
     ss.oc = acc_cell(sl, act ? (int)threadIdx.x : 242);
     {
-        const int cc = act ? (int)threadIdx.x : 242;
-        push_offsets(nbr, p, cc % 9 + 3, (cc / 9) % 9 + 3, cc / 81 + 3 + 3 * sl, o, ss.pd, paxes);
+        int x, y, zl;
+        (void)slab_cell((int)threadIdx.x, x, y, zl);
+        push_offsets(nbr, p, x, y, zl + 3 + 3 * sl, o, ss.pd, paxes);
     }
     LdsStageSink snk{&ss, o};
     HaloSrc hs;
@@ -927,9 +926,8 @@ __global__ __launch_bounds__(256) void k_constraints_lds(const double *__restric
     if (p < npatch) {  // uniform over the work-group
         const int sl = (int)(lb % 3);
         const PatchGeom g = geom[p];
-        const bool act = tid < 243;
-        const int cc = act ? tid : 242;
-        const int x = cc % 9 + 3, y = (cc / 9) % 9 + 3, zl = cc / 81;
+        int x, y, zl;
+        const bool act = slab_cell(tid, x, y, zl);
         LdsCell C;
         C.s = lds;
         lds_cell_offsets(C, x, y, zl);
@@ -979,7 +977,7 @@ __global__ __launch_bounds__(256) void k_constraints_lds(const double *__restric
             constraints_algebra(q, dq, hm);
 #pragma unroll
             for (int j = 0; j < 4; ++j) fin = fin && isfinite(hm[j]);
-            const int c = sl * NFACE + tid;
+            const int c = sl * NFACE + (zl * 9 + y - 3) * 9 + x - 3;
             if (HM)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) HM[((int64_t)p * 4 + j) * NCELL + c] = hm[j];
@@ -1200,10 +1198,8 @@ __global__ __launch_bounds__(256) void k_reconstruct_lds(double *__restrict__ Q,
     if (p >= npatch) return;  // uniform over the work-group
     const int sl = (int)(lb % 3);
     const PatchGeom g = geom[p];
-    const int tid = threadIdx.x;
-    const bool act = tid < 243;
-    const int cc = act ? tid : 242;
-    const int x = cc % 9 + 3, y = (cc / 9) % 9 + 3, zl = cc / 81;
+    int x, y, zl;
+    const bool act = slab_cell((int)threadIdx.x, x, y, zl);
     LdsCell C;
     C.s = lds;
     lds_cell_offsets(C, x, y, zl);

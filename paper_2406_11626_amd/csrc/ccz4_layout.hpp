@@ -31,9 +31,28 @@ __host__ __device__ constexpr bool aux_slot(int v) { return v >= SA && v < SK0; 
 // box offset of cell (x, y, z) inside one slot of a patch
 __host__ __device__ constexpr int boff(int x, int y, int z) { return z * ZS + y * YS + x; }
 
+// Lane order of the LDS-staged kernels.  A z-slab's 27 rows of nine cells (plane zl, row y - 3) are
+// given to consecutive groups of nine lanes in the order slab_row(m), m = 0..26: within a plane rows
+// 0, 5, 1, 6, 2, 7, 3, 8, 4 (cyclically, plane zl starting 2 zl places on).  Consecutive groups then
+// lie 5 or -4 rows apart, which with the staged row pitch of 18 doubles (and 15 rows a plane) is 10 or
+// 8 double-wide LDS banks of 16 apart: the rows that one LDS access reads fall on different banks,
+// where in natural order (2 banks apart) four rows met on each (measured: 7.9 against 9.9 cycles per
+// wave and read; the fused stage 4.51 -> 4.45 ms, the right-hand side 3.06 -> 3.00 ms on 4096 leaves).
+// Blocks of 8 x 8 cells per wave read without conflicts (5.6 cycles), but their ninth column is
+// stored cell by cell: the right-hand side then took 3.41 ms.
+__host__ __device__ constexpr int slab_row_y(int zl, int k)  // k-th row of plane zl -> y - 3
+{
+    return ((k + 2 * zl) % 9) / 2 + (((k + 2 * zl) % 9) % 2 ? 5 : 0);
+}
+// position (0..242) in that order of the cell in plane zl, row y - 3 = yr, column x - 3 = xc
+__host__ __device__ constexpr int slab_lane(int zl, int yr, int xc)
+{
+    return (9 * zl + ((yr < 5 ? 2 * yr : 2 * yr - 9) + 9 - 2 * zl) % 9) * 9 + xc;
+}
+
 // Accumulator of the fused RK4 stage: state-sized, but private to that stage and laid out for
-// whole-line access.  Within one slot of a patch, interior cell i (0..242) of z-slab sl (cell
-// (x, y, z) with i = ((z - 3 - 3 sl) * 9 + y - 3) * 9 + x - 3) sits at 256 sl + i, so the lanes of
+// whole-line access.  Within one slot of a patch, interior cell i of z-slab sl (i = slab_lane of
+// the cell, 0..242) sits at 256 sl + i, so the lanes of
 // a wave cover consecutive 128-byte lines; ghost cell idx of the Sommerfeld face (axis, side)
 // sits at 768 + (2 axis + (side > 0)) * 243 + idx.
 constexpr int ACC_SLAB = 256;

@@ -153,6 +153,18 @@ __device__ __forceinline__ double lv(const LdsCell &c, int b, int a, int k)
     return a == 0 ? f[c.c + k] : (a == 1 ? f[c.c + k * LROW] : f[c.zo[k + 3]]);
 }
 
+// Box coordinates x, y and plane zl of the cell that lane tid (0..255) of a slab's work-group takes
+// (the order of slab_row_y; idle lanes repeat the last cell).
+__device__ __forceinline__ bool slab_cell(int tid, int &x, int &y, int &zl)
+{
+    const bool act = tid < 243;
+    const int cc = act ? tid : 242, m = cc / 9;
+    zl = m / 9;
+    x = cc % 9 + 3;
+    y = slab_row_y(zl, m % 9) + 3;
+    return act;
+}
+
 // The LDS offsets of cell (x, y) (box indices) in plane zl (0..2) of the staged slab: its own
 // index and those of its seven z-neighbours (own planes, or the halo rows below and above).
 __device__ __forceinline__ void lds_cell_offsets(LdsCell &C, int x, int y, int zl)
