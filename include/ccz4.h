@@ -197,9 +197,9 @@ enum { CCZ4_STAGE_FILL_SAME_LEVEL = 1, CCZ4_STAGE_GATHER_SAME_LEVEL = 2, CCZ4_ST
 ccz4_status ccz4_rhs_rk4_stage(ccz4_ctx *ctx, int32_t s, double dt, const double *Qs, const double *Qn,
                                double *acc, double *Qnext, int32_t precision, int32_t flags, void *stream);
 
-/* The flags the step graph passes to stage s (0..3), and in the second-order formulation to the
-   reconstruction after it, with the context's current kernel for this precision, into *flags
-   (host).  LDS kernel: GATHER at every stage, FILL_SAME_LEVEL_X at s = 0..2 and FILL_SAME_LEVEL
+/* The flags with which stage s (0..3) of a step made of single calls leaves least to fill, and in the
+   second-order formulation the reconstruction after it, with the context's current kernel for this
+   precision, into *flags (host).  LDS kernel: GATHER at every stage, FILL_SAME_LEVEL_X at s = 0..2 and FILL_SAME_LEVEL
    at s = 3 (between stages only the x-face halos are copied; the y and z ones are read from the
    neighbours, and the step leaves complete halos).  Phased kernel: FILL_SAME_LEVEL at every
    stage.  Between stages only ccz4_fill_halos_kinds(NEUMANN | LEVELS) is needed either way, and
@@ -275,7 +275,7 @@ typedef enum {
 ccz4_status ccz4_set_kernel(ccz4_ctx *ctx, int32_t precision, int32_t kernel);
 ccz4_status ccz4_get_kernel(const ccz4_ctx *ctx, int32_t precision, int32_t *kernel);
 
-/* Autotuner: times one fused stage (s = 1, with the flags ccz4_step_stage_flags gives that
+/* Autotuner: times one fused stage (s = 1, as ccz4_step_fused launches it with that
    configuration) of every launch configuration (0..CCZ4_KERNEL_CONFIGS-1 above: kernel, block
    order and leaf order) on this context's mesh, `reps` launches each after one warm-up, with
    events on `stream`, and selects the fastest for `precision`.  Q: a state with filled halos
@@ -285,10 +285,20 @@ ccz4_status ccz4_get_kernel(const ccz4_ctx *ctx, int32_t precision, int32_t *ker
 ccz4_status ccz4_autotune(ccz4_ctx *ctx, const double *Q, double *acc, double *Qx, int32_t precision,
                           int32_t reps, double *ms, void *stream);
 
-/* A fused RK4 step captured as a HIP graph: the four stages of ccz4_rhs_rk4_stage with the
-   flags of ccz4_step_stage_flags, (Qn -> Q1), (Q1 -> Q2), (Q2 -> Q1), (Q1 -> Qn), each followed
-   by ccz4_fill_halos_kinds(NEUMANN | LEVELS) of its output (in the second-order formulation then
-   ccz4_reconstruct_aux with the same flags and the same fill again), with the launch
+/* One whole RK4 step in place on Qn: the four fused stages (Qn -> Q1), (Q1 -> Q2), (Q2 -> Q1),
+   (Q1 -> Qn), each followed by ccz4_fill_halos_kinds(NEUMANN | LEVELS) of its output (in the
+   second-order formulation then ccz4_reconstruct_aux and the same fill again), with the context's
+   launch configuration for this precision.  Qn must enter with all halos filled and leaves with them
+   filled; Q1, Q2 and acc are work buffers, whose contents afterwards are unspecified.  Equal to the
+   stages called one by one up to floating-point rounding order: with the LDS kernel the step reads
+   every same-level halo of Q1 and Q2 (x faces too) from the neighbours, writes none of them, and
+   takes classical RK4 in the form Q^{n+1} = A + (Q3 - A)/3 + dt/6 k4, A = Q2 + (Q1 - Q^n)/2, Qi the
+   stage states, which touches acc in two stages only.  EINVAL on NULL or equal buffers, dt or
+   precision. */
+ccz4_status ccz4_step_fused(ccz4_ctx *ctx, double *Qn, double *Q1, double *Q2, double *acc, double dt,
+                            int32_t precision, void *stream);
+
+/* The step of ccz4_step_fused captured as a HIP graph, with the launch
    configuration current at creation.  Buffers and dt are fixed at creation; Qn must enter each launch with all halos filled
    and leaves with them filled.  The graph uses the context's tables: destroy it before the
    context.  Launch is asynchronous on `stream`. */

@@ -2,11 +2,13 @@
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libccz4.so")
-SOURCES = ["ccz4_kernels.hip", "ccz4_mlp.hip", "ccz4_host.cpp"]
+SOURCES = ["ccz4_lds_fp64.hip", "ccz4_lds_fp64_lop.hip", "ccz4_lds_mixed.hip", "ccz4_lds_mixed_lop.hip",
+           "ccz4_kernels.hip", "ccz4_mlp.hip", "ccz4_host.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -14,16 +16,19 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 
 
 def build(verbose=False, out=OUT, defines=()):
-    objs = []
-    for src in SOURCES:
-        tag = "".join(d.replace("=", "") for d in defines)
+    os.makedirs(os.path.join(CSRC, "_build"), exist_ok=True)
+    tag = "".join(d.replace("=", "") for d in defines)
+
+    def compile_one(src):
         obj = os.path.join(CSRC, "_build", tag + src + ".o")
-        os.makedirs(os.path.dirname(obj), exist_ok=True)
         cmd = [HIPCC, "-x", "hip", *FLAGS, *["-D" + d for d in defines], "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.check_call(cmd)
-        objs.append(obj)
+        return obj
+
+    with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1, 8)) as pool:
+        objs = list(pool.map(compile_one, SOURCES))
     tmp = out + ".tmp"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
     if verbose:

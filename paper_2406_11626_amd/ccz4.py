@@ -107,6 +107,7 @@ def lib():
             "ccz4_set_kernel": (i32, [P, i32, i32]),
             "ccz4_get_kernel": (i32, [P, i32, ctypes.POINTER(i32)]),
             "ccz4_autotune": (i32, [P, P, P, P, i32, i32, ctypes.POINTER(f64), P]),
+            "ccz4_step_fused": (i32, [P, P, P, P, P, f64, i32, P]),
             "ccz4_step_graph_create": (i32, [P, P, P, P, P, f64, i32, ctypes.POINTER(P)]),
             "ccz4_step_graph_launch": (i32, [P, P]),
             "ccz4_step_graph_destroy": (None, [P]),
@@ -277,6 +278,11 @@ def ccz4_autotune(h, Q, acc, Qx, precision=PREC_FP64, reps=3, stream=None):
     ms = (ctypes.c_double * KERNEL_CONFIGS)()
     _check(lib().ccz4_autotune(h, _ptr(Q), _ptr(acc), _ptr(Qx), int(precision), int(reps), ms, _stream(stream)))
     return list(ms)
+
+
+def ccz4_step_fused(h, Qn, Q1, Q2, acc, dt, precision=PREC_FP64, stream=None):
+    return _check(lib().ccz4_step_fused(h, _ptr(Qn), _ptr(Q1), _ptr(Q2), _ptr(acc), float(dt), int(precision),
+                                        _stream(stream)))
 
 
 def ccz4_step_graph_create(h, Qn, Q1, Q2, acc, dt, precision=PREC_FP64):
@@ -514,31 +520,21 @@ class Context:
 
     def rk4_step_fused(self, Qn, dt, bufs, precision=PREC_FP64, stream=None, push=True):
         """One RK4 step in place on Qn with the fused stage kernel; bufs = (Q1, Q2, acc).
-        With push (default) the stages handle the same-level halos themselves, with the flags of
-        ccz4_step_stage_flags (read from the neighbours, or written into them), so only Neumann
+        With push (default) the step is ccz4_step_fused: the stages handle the same-level halos
+        themselves, so only Neumann
         and coarse-fine faces are filled between stages; Qn must enter with all halos filled
         (ccz4_fill_halos once after the initial data) and leaves with them filled.  Without push
         every halo is filled before each stage."""
         Q1, Q2, acc = bufs
-        order = ((Qn, Q1), (Q1, Q2), (Q2, Q1), (Q1, Qn))
-        rest = FILL_NEUMANN | FILL_LEVELS
-        for s, (src, dst) in enumerate(order):
-            if push:
-                if s > 0:
-                    self.fill_halos_kinds(src, rest, stream)
-                fl = self.step_stage_flags(s, precision)
-                self.rhs_rk4_stage(s, dt, src, Qn, acc, dst, precision, fl, stream)
-                if self.second_order:  # Algorithm 2: the auxiliaries of the new state
-                    self.fill_halos_kinds(dst, rest, stream)
-                    self.reconstruct(dst, stream=stream, flags=fl)
-            else:
-                self.fill_halos(src, stream)
-                self.rhs_rk4_stage(s, dt, src, Qn, acc, dst, precision, 0, stream)
-                if self.second_order:
-                    self.fill_halos(dst, stream)
-                    self.reconstruct(dst, False, stream)
         if push:
-            self.fill_halos_kinds(Qn, rest, stream)
+            ccz4_step_fused(self.h, Qn, Q1, Q2, acc, dt, precision, stream)
+            return
+        for s, (src, dst) in enumerate(((Qn, Q1), (Q1, Q2), (Q2, Q1), (Q1, Qn))):
+            self.fill_halos(src, stream)
+            self.rhs_rk4_stage(s, dt, src, Qn, acc, dst, precision, 0, stream)
+            if self.second_order:  # Algorithm 2: the auxiliaries of the new state
+                self.fill_halos(dst, stream)
+                self.reconstruct(dst, False, stream)
 
     def tune_step_buffers(self, Qn, dt, precision=PREC_FP64, pool=5, steps=2, stream=None):
         """Work buffers (Q1, Q2, acc) for fused steps on Qn, chosen for their place in memory.

@@ -596,25 +596,70 @@ static int32_t step_stage_flags(const ccz4_ctx *, int32_t v, int32_t s)
     return CCZ4_STAGE_GATHER_SAME_LEVEL | (s == 3 ? CCZ4_STAGE_FILL_SAME_LEVEL : CCZ4_STAGE_FILL_SAME_LEVEL_X);
 }
 
-static hipError_t launch_reconstruct_flags(const ccz4_ctx *c, double *Q, int32_t flags, hipStream_t st)
+// The halo handling of a stage or reconstruction: the axes whose same-level halos of the output are
+// written in the neighbours, the axes whose same-level halos of the input are read from them, and
+// whether the stage is one of the four of a closed step.
+struct StageHalos {
+    int32_t paxes, gaxes, closed;
+};
+
+static StageHalos halos_of_flags(int32_t flags)
 {
-    const bool push = flags & (CCZ4_STAGE_FILL_SAME_LEVEL | CCZ4_STAGE_FILL_SAME_LEVEL_X);
-    return launch_reconstruct(Q, c->d_geom.p, (int32_t)c->leaf.size(), push ? c->d_nbr.p : nullptr,
-                              (flags & CCZ4_STAGE_FILL_SAME_LEVEL) ? 7 : 1,
-                              (flags & CCZ4_STAGE_GATHER_SAME_LEVEL) ? c->d_nbr.p : nullptr, st);
+    return {(flags & CCZ4_STAGE_FILL_SAME_LEVEL) ? 7 : ((flags & CCZ4_STAGE_FILL_SAME_LEVEL_X) ? 1 : 0),
+            (flags & CCZ4_STAGE_GATHER_SAME_LEVEL) ? 6 : 0, 0};
 }
 
-// One fused stage launch with the halo handling of `flags` (validated by the caller).
-static hipError_t launch_stage_flags(const ccz4_ctx *c, int32_t s, double dt, const double *Qs, const double *Qn,
-                                     double *acc, double *Qx, int32_t precision, int32_t variant, int32_t flags,
+// ... of stage s of a whole step (the step graph and ccz4_step_fused).  With the LDS kernel the four
+// stages are launched together, so every same-level halo of the intermediate states can be read from
+// the neighbours' interiors, the x ones too: stages 0..2 write no halo at all (the x-face copies
+// alone, three of a row's sixteen doubles into lines that other work-groups write, cost 0.5 of a
+// stage's 4.5 ms on 4096 leaves), and stage 3 copies all of them, leaving Q^{n+1} with complete
+// halos.  The phased kernel reads its own halos: every face is copied after every stage.
+static StageHalos step_halos(int32_t v, int32_t s)
+{
+    if (!(v & KV_LDS)) return {7, 0, 0};
+    return {s == 3 ? 7 : 0, 7, 1};
+}
+
+static hipError_t launch_reconstruct_halos(const ccz4_ctx *c, double *Q, const StageHalos &h, hipStream_t st)
+{
+    return launch_reconstruct(Q, c->d_geom.p, (int32_t)c->leaf.size(), c->d_nbr.p, h.paxes, h.gaxes, st);
+}
+
+// One fused stage launch with the halo handling h.
+static hipError_t launch_stage_halos(const ccz4_ctx *c, int32_t s, double dt, const double *Qs, const double *Qn,
+                                     double *acc, double *Qx, int32_t precision, int32_t variant, const StageHalos &h,
                                      hipStream_t st)
 {
-    const bool push = flags & (CCZ4_STAGE_FILL_SAME_LEVEL | CCZ4_STAGE_FILL_SAME_LEVEL_X);
-    const int32_t axes = (flags & CCZ4_STAGE_FILL_SAME_LEVEL) ? 7 : 1;
     return launch_stage(s, dt, Qs, Qn, acc, Qx, c->d_geom.p, (int32_t)c->leaf.size(), c->prm, precision, variant,
                         order_of(c, variant), c->d_bf.p, c->d_bg.p, (int32_t)c->bface.size(), c->d_pface.p,
-                        push ? c->d_nbr.p : nullptr, axes,
-                        (flags & CCZ4_STAGE_GATHER_SAME_LEVEL) ? c->d_nbr.p : nullptr, st);
+                        c->d_nbr.p, h.paxes, h.gaxes, h.closed, st);
+}
+
+// The launches of one whole fused RK4 step on a stream (captured or not).
+static hipError_t launch_step(const ccz4_ctx *c, double *Qn, double *Q1, double *Q2, double *acc, double dt,
+                              int32_t precision, hipStream_t st)
+{
+    double *src[4] = {Qn, Q1, Q2, Q1}, *dst[4] = {Q1, Q2, Q1, Qn};
+    const int32_t v = c->kernel[precision];
+    auto fill = [&](double *Q) {
+        hipError_t e = launch_fill(Q, c->d_phn.p, (int32_t)c->ph_neu.size(), c->prm.transfer, st);
+        if (e == hipSuccess) e = launch_fill(Q, c->d_phr.p, (int32_t)c->ph_res.size(), c->prm.transfer, st);
+        if (e == hipSuccess) e = launch_fill(Q, c->d_php.p, (int32_t)c->ph_pro.size(), c->prm.transfer, st);
+        return e;
+    };
+    hipError_t e = hipSuccess;
+    for (int s = 0; s < 4 && e == hipSuccess; ++s) {
+        const StageHalos h = step_halos(v, s);
+        e = launch_stage_halos(c, s, dt, src[s], Qn, acc, dst[s], precision, v, h, st);
+        if (e == hipSuccess) e = fill(dst[s]);
+        if (c->prm.formulation == CCZ4_FORMULATION_SECOND_ORDER) {
+            // Algorithm 2: the auxiliaries of the new state from its primaries, then their halos
+            if (e == hipSuccess) e = launch_reconstruct_halos(c, dst[s], h, st);
+            if (e == hipSuccess) e = fill(dst[s]);
+        }
+    }
+    return e;
 }
 
 ccz4_status ccz4_step_stage_flags(ccz4_ctx *c, int32_t precision, int32_t s, int32_t *flags)
@@ -647,7 +692,8 @@ ccz4_status ccz4_rhs_rk4_stage(ccz4_ctx *c, int32_t s, double dt, const double *
     if (acc == Qs || acc == Qn || acc == Qnext) return fail(CCZ4_EINVAL, "acc must not alias the states");
     if (!c->bface.empty() && !c->bg_valid)
         return fail(CCZ4_ESTATE, "Sommerfeld background not set (call ccz4_init_patches or ccz4_set_background)");
-    HIP_TRY(launch_stage_flags(c, s, dt, Qs, Qn, acc, Qnext, precision, c->kernel[precision], flags, S(stream)));
+    HIP_TRY(launch_stage_halos(c, s, dt, Qs, Qn, acc, Qnext, precision, c->kernel[precision], halos_of_flags(flags),
+                               S(stream)));
     return CCZ4_OK;
 }
 
@@ -658,7 +704,7 @@ ccz4_status ccz4_reconstruct_aux(ccz4_ctx *c, double *Q, int32_t flags, void *st
     if (st) return st;
     if (flags & ~(CCZ4_STAGE_FILL_SAME_LEVEL | CCZ4_STAGE_GATHER_SAME_LEVEL | CCZ4_STAGE_FILL_SAME_LEVEL_X))
         return fail(CCZ4_EINVAL, "unknown reconstruction flags");
-    HIP_TRY(launch_reconstruct_flags(c, Q, flags, S(stream)));
+    HIP_TRY(launch_reconstruct_halos(c, Q, halos_of_flags(flags), S(stream)));
     return CCZ4_OK;
 }
 
@@ -771,8 +817,8 @@ ccz4_status ccz4_autotune(ccz4_ctx *c, const double *Q, double *acc, double *Qx,
     const double dt = 1e-3;
     for (int32_t v = 0; v < KV_COUNT && he == hipSuccess; ++v) {
         // the middle stage of a step as the step graph runs it with this variant
-        const int32_t fl = step_stage_flags(c, v, 1);
-        auto stage = [&]() { return launch_stage_flags(c, 1, dt, Q, Q, acc, Qx, precision, v, fl, S(stream)); };
+        const StageHalos h = step_halos(v, 1);
+        auto stage = [&]() { return launch_stage_halos(c, 1, dt, Q, Q, acc, Qx, precision, v, h, S(stream)); };
         he = stage();  // warm-up
         if (he == hipSuccess) he = hipEventRecord(e0, S(stream));
         for (int r = 0; r < reps && he == hipSuccess; ++r) he = stage();
@@ -794,18 +840,16 @@ ccz4_status ccz4_autotune(ccz4_ctx *c, const double *Q, double *acc, double *Qx,
     return CCZ4_OK;
 }
 
-// A captured fused RK4 step: four stages with same-level halo push and the Neumann / coarse-fine
-// fill between them, replayed as one graph launch.
+// A captured fused RK4 step (launch_step), replayed as one graph launch.
 struct ccz4_graph {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
 };
 
-ccz4_status ccz4_step_graph_create(ccz4_ctx *c, double *Qn, double *Q1, double *Q2, double *acc, double dt,
-                                   int32_t precision, ccz4_graph **out)
+// The checks of a whole step's arguments.
+static ccz4_status check_step(const ccz4_ctx *c, const double *Qn, const double *Q1, const double *Q2, const double *acc,
+                              double dt, int32_t precision)
 {
-    if (!c || !out) return fail(CCZ4_EINVAL, "ctx or out is NULL");
-    *out = nullptr;
     ccz4_status st = check_ptr(Qn, "Qn");
     if (!st) st = check_ptr(Q1, "Q1");
     if (!st) st = check_ptr(Q2, "Q2");
@@ -819,6 +863,26 @@ ccz4_status ccz4_step_graph_create(ccz4_ctx *c, double *Qn, double *Q1, double *
             if (bufs[i] == bufs[j]) return fail(CCZ4_EINVAL, "Qn, Q1, Q2 and acc must be distinct");
     if (!c->bface.empty() && !c->bg_valid)
         return fail(CCZ4_ESTATE, "Sommerfeld background not set (call ccz4_init_patches or ccz4_set_background)");
+    return CCZ4_OK;
+}
+
+ccz4_status ccz4_step_fused(ccz4_ctx *c, double *Qn, double *Q1, double *Q2, double *acc, double dt, int32_t precision,
+                            void *stream)
+{
+    if (!c) return fail(CCZ4_EINVAL, "ctx is NULL");
+    const ccz4_status st = check_step(c, Qn, Q1, Q2, acc, dt, precision);
+    if (st) return st;
+    HIP_TRY(launch_step(c, Qn, Q1, Q2, acc, dt, precision, S(stream)));
+    return CCZ4_OK;
+}
+
+ccz4_status ccz4_step_graph_create(ccz4_ctx *c, double *Qn, double *Q1, double *Q2, double *acc, double dt,
+                                   int32_t precision, ccz4_graph **out)
+{
+    if (!c || !out) return fail(CCZ4_EINVAL, "ctx or out is NULL");
+    *out = nullptr;
+    const ccz4_status st = check_step(c, Qn, Q1, Q2, acc, dt, precision);
+    if (st) return st;
     hipStream_t cs = nullptr;
     HIP_TRY(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
     ccz4_graph *g = new (std::nothrow) ccz4_graph;
@@ -827,21 +891,7 @@ ccz4_status ccz4_step_graph_create(ccz4_ctx *c, double *Qn, double *Q1, double *
         return fail(CCZ4_ENOMEM, "graph");
     }
     hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-    double *src[4] = {Qn, Q1, Q2, Q1}, *dst[4] = {Q1, Q2, Q1, Qn};
-    for (int s = 0; s < 4 && e == hipSuccess; ++s) {
-        const int32_t fl = step_stage_flags(c, c->kernel[precision], s);
-        e = launch_stage_flags(c, s, dt, src[s], Qn, acc, dst[s], precision, c->kernel[precision], fl, cs);
-        if (e == hipSuccess) e = launch_fill(dst[s], c->d_phn.p, (int32_t)c->ph_neu.size(), c->prm.transfer, cs);
-        if (e == hipSuccess) e = launch_fill(dst[s], c->d_phr.p, (int32_t)c->ph_res.size(), c->prm.transfer, cs);
-        if (e == hipSuccess) e = launch_fill(dst[s], c->d_php.p, (int32_t)c->ph_pro.size(), c->prm.transfer, cs);
-        if (c->prm.formulation == CCZ4_FORMULATION_SECOND_ORDER) {
-            // Algorithm 2: the auxiliaries of the new state from its primaries, then their halos
-            if (e == hipSuccess) e = launch_reconstruct_flags(c, dst[s], fl, cs);
-            if (e == hipSuccess) e = launch_fill(dst[s], c->d_phn.p, (int32_t)c->ph_neu.size(), c->prm.transfer, cs);
-            if (e == hipSuccess) e = launch_fill(dst[s], c->d_phr.p, (int32_t)c->ph_res.size(), c->prm.transfer, cs);
-            if (e == hipSuccess) e = launch_fill(dst[s], c->d_php.p, (int32_t)c->ph_pro.size(), c->prm.transfer, cs);
-        }
-    }
+    if (e == hipSuccess) e = launch_step(c, Qn, Q1, Q2, acc, dt, precision, cs);
     hipError_t e2 = hipStreamEndCapture(cs, &g->graph);
     if (e == hipSuccess) e = e2;
     if (e == hipSuccess) e = hipGraphInstantiate(&g->exec, g->graph, nullptr, nullptr, 0);

@@ -8,6 +8,7 @@
 #include <algorithm>
 
 #include "ccz4_algebra.hpp"
+#include "ccz4_device.hpp"
 #include "ccz4_kernels.hpp"
 #include "ccz4_rhs_lds.hpp"
 #include "ccz4_rhs_phased.hpp"
@@ -104,24 +105,6 @@ __device__ void init_point(int scen, const double *sp, double x, double y, doubl
     for (int s = 0; s < 6; ++s) q[SAT + s] = ip6 * Ah[s];
 }
 
-// det gt = 1 by rescaling, then remove the trace of At with the rescaled metric
-__device__ void project_cell(double *q)
-{
-    const double det = q[0] * (q[3] * q[5] - q[4] * q[4]) - q[1] * (q[1] * q[5] - q[4] * q[2]) +
-                       q[2] * (q[1] * q[4] - q[3] * q[2]);
-    const double s = 1.0 / cbrt(det);
-    double g[6];
-    for (int v = 0; v < 6; ++v) g[v] = q[v] * s;
-    const double c00 = g[3] * g[5] - g[4] * g[4], c01 = g[2] * g[4] - g[1] * g[5], c02 = g[1] * g[4] - g[2] * g[3];
-    const double c11 = g[0] * g[5] - g[2] * g[2], c12 = g[1] * g[2] - g[0] * g[4], c22 = g[0] * g[3] - g[1] * g[1];
-    const double dn = g[0] * c00 + g[1] * c01 + g[2] * c02;
-    const double tr = (c00 * q[11] + c11 * q[14] + c22 * q[16] + 2.0 * (c01 * q[12] + c02 * q[13] + c12 * q[15])) / dn;
-    for (int v = 0; v < 6; ++v) {
-        q[v] = g[v];
-        q[11 + v] -= g[v] * tr * (1.0 / 3.0);
-    }
-}
-
 __global__ void k_init(double *__restrict__ Q, const PatchGeom *__restrict__ geom,
                        const uint8_t *__restrict__ bmask, int32_t npatch, int32_t scen, InitArgs a)
 {
@@ -151,34 +134,6 @@ __global__ void k_init(double *__restrict__ Q, const PatchGeom *__restrict__ geo
 }
 
 // ------------------------------------------------------------------ halo fill
-// One block per face task, one thread per halo cell of the 3 x 9 x 9 slab, loop over slots.
-// Axis a face: ghost layer L (1..3) sits at box coordinate 11 + L (side +1) or 3 - L (side -1);
-// interior depth d (1..3) from the face at 12 - d (side +1) or 2 + d (side -1).
-__device__ __forceinline__ int ghost_c(int side, int L) { return side > 0 ? 11 + L : 3 - L; }
-__device__ __forceinline__ int depth_c(int side, int d) { return side > 0 ? 12 - d : 2 + d; }
-
-// slab thread -> (layer L in 1..3, tangential t1, t2 in 0..8) with the lowest box axis fastest
-__device__ __forceinline__ void slab_coords(int axis, int idx, int &L, int &t1, int &t2)
-{
-    if (axis == 0) {  // layer index is the contiguous x
-        L = idx % 3 + 1;
-        t1 = (idx / 3) % 9;   // y
-        t2 = idx / 27;        // z
-    } else {
-        t1 = idx % 9;         // x
-        t2 = (idx / 9) % 9;   // z (axis 1) or y (axis 2)
-        L = idx / 81 + 1;
-    }
-}
-
-__device__ __forceinline__ int slab_off(int axis, int coordA, int t1, int t2)
-{
-    // t1/t2 are the tangential axes in increasing order: axis0 -> (y, z); axis1 -> (x, z); axis2 -> (x, y)
-    if (axis == 0) return boff(coordA, t1 + 3, t2 + 3);
-    if (axis == 1) return boff(t1 + 3, coordA, t2 + 3);
-    return boff(t1 + 3, t2 + 3, coordA);
-}
-
 // P_parallel row F (0..26) -> (first coarse index, weights w0, w1)
 __device__ __forceinline__ void ppar(int F, int &l, double &w0, double &w1)
 {
@@ -193,7 +148,6 @@ __device__ __forceinline__ void ppar(int F, int &l, double &w0, double &w1)
 
 // One block per (face task, batch of eight slots), one thread per slab cell; a copy issues all
 // loads of its batch before its stores, since source and destination share the state array.
-constexpr int SB8 = 8;
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_fill(
     double *__restrict__ Q, const FaceTask *__restrict__ tasks, int32_t ntask, int32_t transfer)
@@ -323,20 +277,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 }
 
 // ------------------------------------------------------------------ right-hand side
-__device__ __forceinline__ bool frozen_slot(int v)
-{
-    return (v >= SBETA && v < SBETA + 3) || (v >= SBB && v < SBB + 3) || (v >= SB && v < SB + 9);
-}
-
-// Work-group -> (patch, z-slab of 3 planes) with the three slabs of a patch on one XCD:
-// consecutive block ids are dealt to the 8 XCDs in turn, so logical block L runs at physical
-// id (L % per) * 8 + L / per with per = grid / 8 (the grid is padded to a multiple of 8).
-__device__ __forceinline__ int64_t xcd_logical_block(int64_t b, int64_t nblk)
-{
-    const int64_t per = nblk / 8;
-    return (b % 8) * per + b / 8;
-}
-
 #ifndef CCZ4_RHS_WPE
 #define CCZ4_RHS_WPE 1
 #endif
@@ -437,165 +377,6 @@ struct StageSink {
     }
 };
 
-// Offsets (in doubles, relative to the cell's own element) of the copies of interior cell
-// (x, y, z) of patch p in the face halos of its same-level neighbours: a cell within three layers
-// of a face whose neighbour nbr[6p + 2a + (side > 0)] is a leaf of the same level appears in that
-// neighbour's ghost layer at box coordinate c_a - 9 (side +1) or c_a + 9 (side -1).  0: no copy.
-__device__ __forceinline__ void push_offsets(const int32_t *__restrict__ nbr, int p, int x, int y, int z, int o,
-                                             int64_t pd[3], int axes = 7)
-{
-    const int c[3] = {x, y, z};
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        pd[a] = 0;
-        if (!nbr || !((axes >> a) & 1)) continue;
-        const int side = c[a] >= 9 ? 1 : (c[a] <= 5 ? -1 : 0);
-        if (side == 0) continue;
-        const int np = nbr[p * 6 + 2 * a + (side > 0 ? 1 : 0)];
-        if (np < 0) continue;
-        int m[3] = {x, y, z};
-        m[a] = side > 0 ? c[a] - 9 : c[a] + 9;
-        pd[a] = (int64_t)(np - p) * PS + (boff(m[0], m[1], m[2]) - o);
-    }
-}
-
-// Fused stage on the Sommerfeld ghosts of boundary face fi: G_L of Qs combined at once into
-// stage s (one thread per ghost cell, all slots).
-__device__ __forceinline__ void stage_ghost_face(int fi, int idx, int32_t s, double dt, const double *__restrict__ Qs,
-                                                 const double *__restrict__ Qn, double *__restrict__ acc,
-                                                 double *__restrict__ Qx, const PatchGeom *__restrict__ geom,
-                                                 const BoundaryFace *__restrict__ bf, const double *__restrict__ bg,
-                                                 int32_t frozen)
-{
-    if (idx >= NFACE) return;
-    const BoundaryFace f = bf[fi];
-    int L, t1, t2;
-    slab_coords(f.axis, idx, L, t1, t2);
-    const int cg = ghost_c(f.side, L);
-    const int og = slab_off(f.axis, cg, t1, t2);
-    const int ci = L == 1 ? depth_c(f.side, 1) : ghost_c(f.side, L - 1);
-    const int oi = slab_off(f.axis, ci, t1, t2);
-    const PatchGeom g = geom[f.patch];
-    int cx, cy, cz;
-    if (f.axis == 0) { cx = cg; cy = t1 + 3; cz = t2 + 3; }
-    else if (f.axis == 1) { cx = t1 + 3; cy = cg; cz = t2 + 3; }
-    else { cx = t1 + 3; cy = t2 + 3; cz = cg; }
-    const double X = g.org[0] + (cx - 2.5) * g.dx[0];
-    const double Y = g.org[1] + (cy - 2.5) * g.dx[1];
-    const double Z = g.org[2] + (cz - 2.5) * g.dx[2];
-    const double rr = sqrt(X * X + Y * Y + Z * Z);
-    const double xn = f.axis == 0 ? X : (f.axis == 1 ? Y : Z);
-    const double cadv = rr / (fabs(xn) * g.dx[f.axis]), cdmp = 1.0 / rr;
-    const int64_t base = (int64_t)f.patch * PS;
-    const double *B = bg + (int64_t)f.bg * NV * NFACE + idx;
-    const int oa = acc_ghost(f.axis, f.side, idx);
-    // the slots in batches of eight, every load of a batch issued before its arithmetic and stores
-    // (this work-group holds a whole CU's LDS while it runs, so it must not wait slot by slot)
-    for (int v0 = 0; v0 < NV; v0 += SB8) {
-        double qL[SB8], qI[SB8], qB[SB8], q0[SB8], a0[SB8];
-#pragma unroll
-        for (int j = 0; j < SB8; ++j) {
-            const int v = v0 + j;
-            if (v >= NV) break;
-            qL[j] = Qs[base + v * CS + og];
-            qI[j] = Qs[base + v * CS + oi];
-            qB[j] = B[v * NFACE];
-            q0[j] = s < 3 ? Qn[base + v * CS + og] : 0.0;
-            a0[j] = s > 0 ? acc[base + v * CS + oa] : 0.0;
-        }
-#pragma unroll
-        for (int j = 0; j < SB8; ++j) {
-            const int v = v0 + j;
-            if (v >= NV) break;
-            const double r = (v != SK0 && !(frozen && frozen_slot(v)))
-                                 ? -cadv * (qL[j] - qI[j]) - cdmp * (qL[j] - qB[j]) : 0.0;
-            const int64_t e = base + v * CS + og;
-            const int64_t ea = base + v * CS + oa;
-            if (s == 0) {
-                acc[ea] = q0[j] + (1.0 / 6.0) * dt * r;
-                Qx[e] = q0[j] + 0.5 * dt * r;
-            } else if (s < 3) {
-                acc[ea] = a0[j] + (1.0 / 3.0) * dt * r;
-                Qx[e] = q0[j] + (s == 1 ? 0.5 : 1.0) * dt * r;
-            } else {
-                Qx[e] = a0[j] + (1.0 / 6.0) * dt * r;
-            }
-        }
-    }
-}
-
-
-// The Sommerfeld ghost cells beside z-slab sl of patch p, handled by that slab's work-group after
-// its interior: of each boundary face of the patch, the ghost cells next to the slab's three planes
-// (81 for an x or y face; the whole face slab of 243 for the z face below slab 0 or above slab 2).
-// Those rows were just fetched and written by the same work-group, so the ghost update finds them
-// in the L2 instead of touching a line of HBM for every 3 ghost cells of an x face.  cell(fi, idx)
-// is called once for every such ghost cell (face fi of the boundary-face list, index idx in its slab).
-template <typename Cell>
-__device__ __forceinline__ void ghost_slab_cells(int p, int sl, const int32_t *__restrict__ pface, Cell &&cell)
-{
-#pragma unroll
-    for (int f = 0; f < 6; ++f) {
-        const int fi = pface[p * 6 + f];
-        const int axis = f >> 1;
-        const int n = fi < 0 ? 0 : (axis < 2 ? 81 : ((f & 1) ? (sl == 2 ? NFACE : 0) : (sl == 0 ? NFACE : 0)));
-        for (int r = (int)threadIdx.x; r < n; r += (int)blockDim.x) {
-            // slab_coords order: x face idx = (L - 1) + 3 y + 27 z; y face idx = x + 9 z + 81 (L - 1)
-            const int idx = axis == 0 ? 81 * sl + r : (axis == 1 ? 81 * (r / 27) + 27 * sl + r % 27 : r);
-            cell(fi, idx);
-        }
-    }
-}
-
-// Right-hand side G_L of all slots at ghost cell idx of boundary face fi (what k_rhs_sommerfeld
-// computes one thread per slot), the slots in batches of eight with every load of a batch first.
-__device__ __forceinline__ void rhs_ghost_cell(int fi, int idx, const double *__restrict__ Q, double *__restrict__ K,
-                                               const PatchGeom *__restrict__ geom,
-                                               const BoundaryFace *__restrict__ bf, const double *__restrict__ bg,
-                                               int32_t frozen)
-{
-    if (idx >= NFACE) return;
-    const BoundaryFace f = bf[fi];
-    int L, t1, t2;
-    slab_coords(f.axis, idx, L, t1, t2);
-    const int cg = ghost_c(f.side, L);
-    const int og = slab_off(f.axis, cg, t1, t2);
-    const int ci = L == 1 ? depth_c(f.side, 1) : ghost_c(f.side, L - 1);
-    const int oi = slab_off(f.axis, ci, t1, t2);
-    const PatchGeom g = geom[f.patch];
-    int cx, cy, cz;
-    if (f.axis == 0) { cx = cg; cy = t1 + 3; cz = t2 + 3; }
-    else if (f.axis == 1) { cx = t1 + 3; cy = cg; cz = t2 + 3; }
-    else { cx = t1 + 3; cy = t2 + 3; cz = cg; }
-    const double X = g.org[0] + (cx - 2.5) * g.dx[0];
-    const double Y = g.org[1] + (cy - 2.5) * g.dx[1];
-    const double Z = g.org[2] + (cz - 2.5) * g.dx[2];
-    const double rr = sqrt(X * X + Y * Y + Z * Z);
-    const double xn = f.axis == 0 ? X : (f.axis == 1 ? Y : Z);
-    const double *Qp = Q + (int64_t)f.patch * PS;
-    double *Kp = K + (int64_t)f.patch * PS;
-    const double *B = bg + (int64_t)f.bg * NV * NFACE + idx;
-    for (int v0 = 0; v0 < NV; v0 += SB8) {
-        double qL[SB8], qI[SB8], qB[SB8];
-#pragma unroll
-        for (int j = 0; j < SB8; ++j) {
-            const int v = v0 + j;
-            if (v >= NV) break;
-            qL[j] = Qp[v * CS + og];
-            qI[j] = Qp[v * CS + oi];
-            qB[j] = B[v * NFACE];
-        }
-#pragma unroll
-        for (int j = 0; j < SB8; ++j) {
-            const int v = v0 + j;
-            if (v >= NV) break;
-            Kp[v * CS + og] = (v == SK0 || (frozen && frozen_slot(v)))
-                                  ? 0.0
-                                  : -(rr / (fabs(xn) * g.dx[f.axis])) * (qL[j] - qI[j]) - (1.0 / rr) * (qL[j] - qB[j]);
-        }
-    }
-}
-
 template <typename T, int LOP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CCZ4_RHS_WPE))) void k_stage(
     const double *__restrict__ Qs, const double *__restrict__ Qn, double *__restrict__ acc, double *__restrict__ Qx,
@@ -632,150 +413,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CCZ4_RHS_WP
     snk.oc = acc_cell((int)(lb % 3), slab_lane((int)threadIdx.x / 81, ((int)threadIdx.x / 9) % 9, (int)threadIdx.x % 9));
     push_offsets(nbr, p, c % 9 + 3, (c / 9) % 9 + 3, c / 81 + 3, cr.o, snk.pd, paxes);
     rhs_cell_phased<T>(cr, prm, snk);
-}
-
-// LDS-staged variants: one work-group per (patch, z-slab), every lane takes part in staging;
-// the 151 KB of LDS leave one work-group per CU, so the waves may use the whole register file.
-__device__ __forceinline__ void lds_cell_setup(double *lds, int sl, const PatchGeom &g, const RhsParams &prm,
-                                               LdsCell &C, int &o, bool &act)
-{
-    int x, y, zl;
-    act = slab_cell((int)threadIdx.x, x, y, zl);
-    C.s = lds;
-    lds_cell_offsets(C, x, y, zl);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        C.i12[a] = 1.0 / (12.0 * g.dx[a]);
-        C.koc[a] = prm.ko_eps / (64.0 * g.dx[a]);
-    }
-    o = boff(x, y, zl + 3 + 3 * sl);
-}
-
-template <typename T, int LOP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_rhs_lds(
-    const double *__restrict__ Q, double *__restrict__ K, const PatchGeom *__restrict__ geom, int32_t npatch,
-    RhsParams prm, const BoundaryFace *__restrict__ bf, const double *__restrict__ bg,
-    const int32_t *__restrict__ pface, int32_t linear, const int32_t *__restrict__ order)
-{
-    __shared__ double lds[LDS_DOUBLES];
-    const int64_t lb = linear ? (int64_t)blockIdx.x : xcd_logical_block(blockIdx.x, gridDim.x);
-    if (lb / 3 >= npatch) return;  // uniform over the work-group
-    const int p = order[lb / 3];
-    const int sl = (int)(lb % 3);
-    const PatchGeom g = geom[p];
-    LdsCell C;
-    int o;
-    bool act;
-    lds_cell_setup(lds, sl, g, prm, C, o, act);
-    LdsRhsSink snk;
-    snk.kb = K + (int64_t)p * PS;
-    snk.o = o;
-    snk.so = prm.formulation;
-    const HaloSrc hs{{0, 0, 0, 0}};
-    rhs_slab_lds<T, LOP>(Q + (int64_t)p * PS, lds, sl, act, o, C, prm, snk, hs);
-    if (pface) {
-        const int32_t frozen = prm.shift == 0;
-        ghost_slab_cells(p, sl, pface, [&](int fi, int idx) { rhs_ghost_cell(fi, idx, Q, K, geom, bf, bg, frozen); });
-    }
-}
-
-struct LdsStageSink {
-    StageSink<0> *st;
-    int o;
-    __device__ __forceinline__ void put(int v, double r) { st->combine_at(o, v, r); }
-    __device__ __forceinline__ void finish() { st->finish_at(o); }
-    // A round's outputs in two halves: every load of Q^n and acc first, so that they are in
-    // flight together (the compiler cannot move them past the stores itself, not knowing that
-    // acc, Q^n and Q_next do not overlap), then the combines and stores.  The acc stream, and
-    // Q^n at s > 0, are touched once per launch, so they go through the caches as nontemporal:
-    // the lines the slab staging shares between work-groups stay in L2 longer (2-3% per stage).
-    // At s = 0, Q^n is Q_s and its loads hit the lines just staged, which must stay.  Q_next
-    // keeps ordinary stores: its rows are partial lines that merge in L2 with the copies the
-    // neighbours push into the same lines.
-    template <int N>
-    __device__ __forceinline__ void load(const int (&slots)[N], double (&a)[N], double (&b)[N])
-    {
-        const int s = st->s;
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-            if (st->so && aux_slot(slots[j])) continue;
-            const int e = slots[j] * CS + o;
-            a[j] = s == 0 ? st->qn[e] : (s < 3 ? __builtin_nontemporal_load(st->qn + e) : 0.0);
-            b[j] = s > 0 ? __builtin_nontemporal_load(st->acc + slots[j] * CS + st->oc) : 0.0;
-        }
-    }
-    template <int N>
-    __device__ __forceinline__ void store(const int (&slots)[N], const double (&r)[N], const double (&a)[N],
-                                          const double (&b)[N])
-    {
-        const int s = st->s;
-        const double dt = st->dt;
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-            const int v = slots[j];
-            if (st->so && aux_slot(v)) continue;
-            const int e = v * CS + o;
-            if (s == 0) {
-                __builtin_nontemporal_store(a[j] + (1.0 / 6.0) * dt * r[j], st->acc + v * CS + st->oc);
-                st->out(e, a[j] + 0.5 * dt * r[j]);
-            } else if (s < 3) {
-                __builtin_nontemporal_store(b[j] + (1.0 / 3.0) * dt * r[j], st->acc + v * CS + st->oc);
-                st->out(e, a[j] + (s == 1 ? 0.5 : 1.0) * dt * r[j]);
-            } else {
-                const double val = b[j] + (1.0 / 6.0) * dt * r[j];
-                if (v < 6) st->carry[v] = val;
-                else if (v >= SAT && v < SAT + 6) st->carry[v - SAT + 6] = val;
-                else st->out(e, val);
-            }
-        }
-    }
-};
-
-template <typename T, int LOP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_stage_lds(
-    const double *__restrict__ Qs, const double *__restrict__ Qn, double *__restrict__ acc, double *__restrict__ Qx,
-    const PatchGeom *__restrict__ geom, int32_t npatch, int32_t nb_slab, RhsParams prm, int32_t s, double dt,
-    const BoundaryFace *__restrict__ bf, const double *__restrict__ bg, const int32_t *__restrict__ pface,
-    const int32_t *__restrict__ nbr, int32_t paxes, const int32_t *__restrict__ gnbr, int32_t linear,
-    const int32_t *__restrict__ order)
-{
-    __shared__ double lds[LDS_DOUBLES];
-    const int64_t lb = linear ? (int64_t)blockIdx.x : xcd_logical_block(blockIdx.x, nb_slab);
-    if (lb / 3 >= npatch) return;  // uniform over the work-group
-    const int p = order[lb / 3];
-    const int sl = (int)(lb % 3);
-    const PatchGeom g = geom[p];
-    LdsCell C;
-    int o;
-    bool act;
-    lds_cell_setup(lds, sl, g, prm, C, o, act);
-    StageSink<0> ss;
-    ss.qn = Qn + (int64_t)p * PS;
-    ss.acc = acc + (int64_t)p * PS;
-    ss.qx = Qx + (int64_t)p * PS;
-    ss.s = s;
-    ss.so = prm.formulation;
-    ss.dt = dt;
-    ss.oc = acc_cell(sl, act ? (int)threadIdx.x : 242);
-    {
-        int x, y, zl;
-        (void)slab_cell((int)threadIdx.x, x, y, zl);
-        push_offsets(nbr, p, x, y, zl + 3 + 3 * sl, o, ss.pd, paxes);
-    }
-    LdsStageSink snk{&ss, o};
-    HaloSrc hs;
-#pragma unroll
-    for (int f = 0; f < 4; ++f) {  // faces y-, y+, z-, z+
-        const int n = gnbr ? gnbr[p * 6 + 2 + f] : -1;
-        hs.d[f] = n >= 0 ? (int64_t)(n - p) * PS + ((f & 1) ? -9 : 9) * (f < 2 ? YS : ZS) : 0;
-    }
-    rhs_slab_lds<T, LOP>(Qs + (int64_t)p * PS, lds, sl, act, o, C, prm, snk, hs);
-    if (pface) {
-        const int32_t frozen = prm.shift == 0;
-        ghost_slab_cells(p, sl, pface, [&](int fi, int idx) {
-            stage_ghost_face(fi, idx, s, dt, Qs, Qn, acc, Qx, geom, bf, bg, frozen);
-        });
-    }
 }
 
 // Sommerfeld ghosts: one thread per (boundary face, slot, ghost cell)
@@ -928,22 +565,22 @@ __global__ __launch_bounds__(256) void k_constraints_lds(const double *__restric
         const PatchGeom g = geom[p];
         int x, y, zl;
         const bool act = slab_cell(tid, x, y, zl);
-        LdsCell C;
+        LdsCell<0> C;
         C.s = lds;
-        lds_cell_offsets(C, x, y, zl);
+        const HaloSrc hs{};
+        lds_cell_offsets(C, x, y, zl, hs);
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             C.i12[a] = 1.0 / (12.0 * g.dx[a]);
             C.koc[a] = 0.0;
         }
-        const HaloSrc hs{{0, 0, 0, 0}};
         const double *qb = Q + (int64_t)p * PS;
         const int z = zl + 3 + 3 * sl;
         const int o = boff(x, y, z);
         double q[NV], dq[3][NDIFF];
         const int ra[CONS_NB] = {SD, SD + 1, SD + 2, SD + 3, SD + 4, SD + 5, SD + 6, SD + 7,
                                  SD + 8, SD + 9, SD + 10, SD + 11, SD + 12, SD + 13};
-        const Stager sg = lds_stager(qb, sl, hs);
+        const Stager sg = lds_stager<0>(qb, sl, hs);
         lds_round(lds, ra, sg);
         if (act)
 #pragma unroll
@@ -1152,8 +789,8 @@ __global__ __launch_bounds__(256) void k_regrid(const double *__restrict__ Qo, d
 }
 
 // Differences of primaries V0..V1-1, staged in LDS buffers 0.., into the auxiliaries of the cell.
-template <int V0, int V1>
-__device__ __forceinline__ void reconstruct_from_lds(const LdsCell &C, double *__restrict__ qb, int o,
+template <int V0, int V1, int XG>
+__device__ __forceinline__ void reconstruct_from_lds(const LdsCell<XG> &C, double *__restrict__ qb, int o,
                                                      const int64_t (&pd)[3])
 {
 #pragma unroll
@@ -1184,13 +821,14 @@ __device__ __forceinline__ void reconstruct_from_lds(const LdsCell &C, double *_
 // the three planes below and above), then every lane forms its cell's 33 differences from LDS
 // (110 KB: one work-group per CU; two rounds of six primaries in 60 KB, two work-groups per CU, ran
 // 5% slower; one thread per cell reading its stencils through the caches ran 30% slower).  The
-// primaries' halos must be filled, except, with gnbr, the y and z face halos shared with a
-// same-level leaf, which are then read from that leaf's interior.  With nbr, every value within
+// primaries' halos must be filled, except the face halos normal to an axis of gaxes and shared with a
+// same-level leaf, which are read from that leaf's interior.  Every value within
 // three layers of a face shared with a same-level leaf and normal to an axis of paxes is also
 // written into that leaf's face halo (as the stage push does).
+template <int XG>
 __global__ __launch_bounds__(256) void k_reconstruct_lds(double *__restrict__ Q, const PatchGeom *__restrict__ geom,
                                                          int32_t npatch, const int32_t *__restrict__ nbr,
-                                                         int32_t paxes, const int32_t *__restrict__ gnbr)
+                                                         int32_t paxes, int32_t gaxes)
 {
     __shared__ double lds[(SPHI + 1) * LDS_SLOT];
     const int64_t lb = xcd_logical_block(blockIdx.x, gridDim.x);
@@ -1200,37 +838,37 @@ __global__ __launch_bounds__(256) void k_reconstruct_lds(double *__restrict__ Q,
     const PatchGeom g = geom[p];
     int x, y, zl;
     const bool act = slab_cell((int)threadIdx.x, x, y, zl);
-    LdsCell C;
+    const HaloSrc hs = halo_sources(nbr, p, gaxes);
+    LdsCell<XG> C;
     C.s = lds;
-    lds_cell_offsets(C, x, y, zl);
+    lds_cell_offsets(C, x, y, zl, hs);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         C.i12[a] = 1.0 / (12.0 * g.dx[a]);
         C.koc[a] = 0.0;
     }
-    HaloSrc hs;
-#pragma unroll
-    for (int f = 0; f < 4; ++f) {  // faces y-, y+, z-, z+
-        const int n = gnbr ? gnbr[p * 6 + 2 + f] : -1;
-        hs.d[f] = n >= 0 ? (int64_t)(n - p) * PS + ((f & 1) ? -9 : 9) * (f < 2 ? YS : ZS) : 0;
-    }
     double *qb = Q + (int64_t)p * PS;
     const int z = zl + 3 + 3 * sl;
     const int o = boff(x, y, z);
     int64_t pd[3];
-    push_offsets(nbr, p, x, y, z, o, pd, paxes);
+    push_offsets(paxes ? nbr : nullptr, p, x, y, z, o, pd, paxes);
     const int slots[SPHI + 1] = {0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10};
-    lds_round(lds, slots, lds_stager(qb, sl, hs));
-    if (act) reconstruct_from_lds<0, SPHI + 1>(C, qb, o, pd);
+    lds_round(lds, slots, lds_stager<XG>(qb, sl, hs));
+    if (act) reconstruct_from_lds<0, SPHI + 1, XG>(C, qb, o, pd);
 }
 
 
 hipError_t launch_reconstruct(double *Q, const PatchGeom *geom, int32_t npatch, const int32_t *nbr, int32_t paxes,
-                              const int32_t *gnbr, hipStream_t st)
+                              int32_t gaxes, hipStream_t st)
 {
     if (npatch <= 0) return hipSuccess;
     const int64_t nb = ((int64_t)npatch * 3 + 7) / 8 * 8;  // a multiple of 8 for the XCD block order
-    hipLaunchKernelGGL(k_reconstruct_lds, dim3((unsigned)nb), dim3(256), 0, st, Q, geom, npatch, nbr, paxes, gnbr);
+    if (gaxes & 1)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_reconstruct_lds<1>), dim3((unsigned)nb), dim3(256), 0, st, Q, geom, npatch,
+                           nbr, paxes, gaxes);
+    else
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_reconstruct_lds<0>), dim3((unsigned)nb), dim3(256), 0, st, Q, geom, npatch,
+                           nbr, paxes, gaxes);
     return hipGetLastError();
 }
 
@@ -1432,22 +1070,9 @@ hipError_t launch_rhs(const double *Q, double *K, const PatchGeom *geom, int32_t
     const int64_t nb = ((int64_t)npatch * 3 + 7) / 8 * 8;
     const int32_t lin = (variant & KV_LINEAR) ? 1 : 0;
     if (variant & KV_LDS) {
-        const dim3 g((unsigned)nb), b(256);
-        if (p.advection) {
-            if (precision == 1)
-                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rhs_lds<float, 1>), g, b, 0, st, Q, K, geom, npatch, p, bf, bg,
-                                   slab_ghosts, lin, order);
-            else
-                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rhs_lds<double, 1>), g, b, 0, st, Q, K, geom, npatch, p, bf, bg,
-                                   slab_ghosts, lin, order);
-        } else {
-            if (precision == 1)
-                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rhs_lds<float, 0>), g, b, 0, st, Q, K, geom, npatch, p, bf, bg,
-                                   slab_ghosts, lin, order);
-            else
-                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rhs_lds<double, 0>), g, b, 0, st, Q, K, geom, npatch, p, bf, bg,
-                                   slab_ghosts, lin, order);
-        }
+        const RhsLaunch a{Q, K, geom, npatch, p, bf, bg, slab_ghosts, lin, order, (int32_t)nb};
+        if (p.advection) return precision == 1 ? launch_rhs_lds<float, 1>(a, st) : launch_rhs_lds<double, 1>(a, st);
+        return precision == 1 ? launch_rhs_lds<float, 0>(a, st) : launch_rhs_lds<double, 0>(a, st);
     } else {
         const dim3 g((unsigned)nb), b(256);
         if (p.advection) {
@@ -1476,7 +1101,7 @@ hipError_t launch_rhs(const double *Q, double *K, const PatchGeom *geom, int32_t
 hipError_t launch_stage(int32_t s, double dt, const double *Qs, const double *Qn, double *acc, double *Qx,
                         const PatchGeom *geom, int32_t npatch, const RhsParams &p, int32_t precision,
                         int32_t variant, const int32_t *order, const BoundaryFace *bf, const double *bg, int32_t nbf,
-                        const int32_t *pface, const int32_t *nbr, int32_t paxes, const int32_t *gnbr,
+                        const int32_t *pface, const int32_t *nbr, int32_t paxes, int32_t gaxes, int32_t closed,
                         hipStream_t st)
 {
     // the LDS kernel updates the Sommerfeld ghosts inside the slab work-groups (per-leaf face table)
@@ -1485,39 +1110,28 @@ hipError_t launch_stage(int32_t s, double dt, const double *Qs, const double *Qn
     const int64_t nb = nb_slab + (nbf > 0 ? nbf : 0);
     const int32_t ns = (int32_t)nb_slab;
     const int32_t lin = (variant & KV_LINEAR) ? 1 : 0;
+    const int32_t *pushed = paxes ? nbr : nullptr;
     if (variant & KV_LDS) {
-        const dim3 g((unsigned)nb_slab), b(256);
-        if (p.advection) {
-            if (precision == 1)
-                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stage_lds<float, 1>), g, b, 0, st, Qs, Qn, acc, Qx, geom, npatch,
-                                   ns, p, s, dt, bf, bg, slab_ghosts, nbr, paxes, gnbr, lin, order);
-            else
-                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stage_lds<double, 1>), g, b, 0, st, Qs, Qn, acc, Qx, geom, npatch,
-                                   ns, p, s, dt, bf, bg, slab_ghosts, nbr, paxes, gnbr, lin, order);
-        } else {
-            if (precision == 1)
-                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stage_lds<float, 0>), g, b, 0, st, Qs, Qn, acc, Qx, geom, npatch,
-                                   ns, p, s, dt, bf, bg, slab_ghosts, nbr, paxes, gnbr, lin, order);
-            else
-                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stage_lds<double, 0>), g, b, 0, st, Qs, Qn, acc, Qx, geom, npatch,
-                                   ns, p, s, dt, bf, bg, slab_ghosts, nbr, paxes, gnbr, lin, order);
-        }
+        const StageLaunch a{Qs, Qn, acc, Qx, geom, npatch, p, s, dt, bf, bg, slab_ghosts, nbr, paxes, gaxes, closed, lin,
+                            order, ns};
+        if (p.advection) return precision == 1 ? launch_stage_lds<float, 1>(a, st) : launch_stage_lds<double, 1>(a, st);
+        return precision == 1 ? launch_stage_lds<float, 0>(a, st) : launch_stage_lds<double, 0>(a, st);
     } else {
         const dim3 g((unsigned)nb), b(256);
         if (p.advection) {
             if (precision == 1)
                 hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stage<float, 1>), g, b, 0, st, Qs, Qn, acc, Qx, geom, npatch, ns,
-                                   p, s, dt, bf, bg, nbr, paxes, lin, order);
+                                   p, s, dt, bf, bg, pushed, paxes, lin, order);
             else
                 hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stage<double, 1>), g, b, 0, st, Qs, Qn, acc, Qx, geom, npatch, ns,
-                                   p, s, dt, bf, bg, nbr, paxes, lin, order);
+                                   p, s, dt, bf, bg, pushed, paxes, lin, order);
         } else {
             if (precision == 1)
                 hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stage<float, 0>), g, b, 0, st, Qs, Qn, acc, Qx, geom, npatch, ns,
-                                   p, s, dt, bf, bg, nbr, paxes, lin, order);
+                                   p, s, dt, bf, bg, pushed, paxes, lin, order);
             else
                 hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stage<double, 0>), g, b, 0, st, Qs, Qn, acc, Qx, geom, npatch, ns,
-                                   p, s, dt, bf, bg, nbr, paxes, lin, order);
+                                   p, s, dt, bf, bg, pushed, paxes, lin, order);
         }
     }
     return hipGetLastError();

@@ -3,9 +3,9 @@
 //
 // Every evolved slot is copied once per evaluation from the patch box into LDS with gfx950's
 // direct global->LDS loads (16 bytes per lane, no registers involved), at most 15 slots per
-// round.  A slot occupies, in LDS, the slab's three planes in box layout (3 x 15 x 16 doubles,
+// round.  A slot occupies, in LDS, the slab's three planes in box layout (3 x 15 x 18 doubles,
 // carrying the x and y halos) followed by the interior rows of the three planes below and the
-// three planes above the slab (6 x 9 rows x 10 doubles, columns x = 2..11).  Each y or z face
+// three planes above the slab (6 x 9 rows x 10 doubles, columns x = 2..11).  Each face
 // halo is read either from the patch's own halo or straight from the interior of the same-level
 // neighbour across that face (HaloSrc).  Every FD4
 // derivative and Kreiss-Oliger sum is then read from LDS; a per-lane table maps the seven
@@ -27,39 +27,82 @@
 
 namespace ccz4 {
 
-// Row pitch of the staged own planes in LDS (doubles): 18 (default), whose odd pair count spreads
-// the rows of a wave's reads over the LDS banks (the extra pair is a repeat copy), or the box row
-// (16), whose rows all fall on the same banks.
-#ifndef CCZ4_LDS_ROW
-#define CCZ4_LDS_ROW 18
-#endif
-constexpr int LROW = CCZ4_LDS_ROW;
-static_assert(LROW == 16 || LROW == 18, "LDS row pitch: 16 or 18 doubles");
+// A staged row of the own planes is 18 doubles, in one of two layouts (XG, a template parameter):
+//   XG = 0: the patch's own row, x = 0..15 (the ninth pair repeats the eighth): every neighbour of a
+//           cell along x at a fixed distance.
+//   XG = 1: the x halos may be gathered from the neighbours.  Columns 0..3: the x- halo group, 4..13:
+//           x = 2..11 of the patch, 14..17: the x+ halo group.  A halo group is two 16-byte pairs: the
+//           patch's own (x = 0..3; x = 12..15), or the pairs of the neighbour's interior that hold the
+//           three cells (x = 8..11 of the x- neighbour; x = 2..5 of the x+ one).  Interior cells sit at
+//           x + 2; a halo cell of the x- face at x (own) or x + 1 (gathered), of the x+ face at x + 2
+//           or x + 3: a per-lane table (LdsCell::xo), whose six base registers cost the merged reads of
+//           XG = 0 (right-hand side alone: 2.98 against 3.07 ms on 4096 leaves), which the copies that
+//           a step then does not make pay for (a step: 18.1 -> 16.2 ms).
+// The pitch of 18 doubles (an odd number of pairs) spreads the rows of a wave's reads over the banks.
+constexpr int LROW = 18;
 constexpr int LPAIRS = LROW / 2;                  // 16-byte copies per staged row
 constexpr int LPLANE = NBX * LROW;                // one staged plane, 15 rows
 constexpr int LDS_OWN = 3 * LPLANE;               // the slab's planes
-constexpr int LDS_OWN_PAIRS = 3 * NBX * LPAIRS;   // 360 or 405 copies
+constexpr int LDS_OWN_PAIRS = 3 * NBX * LPAIRS;   // 405 copies
 constexpr int LDS_HROW = 10;                      // halo row: x = 2..11 (16-byte aligned pairs)
 constexpr int LDS_HALO = 6 * 9 * LDS_HROW;        // 540 doubles
-constexpr int LDS_SLOT = LDS_OWN + LDS_HALO;      // 1260 (1350) doubles
+constexpr int LDS_SLOT = LDS_OWN + LDS_HALO;      // 1350 doubles
 constexpr int LDS_NBUF = 15;
-constexpr int LDS_DOUBLES = LDS_NBUF * LDS_SLOT;  // 151200 bytes
+constexpr int LDS_DOUBLES = LDS_NBUF * LDS_SLOT;  // 162000 bytes
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 
-// Where the y and z face halos of a patch are read from: d[2 (a - 1) + (side > 0)] (a = 1, 2) is
-// added to the element index of a halo cell of the face of axis a on that side.  0 reads the
-// patch's own halo (filled beforehand); for a same-level neighbour n it is (n - p) PS -+ 9 stride_a,
-// which reads the neighbour's interior cell at the same position directly, so that those halos
-// need no copy.  The x halos always come from the patch's own halo: x-face sources would split a
-// 16-byte pair (x = 2 from the neighbour, x = 3 from the patch) and need 4-byte copies, which cost
-// more than the x-face copies themselves (the x neighbours are mostly resident in the same L2).
-struct HaloSrc {
-    int64_t d[4];
+// One patch of a state (or of the accumulator), addressed as a buffer: a uniform base, a byte offset
+// per lane within a slot (8 o, the same for every slot) and the slot's byte offset in a scalar
+// register, so that no access needs vector address arithmetic (64-bit adds on a slot stride beyond
+// the instructions' immediate range took two vector instructions per access and array).
+typedef unsigned int buf_b64_t __attribute__((ext_vector_type(2)));
+constexpr int BUF_DEFAULT = 0, BUF_NT = 2;  // cache policy: default, nontemporal
+
+struct PatchBuf {
+    const double *base;
+    template <int POLICY = BUF_DEFAULT>
+    __device__ __forceinline__ double load(uint32_t ob, int v) const
+    {
+        return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rsrc(), ob, v * CS * 8, POLICY));
+    }
+    template <int POLICY = BUF_DEFAULT>
+    __device__ __forceinline__ void store(double x, uint32_t ob, int v) const
+    {
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(buf_b64_t, x), rsrc(), ob, v * CS * 8, POLICY);
+    }
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc() const
+    {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(base), 0, (int)(PS * 8), 0x00027000);
+    }
 };
 
+// Where the face halos of a patch are read from: d[2 a + (side > 0)] is added to the element index of
+// a halo cell of the face of axis a on that side.  0 reads the patch's own halo (filled beforehand);
+// for a same-level neighbour n the offset reads the neighbour's interior cell at the same position,
+// so that those halos need no copy: (n - p) PS -+ 9 stride_a for y and z.  An x group is whole 16-byte
+// pairs, which in the neighbour begin one cell lower: (n - p) PS + 8 (x-) and (n - p) PS - 10 (x+).
+struct HaloSrc {
+    int64_t d[6];
+};
+
+// The sources of patch p's halos with the faces of the axes in gaxes gathered from same-level
+// neighbours (nbr: the leaves' face neighbours, -1 where there is none of the same level).
+__device__ __forceinline__ HaloSrc halo_sources(const int32_t *__restrict__ nbr, int p, int32_t gaxes)
+{
+    HaloSrc hs;
+#pragma unroll
+    for (int f = 0; f < 6; ++f) {
+        const int a = f >> 1;
+        const int n = (gaxes >> a) & 1 ? __builtin_amdgcn_readfirstlane(nbr[p * 6 + f]) : -1;
+        const int64_t step = a == 0 ? ((f & 1) ? -10 : 8) : ((f & 1) ? -9 : 9) * (a == 1 ? YS : ZS);
+        hs.d[f] = n >= 0 ? (int64_t)(n - p) * PS + step : 0;
+    }
+    return hs;
+}
+
 // The staging copies of one lane.  A slot's LDS_PAIRS 16-byte pairs (own planes first: 45 rows of
-// LPAIRS pairs, where with an 18-double pitch the ninth pair of a row repeats its eighth; then the
+// LPAIRS pairs; then the
 // halo rows: pair e being plane e / 45 (0..2 below, 3..5 above), row (e / 5) % 9, columns
 // 2 + 2 (e % 5)) are contiguous in LDS, so wave w copies chunks w, w + 4, w + 8 of 64 pairs.  The
 // source addresses of a lane's copies are the same in every slot up to the slot stride: they are
@@ -76,7 +119,9 @@ struct Stager {
 };
 
 // slab sl of the patch at qp; the rows y <= 2 and y >= 12 come from the y faces' sources, planes
-// outside the patch from the z faces' sources
+// outside the patch from the z faces' sources (the x halos of those rows are never read: with XG
+// their pairs repeat the row's first and last interior ones)
+template <int XG>
 __device__ __forceinline__ Stager lds_stager(const double *__restrict__ qp, int sl, const HaloSrc &hs)
 {
     Stager g;
@@ -88,13 +133,21 @@ __device__ __forceinline__ Stager lds_stager(const double *__restrict__ qp, int 
         int64_t d;  // selects, not an index into hs.d: a lane-dependent index would put the array in memory
         if (q < LDS_OWN_PAIRS) {
             const int r = q / LPAIRS, j = q % LPAIRS, y = r % 15;
-            e = (3 + 3 * sl) * ZS + r * XS + 2 * (j < 8 ? j : 7);
-            d = y <= 2 ? hs.d[0] : (y >= 12 ? hs.d[1] : 0);
+            int x;
+            if (XG) {
+                const bool in = y >= 3 && y <= 11, lo = j < 2, hi = j >= 7;
+                d = y <= 2 ? hs.d[2] : (y >= 12 ? hs.d[3] : (lo ? hs.d[0] : (hi ? hs.d[1] : 0)));
+                x = lo ? (in ? 2 * j : 2) : (hi ? (in ? 2 * j - 2 : 10) : 2 * j - 2);
+            } else {
+                d = y <= 2 ? hs.d[2] : (y >= 12 ? hs.d[3] : 0);
+                x = 2 * (j < 8 ? j : 7);
+            }
+            e = (3 + 3 * sl) * ZS + r * XS + x;
         } else {
             const int h = q - LDS_OWN_PAIRS, hp = h / 45, row = (h / 5) % 9, pr = h % 5;
             const int z = hp < 3 ? 3 * sl + hp : 3 * sl + 3 + hp;
             e = z * ZS + (row + 3) * YS + 2 + 2 * pr;
-            d = z <= 2 ? hs.d[2] : (z >= 12 ? hs.d[3] : 0);
+            d = z <= 2 ? hs.d[4] : (z >= 12 ? hs.d[5] : 0);
         }
         g.src[i] = qp + e + d;
     }
@@ -139,18 +192,22 @@ __device__ __forceinline__ void lds_round(double *lds, const int (&slots)[N], co
 }
 
 // One cell's view of the staged slab.
+template <int XG>
 struct LdsCell {
     const double *s;  // LDS base
-    int c;            // index of the cell in the own planes: zl * 240 + y * 16 + x
+    int c;            // index of the cell in the own planes: zl * LPLANE + y * LROW + x (+ 2 with XG)
+    int xo[7];        // with XG, index of the x-neighbour at offset k - 3
     int zo[7];        // index of the z-neighbour at offset k - 3
     double i12[3];    // 1 / (12 dx_a)
     double koc[3];    // eps / (64 dx_a)
 };
 
-__device__ __forceinline__ double lv(const LdsCell &c, int b, int a, int k)
+template <int XG>
+__device__ __forceinline__ double lv(const LdsCell<XG> &c, int b, int a, int k)
 {
     const double *f = c.s + b * LDS_SLOT;
-    return a == 0 ? f[c.c + k] : (a == 1 ? f[c.c + k * LROW] : f[c.zo[k + 3]]);
+    return k == 0 ? f[c.c]
+                  : (a == 0 ? f[XG ? c.xo[k + 3] : c.c + k] : (a == 1 ? f[c.c + k * LROW] : f[c.zo[k + 3]]));
 }
 
 // Box coordinates x, y and plane zl of the cell that lane tid (0..255) of a slab's work-group takes
@@ -166,24 +223,31 @@ __device__ __forceinline__ bool slab_cell(int tid, int &x, int &y, int &zl)
 }
 
 // The LDS offsets of cell (x, y) (box indices) in plane zl (0..2) of the staged slab: its own
-// index and those of its seven z-neighbours (own planes, or the halo rows below and above).
-__device__ __forceinline__ void lds_cell_offsets(LdsCell &C, int x, int y, int zl)
+// index, those of its x-neighbours (own columns, or the halo groups; hs tells which are gathered) and
+// those of its z-neighbours (own planes, or the halo rows below and above).
+template <int XG>
+__device__ __forceinline__ void lds_cell_offsets(LdsCell<XG> &C, int x, int y, int zl, const HaloSrc &hs)
 {
-    C.c = zl * LPLANE + y * LROW + x;
+    const int row = zl * LPLANE + y * LROW, own = XG ? 2 : 0;
+    const int lo = XG && hs.d[0] != 0 ? 1 : 0, hi = XG ? (hs.d[1] != 0 ? 3 : 2) : 0;
+    C.c = row + x + own;
 #pragma unroll
     for (int k = -3; k <= 3; ++k) {
-        const int z2 = zl + k;
-        C.zo[k + 3] = (z2 >= 0 && z2 <= 2) ? z2 * LPLANE + y * LROW + x
+        const int x2 = x + k, z2 = zl + k;
+        C.xo[k + 3] = row + x2 + (x2 < 3 ? lo : (x2 > 11 ? hi : own));
+        C.zo[k + 3] = (z2 >= 0 && z2 <= 2) ? z2 * LPLANE + y * LROW + x + own
                                             : LDS_OWN + (z2 < 0 ? z2 + 3 : z2) * 90 + (y - 3) * LDS_HROW + (x - 2);
     }
 }
 
-__device__ __forceinline__ double fd(const LdsCell &c, int b, int a)
+template <int XG>
+__device__ __forceinline__ double fd(const LdsCell<XG> &c, int b, int a)
 {
     return (8.0 * (lv(c, b, a, 1) - lv(c, b, a, -1)) - (lv(c, b, a, 2) - lv(c, b, a, -2))) * c.i12[a];
 }
 
-__device__ __forceinline__ double ko_axis_lds(const LdsCell &c, int b, int a)
+template <int XG>
+__device__ __forceinline__ double ko_axis_lds(const LdsCell<XG> &c, int b, int a)
 {
 #if CCZ4_KO_PRINTED_ORDER
 #pragma clang fp contract(off)
@@ -196,37 +260,36 @@ __device__ __forceinline__ double ko_axis_lds(const LdsCell &c, int b, int a)
 #endif
 }
 
-__device__ __forceinline__ double ko(const LdsCell &c, int b)
+template <int XG>
+__device__ __forceinline__ double ko(const LdsCell<XG> &c, int b)
 {
     const double kx = c.koc[0] * ko_axis_lds(c, b, 0), ky = c.koc[1] * ko_axis_lds(c, b, 1),
                  kz = c.koc[2] * ko_axis_lds(c, b, 2);
     return (kx + ky) + kz;
 }
 
-__device__ __forceinline__ double adv(const LdsCell &c, int b, const double be[3])
-{
-    return be[0] * fd(c, b, 0) + be[1] * fd(c, b, 1) + be[2] * fd(c, b, 2);
-}
-
-// Output sinks of the slab evaluation: put(v, r) receives the complete right-hand side of slot v
-// (algebra, advection and KO) of the lane's cell, at offset o of the patch box.
+// Output sinks of the slab evaluation receive the complete right-hand sides (algebra, advection and
+// KO) of the lane's cell, a round's slots at a time.
 struct LdsRhsSink {
-    double *__restrict__ kb;
-    int o;
+    PatchBuf kb;
+    uint32_t ob;
     int so;  // second-order formulation: the auxiliaries' right-hand sides are 0
+    __device__ __forceinline__ void finish() {}
+    // A round's outputs in two halves (see rhs_slab_lds): the RHS alone reads nothing.
+    template <int N, typename Own>
+    __device__ __forceinline__ void load(const int (&)[N], double (&)[N], double (&)[N], Own) {}
     // K is written once and not read again in this launch, and no other work-group writes the
     // same lines: nontemporal stores keep the staged lines in L2 (2% per launch).
-    __device__ __forceinline__ void put(int v, double r) { __builtin_nontemporal_store(r, kb + v * CS + o); }
-    __device__ __forceinline__ void finish() {}
-    // A round's outputs in two halves (see flush below): the RHS alone reads nothing.
     template <int N>
-    __device__ __forceinline__ void load(const int (&)[N], double (&)[N], double (&)[N]) {}
-    template <int N>
-    __device__ __forceinline__ void store(const int (&slots)[N], const double (&r)[N], const double (&)[N],
+    __device__ __forceinline__ void store(const int (&slots)[N], double (&r)[N], const double (&)[N],
                                           const double (&)[N])
     {
+        if (so)
 #pragma unroll
-        for (int j = 0; j < N; ++j) put(slots[j], (so && aux_slot(slots[j])) ? 0.0 : r[j]);
+            for (int j = 0; j < N; ++j)
+                if (aux_slot(slots[j])) r[j] = 0.0;
+#pragma unroll
+        for (int j = 0; j < N; ++j) kb.store<BUF_NT>(r[j], ob, slots[j]);
     }
 };
 
@@ -258,19 +321,24 @@ __device__ __forceinline__ void dD_accumulate(const double d[3], int j, const T 
 
 // An opaque copy of the cell's offsets, so that loads of one block of the algebra are neither
 // merged with nor hoisted above those of another (this bounds the registers each block holds).
-__device__ __forceinline__ LdsCell fresh(const LdsCell &c)
+template <int XG>
+__device__ __forceinline__ LdsCell<XG> fresh(const LdsCell<XG> &c)
 {
-    LdsCell r = c;
+    LdsCell<XG> r = c;
     asm volatile("" : "+v"(r.c));
 #pragma unroll
-    for (int k = 0; k < 7; ++k) asm volatile("" : "+v"(r.zo[k]));
+    for (int k = 0; k < 7; ++k) {
+        if (k == 3) continue;
+        if (XG) asm volatile("" : "+v"(r.xo[k]));
+        asm volatile("" : "+v"(r.zo[k]));
+    }
     return r;
 }
 
-__device__ __forceinline__ int fresh(int o)
+__device__ __forceinline__ uint32_t fresh(uint32_t ob)
 {
-    asm volatile("" : "+v"(o));
-    return o;
+    asm volatile("" : "+v"(ob));
+    return ob;
 }
 
 // The pointwise metric of the cell, its slots read by ld(v): g, its inverse and its determinant.
@@ -287,18 +355,19 @@ __device__ __forceinline__ void load_metric_with(Ld ld, double gd[6], double igd
     }
 }
 
-// ... of the cell at offset o of the patch box
+// ... of the cell at byte offset ob of the patch's slots
 template <typename T>
-__device__ __forceinline__ void load_metric(const double *__restrict__ qp, int o, double gd[6], double igd[6],
+__device__ __forceinline__ void load_metric(const PatchBuf &qp, uint32_t ob, double gd[6], double igd[6],
                                             double &detg, T g[6], T ig[6])
 {
-    load_metric_with<T>([&](int v) -> double { return qp[v * CS + o]; }, gd, igd, detg, g, ig);
+    load_metric_with<T>([&](int v) -> double { return qp.load(ob, v); }, gd, igd, detg, g, ig);
 }
 
 // The LDS buffer that holds slot v during round r of rhs_slab_lds, or -1 (see the round lists).
 __device__ __forceinline__ constexpr int round_buffer(int r, int v)
 {
     if (r == 1) return (v >= SAT && v < SAT + 6) ? v - SAT : ((v >= SB && v < SB + 9) ? 6 + v - SB : -1);
+    if (r == 2) return v >= SD && v < SD + 15 ? v - SD : -1;
     if (r == 3)
         return (v >= SD + 15 && v < SD + 18) ? v - SD - 15
                : (v >= SP && v < SP + 3)     ? 3 + v - SP
@@ -318,18 +387,13 @@ __device__ __forceinline__ constexpr int round_buffer(int r, int v)
 }
 
 // Pointwise value of slot v at the lane's cell during round R: from the staged copy in LDS when
-// the round stages v (the same double), else from the patch box at offset o.
-#ifndef CCZ4_PW_LDS
-#define CCZ4_PW_LDS 1
-#endif
-template <int R>
-__device__ __forceinline__ double pw(const double *__restrict__ qp, int o, const LdsCell &C, int v)
+// the round stages v (the same double), else from the patch.
+template <int R, int XG>
+__device__ __forceinline__ double pw(const PatchBuf &qp, uint32_t ob, const LdsCell<XG> &C, int v)
 {
-    if (CCZ4_PW_LDS) {
-        const int b = round_buffer(R, v);
-        if (b >= 0) return C.s[b * LDS_SLOT + C.c];
-    }
-    return qp[v * CS + o];
+    const int b = round_buffer(R, v);
+    if (b >= 0) return C.s[b * LDS_SLOT + C.c];
+    return qp.load(ob, v);
 }
 
 // The three FD4 derivatives and the Kreiss-Oliger sum of staged buffer b at the lane's cell,
@@ -341,7 +405,8 @@ struct SlotDeriv {
     double a;  // advection beta^k d_k (central or lopsided), with the 4-argument form only
 };
 
-__device__ __forceinline__ SlotDeriv stencils(const LdsCell &c, int b)
+template <int XG>
+__device__ __forceinline__ SlotDeriv stencils(const LdsCell<XG> &c, int b)
 {
     SlotDeriv r;
 #pragma unroll
@@ -355,8 +420,8 @@ __device__ __forceinline__ SlotDeriv stencils(const LdsCell &c, int b)
 // ... and the advection term with shift be: the central derivatives (LOP = 0), or the lopsided
 // stencils of App. D (LOP = 1, pairing `mode` as RhsParams::advection) from the same staged
 // points.  LOP is a template parameter so that the central kernel carries no lopsided code.
-template <int LOP>
-__device__ __forceinline__ SlotDeriv stencils(const LdsCell &c, int b, const double be[3], int32_t mode)
+template <int LOP, int XG>
+__device__ __forceinline__ SlotDeriv stencils(const LdsCell<XG> &c, int b, const double be[3], int32_t mode)
 {
     SlotDeriv r;
 #pragma unroll
@@ -393,8 +458,8 @@ __device__ __forceinline__ void keep(double &r, double v)
 // Round 3's Ghat^i sector: its right-hand side (ro3[11..13]), the part of b^i's right-hand side it
 // shares (rGb) and the pointwise part of the gt_ij equation (pwG), from the cell's metric, D, At,
 // B, A, P / phi, the Christoffel symbols and Z, and the contractions carried from rounds 1 and 2.
-template <typename T, int LOP>
-__device__ __forceinline__ void ghat_sector(const LdsCell &C, const RhsParams &p, const double be[3], const T g[6],
+template <typename T, int LOP, int XG>
+__device__ __forceinline__ void ghat_sector(const LdsCell<XG> &C, const RhsParams &p, const double be[3], const T g[6],
                                             const T ig[6], const double gd[6], double detg, const T (&D)[3][6],
                                             const T (&Gt)[3][6], const T Gtv[3], const T At[6], const T (&Am)[3][3],
                                             const T (&Bm)[3][3], const T A[3], const T Ph[3], T trB, T al, T Kt, T Th,
@@ -479,11 +544,12 @@ __device__ constexpr int R4_OUT[24] = {SB, SB + 1, SB + 2, SB + 3, SB + 4, SB + 
 // together, and waits for both; the stores are then left in flight over the next barrier.
 // Right-hand side of the lane's cell of slab sl of the patch at qp.  Every lane of the
 // work-group must call this (staging and barriers); only lanes with act = true compute.
-template <typename T, int LOP, typename Sink>
-__device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, double *lds, int sl, bool act, int o0,
-                                             const LdsCell &C0, const RhsParams &p, Sink &snk, const HaloSrc &hs)
+template <typename T, int LOP, int XG, typename Sink>
+__device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, double *lds, int sl, bool act, uint32_t o0,
+                                             const LdsCell<XG> &C0, const RhsParams &p, Sink &snk, const HaloSrc &hs)
 {
-    const Stager sg = lds_stager(qp, sl, hs);
+    const Stager sg = lds_stager<XG>(qp, sl, hs);
+    const PatchBuf qb{qp};
     const bool gdrv = p.shift != 0;
     const T sfac = gdrv ? T(1) : T(0);
     const T cc = cvt<T>(p.c);
@@ -516,14 +582,14 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
     if (act) {
         {  // B: advection + KO, GB^i = gt^kl d_(k B_l)^i, sdBtr_k = d_(k B_l)^l, and the shift
            // terms of the D equations
-            const LdsCell C = fresh(C0);
-            const int o = fresh(o0);
+            const LdsCell<XG> C = fresh(C0);
+            const uint32_t o = fresh(o0);
             double be[3];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) be[k] = qp[(SBETA + k) * CS + o];
+            for (int k = 0; k < 3; ++k) be[k] = qb.load(o, SBETA + k);
             double gd[6], igd[6], detg;
             T g[6], ig[6];
-            load_metric<T>(qp, o, gd, igd, detg, g, ig);
+            load_metric<T>(qb, o, gd, igd, detg, g, ig);
             double dB[3][3][3];  // dB[l][i][k] = d_k B_l^i
 #pragma unroll
             for (int i = 0; i < 3; ++i) GB[i] = sdBtr[i] = T(0);
@@ -569,9 +635,9 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
         }
         CCZ4_PHASE_BARRIER();
         {  // At: advection + KO, d_k tr(At), and the rest of the D equations
-            const LdsCell C = fresh(C0);
-            const int o = fresh(o0);
-            auto q = [&](int v) -> double { return pw<1>(qp, o, C, v); };
+            const LdsCell<XG> C = fresh(C0);
+            const uint32_t o = fresh(o0);
+            auto q = [&](int v) -> double { return pw<1>(qb, o, C, v); };
             double be[3];
 #pragma unroll
             for (int k = 0; k < 3; ++k) be[k] = q(SBETA + k);
@@ -585,7 +651,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
             }
             double gd[6], igd[6], detg;
             T g[6], ig[6];
-            load_metric<T>(qp, o, gd, igd, detg, g, ig);
+            load_metric<T>(qb, o, gd, igd, detg, g, ig);
             T At[6], D[3][6], Bm[3][3], A[3];
 #pragma unroll
             for (int s = 0; s < 6; ++s) At[s] = cvt<T>(q(SAT + s));
@@ -646,14 +712,14 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
         lds_round(lds, r2, sg);
     }
     if (act) {
-        const LdsCell C = fresh(C0);
-        const int o = fresh(o0);
+        const LdsCell<XG> C = fresh(C0);
+        const uint32_t o = fresh(o0);
         double gd[6], igd[6], detg;
         T g[6], ig[6];
-        load_metric<T>(qp, o, gd, igd, detg, g, ig);
+        load_metric<T>(qb, o, gd, igd, detg, g, ig);
         double be[3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) be[k] = qp[(SBETA + k) * CS + o];
+        for (int k = 0; k < 3; ++k) be[k] = qb.load(o, SBETA + k);
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
 #pragma unroll
@@ -671,27 +737,27 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
     {
         const int r3[14] = {SD + 15, SD + 16, SD + 17, SP, SP + 1, SP + 2, SA, SA + 1, SA + 2,
                             SGHAT, SGHAT + 1, SGHAT + 2, SK, STHETA};
-        double qa[15], qb[15];
-        if (act) snk.load(R2_OUT, qa, qb);
+        double qa[15], qc[15];
+        if (act) snk.load(R2_OUT, qa, qc, [&](int v) -> double { return pw<2>(qb, o0, C0, v); });
         lds_issue(lds, r3, sg);
         __builtin_amdgcn_s_waitcnt(0);  // the sink's loads and this wave's copies have landed
-        if (act) snk.store(R2_OUT, ro2, qa, qb);
+        if (act) snk.store(R2_OUT, ro2, qa, qc);
     }
     __syncthreads();  // every wave's copies have landed; the stores may still be in flight
 
     // ------------------------------------------------------------ round 3
     // buffers: 0..2 D_zyy, D_zyz, D_zzz; 3..5 P; 6..8 A; 9..11 Ghat; 12 K; 13 Theta
     if (act) {
-        const LdsCell C = fresh(C0);
-        const int o = fresh(o0);
-        auto q = [&](int v) -> double { return pw<3>(qp, o, C, v); };
+        const LdsCell<XG> C = fresh(C0);
+        const uint32_t o = fresh(o0);
+        auto q = [&](int v) -> double { return pw<3>(qb, o, C, v); };
         double be[3];
 #pragma unroll
         for (int k = 0; k < 3; ++k) be[k] = q(SBETA + k);
         {
             double gd[6], igd[6], detg;
             T g[6], ig[6];
-            load_metric<T>(qp, o, gd, igd, detg, g, ig);
+            load_metric<T>(qb, o, gd, igd, detg, g, ig);
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
                 const SlotDeriv sd = stencils<LOP>(C, j, be, p.advection);
@@ -700,11 +766,11 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
             }
         }
         {  // ---- Ricci sector: At, K, Theta; the curl term of B
-            const int o1 = fresh(o);
-            auto q1 = [&](int v) -> double { return pw<3>(qp, o1, C, v); };
+            const uint32_t o1 = fresh(o);
+            auto q1 = [&](int v) -> double { return pw<3>(qb, o1, C, v); };
             double gd[6], igd[6], detg;
             T g[6], ig[6];
-            load_metric<T>(qp, o1, gd, igd, detg, g, ig);
+            load_metric<T>(qb, o1, gd, igd, detg, g, ig);
             const double phid = q1(SPHI), iphid = 1.0 / phid;
             double Pphid[3];
 #pragma unroll
@@ -917,16 +983,16 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
                     }
             }
             if constexpr (GHAT_IN_RICCI)  // the same metric, D, At, B, A, P / phi and Christoffel symbols
-                ghat_sector<T, LOP>(C, p, be, g, ig, gd, detg, D, Gt, Gtv, At, Am, Bm, A, Pphi, trB, al, Kt, Th, Zl, GB,
+                ghat_sector<T, LOP, XG>(C, p, be, g, ig, gd, detg, D, Gt, Gtv, At, Am, Bm, A, Pphi, trB, al, Kt, Th, Zl, GB,
                                     sdBtr, dtrA, red, sfac, ro3, rGb, pwG);
         }
         CCZ4_PHASE_BARRIER();
         if constexpr (!GHAT_IN_RICCI) {  // ---- Ghat^i, and the part of b^i it shares
-            const int o1 = fresh(o);
-            auto q1 = [&](int v) -> double { return pw<3>(qp, o1, C, v); };
+            const uint32_t o1 = fresh(o);
+            auto q1 = [&](int v) -> double { return pw<3>(qb, o1, C, v); };
             double gd[6], igd[6], detg;
             T g[6], ig[6];
-            load_metric<T>(qp, o1, gd, igd, detg, g, ig);
+            load_metric<T>(qb, o1, gd, igd, detg, g, ig);
             T D[3][6], At[6];
 #pragma unroll
             for (int k = 0; k < 3; ++k)
@@ -960,13 +1026,13 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
 #pragma unroll
             for (int i = 0; i < 3; ++i)
                 Zl[i] = T(0.5) * (g[sym(i, 0)] * dG[0] + g[sym(i, 1)] * dG[1] + g[sym(i, 2)] * dG[2]);
-            ghat_sector<T, LOP>(C, p, be, g, ig, gd, detg, D, Gt, Gtv, At, Am, Bm, A, Ph, trB, al, Kt, Th, Zl, GB, sdBtr,
+            ghat_sector<T, LOP, XG>(C, p, be, g, ig, gd, detg, D, Gt, Gtv, At, Am, Bm, A, Ph, trB, al, Kt, Th, Zl, GB, sdBtr,
                                 dtrA, red, sfac, ro3, rGb, pwG);
         }
         CCZ4_PHASE_BARRIER();
         {  // ---- A_k and P_k
-            const int o1 = fresh(o);
-            auto q1 = [&](int v) -> double { return pw<3>(qp, o1, C, v); };
+            const uint32_t o1 = fresh(o);
+            auto q1 = [&](int v) -> double { return pw<3>(qb, o1, C, v); };
             T Bm[3][3], A[3], P[3];
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
@@ -1013,20 +1079,20 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
     {
         const int r4[14] = {SBB, SBB + 1, SBB + 2, SG, SG + 1, SG + 2, SG + 3, SG + 4, SG + 5,
                             SALPHA, SBETA, SBETA + 1, SBETA + 2, SPHI};
-        double qa[20], qb[20];
-        if (act) snk.load(R3_OUT, qa, qb);
+        double qa[20], qc[20];
+        if (act) snk.load(R3_OUT, qa, qc, [&](int v) -> double { return pw<3>(qb, o0, C0, v); });
         lds_issue(lds, r4, sg);
         __builtin_amdgcn_s_waitcnt(0);  // the sink's loads and this wave's copies have landed
-        if (act) snk.store(R3_OUT, ro3, qa, qb);
+        if (act) snk.store(R3_OUT, ro3, qa, qc);
     }
     __syncthreads();  // every wave's copies have landed; the stores may still be in flight
 
     // ------------------------------------------------------------ round 4
     // buffers: 0..2 b; 3..8 gt; 9 alpha; 10..12 beta; 13 phi
     if (act) {
-        const LdsCell C = fresh(C0);
-        const int o = fresh(o0);
-        auto q = [&](int v) -> double { return pw<4>(qp, o, C, v); };
+        const LdsCell<XG> C = fresh(C0);
+        const uint32_t o = fresh(o0);
+        auto q = [&](int v) -> double { return pw<4>(qb, o, C, v); };
         double be[3];
 #pragma unroll
         for (int k = 0; k < 3; ++k) be[k] = q(SBETA + k);
@@ -1067,10 +1133,10 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
         keep(ro4[23], 0.0);
     }
     {
-        double qa[24], qb[24];
+        double qa[24], qc[24];
         if (act) {
-            snk.load(R4_OUT, qa, qb);
-            snk.store(R4_OUT, ro4, qa, qb);
+            snk.load(R4_OUT, qa, qc, [&](int v) -> double { return pw<4>(qb, o0, C0, v); });
+            snk.store(R4_OUT, ro4, qa, qc);
         }
     }
     if (act) snk.finish();
