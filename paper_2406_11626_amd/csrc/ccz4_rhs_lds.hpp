@@ -341,6 +341,18 @@ __device__ __forceinline__ uint32_t fresh(uint32_t ob)
     return ob;
 }
 
+__device__ __forceinline__ double fresh(double x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+__device__ __forceinline__ float fresh(float x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 // The pointwise metric of the cell, its slots read by ld(v): g, its inverse and its determinant.
 template <typename T, typename Ld>
 __device__ __forceinline__ void load_metric_with(Ld ld, double gd[6], double igd[6], double &detg, T g[6], T ig[6])
@@ -353,14 +365,6 @@ __device__ __forceinline__ void load_metric_with(Ld ld, double gd[6], double igd
         g[s] = cvt<T>(gd[s]);
         ig[s] = cvt<T>(igd[s]);
     }
-}
-
-// ... of the cell at byte offset ob of the patch's slots
-template <typename T>
-__device__ __forceinline__ void load_metric(const PatchBuf &qp, uint32_t ob, double gd[6], double igd[6],
-                                            double &detg, T g[6], T ig[6])
-{
-    load_metric_with<T>([&](int v) -> double { return qp.load(ob, v); }, gd, igd, detg, g, ig);
 }
 
 // The LDS buffer that holds slot v during round r of rhs_slab_lds, or -1 (see the round lists).
@@ -571,6 +575,24 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
     // inputs are at hand (round 4 adds the Kreiss-Oliger sums and f b^i)
     double pwG[6], pwA, pwPhi;
     T bB[3];
+    // Values of the cell that several rounds use, held in registers from round 1 on instead of read
+    // again from memory in each round (the lines have left L2 by then: such reads were a third of a
+    // stage's L2 misses).  With FP64 algebra the register file takes the shift and the metric (a step
+    // on 4096 leaves: 16.19 -> 15.79 ms; with alpha and At, or the nine B, too it spills: 15.88 and
+    // 16.04 ms); with FP32 algebra alpha, At, B and D fit as well, as FP32 values (16.62 -> 15.28 ms).
+    constexpr bool HOLD_ALL = sizeof(T) == 4;
+    double be[3], gd0[6];  // loaded while round 1 is staged
+    {
+        const uint32_t o = fresh(o0);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) be[k] = qb.load(o, SBETA + k);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) gd0[k] = qb.load(o, SG + k);
+    }
+    T al0, At0[HOLD_ALL ? 6 : 1], B0[HOLD_ALL ? 9 : 1], D0[HOLD_ALL ? 18 : 1];
+    auto held_metric = [&](double gd[6], double igd[6], double &detg, T g[6], T ig[6]) {
+        load_metric_with<T>([&](int v) -> double { return fresh(gd0[v - SG]); }, gd, igd, detg, g, ig);
+    };
     double ro2[15], ro3[20], ro4[24];  // each round's outputs, handed to the sink after the round
 
     // ------------------------------------------------------------ round 1: At, B
@@ -583,13 +605,9 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
         {  // B: advection + KO, GB^i = gt^kl d_(k B_l)^i, sdBtr_k = d_(k B_l)^l, and the shift
            // terms of the D equations
             const LdsCell<XG> C = fresh(C0);
-            const uint32_t o = fresh(o0);
-            double be[3];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) be[k] = qb.load(o, SBETA + k);
             double gd[6], igd[6], detg;
             T g[6], ig[6];
-            load_metric<T>(qb, o, gd, igd, detg, g, ig);
+            held_metric(gd, igd, detg, g, ig);
             double dB[3][3][3];  // dB[l][i][k] = d_k B_l^i
 #pragma unroll
             for (int i = 0; i < 3; ++i) GB[i] = sdBtr[i] = T(0);
@@ -638,9 +656,6 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
             const LdsCell<XG> C = fresh(C0);
             const uint32_t o = fresh(o0);
             auto q = [&](int v) -> double { return pw<1>(qb, o, C, v); };
-            double be[3];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) be[k] = q(SBETA + k);
             double dA[6][3];
 #pragma unroll
             for (int s = 0; s < 6; ++s) {
@@ -651,7 +666,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
             }
             double gd[6], igd[6], detg;
             T g[6], ig[6];
-            load_metric<T>(qb, o, gd, igd, detg, g, ig);
+            held_metric(gd, igd, detg, g, ig);
             T At[6], D[3][6], Bm[3][3], A[3];
 #pragma unroll
             for (int s = 0; s < 6; ++s) At[s] = cvt<T>(q(SAT + s));
@@ -666,6 +681,18 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
             const T trB = Bm[0][0] + Bm[1][1] + Bm[2][2];
             const T trAt = tr6(ig, At);
             const T al = cvt<T>(q(SALPHA));
+            if constexpr (HOLD_ALL) {
+                al0 = fresh(al);
+#pragma unroll
+                for (int s = 0; s < 6; ++s) At0[s] = fresh(At[s]);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) B0[3 * k + i] = fresh(Bm[k][i]);
+#pragma unroll
+                    for (int s = 0; s < 6; ++s) D0[6 * k + s] = fresh(D[k][s]);
+                }
+            }
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
                 T Dupk[6];
@@ -713,13 +740,9 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
     }
     if (act) {
         const LdsCell<XG> C = fresh(C0);
-        const uint32_t o = fresh(o0);
         double gd[6], igd[6], detg;
         T g[6], ig[6];
-        load_metric<T>(qb, o, gd, igd, detg, g, ig);
-        double be[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) be[k] = qb.load(o, SBETA + k);
+        held_metric(gd, igd, detg, g, ig);
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
 #pragma unroll
@@ -750,14 +773,10 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
     if (act) {
         const LdsCell<XG> C = fresh(C0);
         const uint32_t o = fresh(o0);
-        auto q = [&](int v) -> double { return pw<3>(qb, o, C, v); };
-        double be[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) be[k] = q(SBETA + k);
         {
             double gd[6], igd[6], detg;
             T g[6], ig[6];
-            load_metric<T>(qb, o, gd, igd, detg, g, ig);
+            held_metric(gd, igd, detg, g, ig);
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
                 const SlotDeriv sd = stencils<LOP>(C, j, be, p.advection);
@@ -770,7 +789,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
             auto q1 = [&](int v) -> double { return pw<3>(qb, o1, C, v); };
             double gd[6], igd[6], detg;
             T g[6], ig[6];
-            load_metric<T>(qb, o1, gd, igd, detg, g, ig);
+            held_metric(gd, igd, detg, g, ig);
             const double phid = q1(SPHI), iphid = 1.0 / phid;
             double Pphid[3];
 #pragma unroll
@@ -798,7 +817,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
 #pragma unroll
             for (int k = 0; k < 3; ++k)
 #pragma unroll
-                for (int s = 0; s < 6; ++s) D[k][s] = cvt<T>(q1(SD + 6 * k + s));
+                for (int s = 0; s < 6; ++s) D[k][s] = HOLD_ALL ? fresh(D0[HOLD_ALL ? 6 * k + s : 0]) : cvt<T>(q1(SD + 6 * k + s));
             T Dup[3][6], Gl[3][6], Gt[3][6], Gtv[3];
             raise_D(ig, D, Dup);
             christoffel(ig, D, Gl, Gt, Gtv);
@@ -902,7 +921,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
                 for (int j = i; j < 3; ++j)
                     DDa[sym(i, j)] = T(0.5) * cvt<T>(fd(C, 6 + j, i) + fd(C, 6 + i, j)) -
                                      (Gam[0][sym(i, j)] * A[0] + Gam[1][sym(i, j)] * A[1] + Gam[2][sym(i, j)] * A[2]);
-            const T al = cvt<T>(q1(SALPHA)), Kt = cvt<T>(q1(SK)), Th = cvt<T>(q1(STHETA));
+            const T al = HOLD_ALL ? fresh(al0) : cvt<T>(q1(SALPHA)), Kt = cvt<T>(q1(SK)), Th = cvt<T>(q1(STHETA));
             T X[6];
 #pragma unroll
             for (int s = 0; s < 6; ++s) X[s] = -DDa[s] + al * RZ[s];
@@ -912,7 +931,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
             const T lapal = phi2 * tr6(ig, DDa);
             T At[6];
 #pragma unroll
-            for (int s = 0; s < 6; ++s) At[s] = cvt<T>(q1(SAT + s));
+            for (int s = 0; s < 6; ++s) At[s] = HOLD_ALL ? fresh(At0[HOLD_ALL ? s : 0]) : cvt<T>(q1(SAT + s));
             T Am[3][3];
 #pragma unroll
             for (int i = 0; i < 3; ++i)
@@ -928,7 +947,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
 #pragma unroll
             for (int k = 0; k < 3; ++k)
 #pragma unroll
-                for (int i = 0; i < 3; ++i) Bm[k][i] = cvt<T>(q1(SB + 3 * k + i));
+                for (int i = 0; i < 3; ++i) Bm[k][i] = HOLD_ALL ? fresh(B0[HOLD_ALL ? 3 * k + i : 0]) : cvt<T>(q1(SB + 3 * k + i));
             const T trB = Bm[0][0] + Bm[1][1] + Bm[2][2];
 #pragma unroll
             for (int i = 0; i < 3; ++i)
@@ -992,14 +1011,14 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
             auto q1 = [&](int v) -> double { return pw<3>(qb, o1, C, v); };
             double gd[6], igd[6], detg;
             T g[6], ig[6];
-            load_metric<T>(qb, o1, gd, igd, detg, g, ig);
+            held_metric(gd, igd, detg, g, ig);
             T D[3][6], At[6];
 #pragma unroll
             for (int k = 0; k < 3; ++k)
 #pragma unroll
-                for (int s = 0; s < 6; ++s) D[k][s] = cvt<T>(q1(SD + 6 * k + s));
+                for (int s = 0; s < 6; ++s) D[k][s] = HOLD_ALL ? fresh(D0[HOLD_ALL ? 6 * k + s : 0]) : cvt<T>(q1(SD + 6 * k + s));
 #pragma unroll
-            for (int s = 0; s < 6; ++s) At[s] = cvt<T>(q1(SAT + s));
+            for (int s = 0; s < 6; ++s) At[s] = HOLD_ALL ? fresh(At0[HOLD_ALL ? s : 0]) : cvt<T>(q1(SAT + s));
             T Dup[3][6], Gl[3][6], Gt[3][6], Gtv[3];
             raise_D(ig, D, Dup);
             christoffel(ig, D, Gl, Gt, Gtv);
@@ -1016,10 +1035,10 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
                 A[k] = cvt<T>(q1(SA + k));
                 Ph[k] = cvt<T>(q1(SP + k) * iphid);
 #pragma unroll
-                for (int i = 0; i < 3; ++i) Bm[k][i] = cvt<T>(q1(SB + 3 * k + i));
+                for (int i = 0; i < 3; ++i) Bm[k][i] = HOLD_ALL ? fresh(B0[HOLD_ALL ? 3 * k + i : 0]) : cvt<T>(q1(SB + 3 * k + i));
             }
             const T trB = Bm[0][0] + Bm[1][1] + Bm[2][2];
-            const T al = cvt<T>(q1(SALPHA)), Kt = cvt<T>(q1(SK)), Th = cvt<T>(q1(STHETA));
+            const T al = HOLD_ALL ? fresh(al0) : cvt<T>(q1(SALPHA)), Kt = cvt<T>(q1(SK)), Th = cvt<T>(q1(STHETA));
             T dG[3], Zl[3];
 #pragma unroll
             for (int i = 0; i < 3; ++i) dG[i] = cvt<T>(q1(SGHAT + i)) - Gtv[i];
@@ -1039,10 +1058,10 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
                 A[k] = cvt<T>(q1(SA + k));
                 P[k] = cvt<T>(q1(SP + k));
 #pragma unroll
-                for (int i = 0; i < 3; ++i) Bm[k][i] = cvt<T>(q1(SB + 3 * k + i));
+                for (int i = 0; i < 3; ++i) Bm[k][i] = HOLD_ALL ? fresh(B0[HOLD_ALL ? 3 * k + i : 0]) : cvt<T>(q1(SB + 3 * k + i));
             }
             const T trB = Bm[0][0] + Bm[1][1] + Bm[2][2];
-            const T al = cvt<T>(q1(SALPHA)), Kt = cvt<T>(q1(SK)), Th = cvt<T>(q1(STHETA)), K0 = cvt<T>(q1(SK0));
+            const T al = HOLD_ALL ? fresh(al0) : cvt<T>(q1(SALPHA)), Kt = cvt<T>(q1(SK)), Th = cvt<T>(q1(STHETA)), K0 = cvt<T>(q1(SK0));
             const double phid = q1(SPHI);
             const bool onelog = p.slicing == 1;
             const T ga = onelog ? T(2) / al : T(1);
@@ -1093,9 +1112,6 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
         const LdsCell<XG> C = fresh(C0);
         const uint32_t o = fresh(o0);
         auto q = [&](int v) -> double { return pw<4>(qb, o, C, v); };
-        double be[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) be[k] = q(SBETA + k);
         // B_k^i and b^i
         if (gdrv) {
             const T ff = cvt<T>(p.f);
