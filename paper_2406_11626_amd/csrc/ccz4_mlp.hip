@@ -10,6 +10,7 @@
 // as the identity (straight-through).  The bias gradients sum the FP32 gradients.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "ccz4_kernels.hpp"
@@ -23,313 +24,450 @@ constexpr int NIN = MLP_NIN, NINP = 96, NH = MLP_NH, NOUT = MLP_NOUT, NOUTP = 16
 constexpr int OW1 = 0, OB1 = OW1 + NH * NIN, OW2 = OB1 + NH, OB2 = OW2 + NH * NH, OW3 = OB2 + NH,
               OB3 = OW3 + NOUT * NH;
 static_assert(OB3 + NOUT == MLP_NPARAM, "parameter layout");
-constexpr int TILE = 64;  // rows (patches) per work-group, 16 per wave
+constexpr int TILE = 64;  // rows (patches) of four waves, 16 per wave
 
 typedef short bf4_t __attribute__((ext_vector_type(4)));
 typedef float f4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 bfv4_t __attribute__((ext_vector_type(4)));
 
-// FP32 -> BF16, round to nearest, ties to even (NaN -> quiet NaN)
 __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
-__device__ __forceinline__ uint16_t f2bf(float f)
+// FP32 -> BF16, round to nearest, ties to even
+__device__ __forceinline__ bf4_t pack4(f4_t v) { return __builtin_bit_cast(bf4_t, __builtin_convertvector(v, bfv4_t)); }
+
+__device__ __forceinline__ f4_t mma(bf4_t a, bf4_t b, f4_t c)
 {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (u & 0x007fffffu) ? (uint16_t)0x7fc0 : (uint16_t)(u >> 16);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
 }
 
-// One 16 x 16 output tile of C = A B over K (a multiple of 16) on the matrix cores.  A(i, k) and
-// B(k, j) return BF16 bits; lane l supplies A rows l % 16 and B columns l % 16 at the four k of
-// its group l / 16; the result element r of lane l is C(4 (l / 16) + r, l % 16).
-template <typename FA, typename FB>
-__device__ __forceinline__ f4_t mma_tile(FA A, FB B, int K)
-{
-    const int l = threadIdx.x & 63, li = l & 15, lk = (l >> 4) * 4;
-    f4_t acc = {0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        bf4_t a, b;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            a[r] = (short)A(li, k0 + lk + r);
-            b[r] = (short)B(k0 + lk + r, li);
-        }
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
-    }
-    return acc;
-}
-
-struct MlpShared {
-    uint16_t w1[NH][NINP];    // W1, inputs padded to 96
-    uint16_t w2[NH][NH];
-    uint16_t w3[NOUTP][NH];   // W3, outputs padded to 16
-    uint16_t x[TILE][NINP];   // standardised inputs
-    uint16_t a1[TILE][NH];    // BF16 hidden activations
-    uint16_t a2[TILE][NH];
-    float z1[TILE][NH];       // FP32 pre-activations (ReLU masks of the backward pass)
-    float z2[TILE][NH];
-    float z3[TILE][NOUTP];
-    uint16_t db[TILE][NH];    // BF16 pre-activation gradient of the current layer
-    float part[TILE];         // per-row loss
+// Every product runs on one wave's 16 rows with the rows as columns: Z^T = W X^T.  Of a 16 x 16 x 16
+// product lane l (li = l % 16, g = l / 16) supplies A(li, 4 g + r) and B(4 g + r, li), r = 0..3, and
+// holds C(4 g + r, li): unit 16 t + 4 g + r of row li, tile t.  That is the B operand of the next
+// layer's k-chunk t, so the activations and the back-propagated gradients go from product to product
+// in registers, without LDS and without a barrier; the weights are A operands held in registers for
+// all the rows of a wave.  (One work-group per 64 rows with every operand gathered from LDS two bytes
+// at a time, the weights converted again for each, took 45 and 382 us forward for 20,112 and 241,344
+// rows; now 12 and 38 us.)
+struct MlpWeights {
+    bf4_t w1[4][6], w2[4][4], w3[4];  // [tile of 16 units][chunk of 16 inputs]
+    __device__ __forceinline__ bf4_t f1(int t, int c) const { return w1[t][c]; }
+    __device__ __forceinline__ bf4_t f2(int t, int c) const { return w2[t][c]; }
+    __device__ __forceinline__ bf4_t f3(int t) const { return w3[t]; }
 };
 
-// forward pass of one tile of rows [r0, r0 + TILE); returns with z3 (logits) in LDS
-__device__ void mlp_forward_tile(MlpShared &S, const float *__restrict__ prm, const float *__restrict__ norm,
-                                 const float *__restrict__ feat, int64_t n, int64_t r0)
+// (clamped indices and selects: no branch per element)
+__device__ __forceinline__ bf4_t weight_frag(const float *__restrict__ w, int row, int rows, int col, int cols)
 {
-    const int t = threadIdx.x, w = t >> 6, l = t & 63, li = l & 15, lk = (l >> 4) * 4;
-    for (int e = t; e < NH * NINP; e += blockDim.x) {
-        const int j = e / NINP, i = e % NINP;
-        S.w1[j][i] = i < NIN ? f2bf(prm[OW1 + j * NIN + i]) : (uint16_t)0;
-    }
-    for (int e = t; e < NH * NH; e += blockDim.x) S.w2[e / NH][e % NH] = f2bf(prm[OW2 + e]);
-    for (int e = t; e < NOUTP * NH; e += blockDim.x) {
-        const int j = e / NH, i = e % NH;
-        S.w3[j][i] = j < NOUT ? f2bf(prm[OW3 + j * NH + i]) : (uint16_t)0;
-    }
-    for (int e = t; e < TILE * NINP; e += blockDim.x) {
-        const int r = e / NINP, i = e % NINP;
-        uint16_t v = 0;
-        if (i < NIN && r0 + r < n) {
-#pragma clang fp contract(off)
-            const float d = feat[(r0 + r) * NIN + i] - norm[i];
-            v = f2bf(d * norm[NIN + i]);
-        }
-        S.x[r][i] = v;
-    }
-    __syncthreads();
-    // layer 1: rows 16 w .. 16 w + 15 of the tile, four column tiles of 16 hidden units
-    for (int jb = 0; jb < 4; ++jb) {
-        const f4_t c = mma_tile([&](int i, int k) { return S.x[16 * w + i][k]; },
-                                [&](int k, int j) { return S.w1[16 * jb + j][k]; }, NINP);
+    f4_t v;
+    const float *p = w + (row < rows ? row : 0) * cols;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = 16 * w + lk + r, col = 16 * jb + li;
-            const float z = c[r] + prm[OB1 + col];
-            S.z1[row][col] = z;
-            S.a1[row][col] = f2bf(z > 0.f ? z : 0.f);
-        }
+    for (int r = 0; r < 4; ++r) {
+        const float t = p[col + r < cols ? col + r : 0];
+        v[r] = row < rows && col + r < cols ? t : 0.f;
     }
-    __syncthreads();
-    for (int jb = 0; jb < 4; ++jb) {
-        const f4_t c = mma_tile([&](int i, int k) { return S.a1[16 * w + i][k]; },
-                                [&](int k, int j) { return S.w2[16 * jb + j][k]; }, NH);
+    return pack4(v);
+}
+
+__device__ __forceinline__ void load_weights(MlpWeights &W, const float *__restrict__ prm, int li, int g)
+{
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = 16 * w + lk + r, col = 16 * jb + li;
-            const float z = c[r] + prm[OB2 + col];
-            S.z2[row][col] = z;
-            S.a2[row][col] = f2bf(z > 0.f ? z : 0.f);
-        }
+    for (int t = 0; t < 4; ++t) {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) W.w1[t][c] = weight_frag(prm + OW1, 16 * t + li, NH, 16 * c + 4 * g, NIN);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) W.w2[t][c] = weight_frag(prm + OW2, 16 * t + li, NH, 16 * c + 4 * g, NH);
+        W.w3[t] = weight_frag(prm + OW3, li, NOUT, 16 * t + 4 * g, NH);
     }
-    __syncthreads();
-    {
-        const f4_t c = mma_tile([&](int i, int k) { return S.a2[16 * w + i][k]; },
-                                [&](int k, int j) { return S.w3[j][k]; }, NH);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = 16 * w + lk + r, col = li;
-            S.z3[row][col] = col < NOUT ? c[r] + prm[OB3 + col] : 0.f;
+}
+
+// The vectors that every row uses, zero where padded: normalisation and biases.
+struct MlpVectors {
+    float mu[NINP], is[NINP], b1[NH], b2[NH], b3[NOUTP];
+};
+
+__device__ __forceinline__ void load_vectors(MlpVectors &V, const float *__restrict__ prm, const float *__restrict__ norm)
+{
+    for (int i = threadIdx.x; i < NINP; i += blockDim.x) {
+        V.mu[i] = i < NIN ? norm[i] : 0.f;
+        V.is[i] = i < NIN ? norm[NIN + i] : 0.f;
+        if (i < NH) {
+            V.b1[i] = prm[OB1 + i];
+            V.b2[i] = prm[OB2 + i];
         }
+        if (i < NOUTP) V.b3[i] = i < NOUT ? prm[OB3 + i] : 0.f;
     }
     __syncthreads();
 }
 
+__device__ __forceinline__ f4_t vec4(const float *v) { return *reinterpret_cast<const f4_t *>(v); }
+
+// One row's features as loaded: chunk c holds inputs 16 c + 4 g + r (a row is 81 floats: four-byte
+// aligned), zero beyond the last input or row.
+struct MlpRow {
+    f4_t f[6];
+};
+
+__device__ __forceinline__ MlpRow load_row(const float *__restrict__ feat, int64_t row, int64_t n, int g)
+{
+    MlpRow R;
+    const bool in = row < n;
+    const float *f = feat + (in ? row : 0) * NIN + 4 * g;
+#pragma unroll
+    for (int c = 0; c < 5; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) R.f[c][r] = in ? f[16 * c + r] : 0.f;
+    R.f[5] = f4_t{in && g == 0 ? f[80] : 0.f, 0.f, 0.f, 0.f};
+    return R;
+}
+
+// The standardised inputs, x = (feat - mu) * inv_sigma in FP32, then BF16; zero rows beyond n.
+__device__ __forceinline__ void standardise(const MlpVectors &V, const MlpRow &R, bool in, int g, bf4_t x[6])
+{
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+        const f4_t mu = vec4(V.mu + 16 * c + 4 * g), is = vec4(V.is + 16 * c + 4 * g);
+        f4_t v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+#pragma clang fp contract(off)
+            const float d = R.f[c][r] - mu[r];
+            v[r] = in ? d * is[r] : 0.f;
+        }
+        x[c] = pack4(v);
+    }
+}
+
+__device__ __forceinline__ f4_t relu4(f4_t z)
+{
+#pragma unroll
+    for (int r = 0; r < 4; ++r) z[r] = z[r] > 0.f ? z[r] : 0.f;
+    return z;
+}
+
+// z1, z2 (pre-activations), a1, a2 (BF16 activations) and z3 (logits of row li: classes r = 0..2 of the
+// lanes g = 0)
+template <typename Weights>
+__device__ __forceinline__ void mlp_layers(const Weights &W, const MlpVectors &V, int g, const bf4_t x[6], f4_t z1[4],
+                                           bf4_t a1[4], f4_t z2[4], bf4_t a2[4], f4_t &z3)
+{
+#pragma unroll
+    for (int t = 0; t < 4; ++t) z1[t] = f4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < 6; ++c)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) z1[t] = mma(W.f1(t, c), x[c], z1[t]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        z1[t] += vec4(V.b1 + 16 * t + 4 * g);
+        a1[t] = pack4(relu4(z1[t]));
+        z2[t] = f4_t{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) z2[t] = mma(W.f2(t, c), a1[c], z2[t]);
+    z3 = f4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        z2[t] += vec4(V.b2 + 16 * t + 4 * g);
+        a2[t] = pack4(relu4(z2[t]));
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) z3 = mma(W.f3(t), a2[t], z3);
+    z3 += vec4(V.b3 + 4 * g);
+}
+
+// Waves take blocks of 16 rows in turn, the next block's features in flight meanwhile.
 __global__ __launch_bounds__(256) void k_mlp_forward(const float *__restrict__ prm, const float *__restrict__ norm,
                                                      const float *__restrict__ feat, int64_t n,
                                                      float *__restrict__ logits)
 {
-    __shared__ MlpShared S;
-    const int64_t r0 = (int64_t)blockIdx.x * TILE;
-    mlp_forward_tile(S, prm, norm, feat, n, r0);
-    for (int e = threadIdx.x; e < TILE * NOUT; e += blockDim.x) {
-        const int r = e / NOUT, j = e % NOUT;
-        if (r0 + r < n) logits[(r0 + r) * NOUT + j] = S.z3[r][j];
+    __shared__ MlpVectors V;
+    const int l = threadIdx.x & 63, li = l & 15, g = l >> 4;
+    const int64_t waves = (int64_t)gridDim.x * 4, first = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    MlpRow next = load_row(feat, first * 16 + li, n, g);
+    MlpWeights W;
+    load_weights(W, prm, li, g);
+    load_vectors(V, prm, norm);
+    for (int64_t b = first; b * 16 < n; b += waves) {
+        const int64_t row = b * 16 + li;
+        const MlpRow R = next;
+        next = load_row(feat, row + waves * 16, n, g);
+        bf4_t x[6], a1[4], a2[4];
+        f4_t z1[4], z2[4], z3;
+        standardise(V, R, row < n, g, x);
+        mlp_layers(W, V, g, x, z1, a1, z2, a2, z3);
+        if (g == 0 && row < n)
+#pragma unroll
+            for (int j = 0; j < NOUT; ++j) logits[row * NOUT + j] = z3[j];
     }
 }
 
-// Loss and gradient partials of one tile: part[blk][0 .. NPARAM-1] gradient, [NPARAM] loss sum.
+// Rows of one pass of a gradient work-group: 16 for each of its eight waves.
+constexpr int GROWS = 128, GWAVES = 8;
+// The operands of the weight gradients (products over the rows) in LDS, unit by unit with the rows
+// contiguous: a lane writes its 4 x 1 piece of a block and reads four rows of one unit.  The row pitch
+// of 132 spreads the units that a read touches over the banks.
+constexpr int GPITCH = 132;
+struct MlpOperands {
+    uint16_t x[NINP][GPITCH], a1[NH][GPITCH], a2[NH][GPITCH], d1[NH][GPITCH], d2[NH][GPITCH], d3[NOUTP][GPITCH];
+};
+
+__device__ __forceinline__ void put_block(uint16_t (*u)[GPITCH], int unit, int row, bf4_t v)
+{
+#pragma unroll
+    for (int r = 0; r < 4; ++r) u[unit + r][row] = (uint16_t)v[r];
+}
+
+__device__ __forceinline__ bf4_t get_block(const uint16_t (*u)[GPITCH], int unit, int row)
+{
+    return *reinterpret_cast<const bf4_t *>(&u[unit][row]);
+}
+
+// The weights as operands in LDS, one fragment of 64 lanes each (a gradient wave's registers hold its
+// share of the gradients instead), and those of the backward pass, W2^T and W3^T.
+struct MlpFragments {
+    bf4_t w1[4][6][64], w2[4][4][64], w3[4][64], w2t[4][4][64], w3t[4][64];
+};
+struct MlpLdsWeights {
+    const MlpFragments &F;
+    int l;
+    __device__ __forceinline__ bf4_t f1(int t, int c) const { return F.w1[t][c][l]; }
+    __device__ __forceinline__ bf4_t f2(int t, int c) const { return F.w2[t][c][l]; }
+    __device__ __forceinline__ bf4_t f3(int t) const { return F.w3[t][l]; }
+};
+
+// wave w of eight fills its share: tile w % 4 of everything, split by w / 4
+__device__ __forceinline__ void load_fragments(MlpFragments &F, const float *__restrict__ prm, int w, int l)
+{
+    const int li = l & 15, g = l >> 4, t = w & 3;
+    if (w < 4) {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) F.w1[t][c][l] = weight_frag(prm + OW1, 16 * t + li, NH, 16 * c + 4 * g, NIN);
+        F.w3[t][l] = weight_frag(prm + OW3, li, NOUT, 16 * t + 4 * g, NH);
+    } else {
+        f4_t v;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            F.w2[t][c][l] = weight_frag(prm + OW2, 16 * t + li, NH, 16 * c + 4 * g, NH);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = prm[OW2 + (16 * c + 4 * g + r) * NH + 16 * t + li];
+            F.w2t[t][c][l] = pack4(v);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float u = prm[OW3 + (r < NOUT ? r : 0) * NH + 16 * t + li];
+            v[r] = g == 0 && r < NOUT ? u : 0.f;
+        }
+        F.w3t[t][l] = pack4(v);
+    }
+}
+
+// Loss and gradient sums of a work-group's rows: part[blk][0 .. NPARAM-1] gradient, [NPARAM] loss sum.
+// Each wave takes 16 of a pass's 128 rows through the layers and back in registers; the gradients of
+// the weights are products over the rows, whose operands pass through LDS once.  The 44 tiles of 16 x
+// 16 of the weight gradients are shared out: wave w holds tile row w / 2 of W1 and W2 (the column tiles
+// of half w % 2) and, for even w, tile w / 2 of W3, in registers over all passes, so that no sum is
+// taken across waves and a launch leaves at most MLP_GRAD_BLOCKS partials (before, one for every 64
+// rows: 145 MB written and read again for 241,344 rows).  Two waves per SIMD: the layers are chains of
+// dependent products, bound by their latency.  Gradient and reduction of 27 / 4096 / 241,344 rows:
+// 33 / 50 / 559 us with operands gathered element by element, 14 / 17 / 62 us now (109 us with one
+// wave per SIMD that holds all gradients, 113 us with the weights in registers, which then spill).
 // With trace != nullptr, each row also leaves the operands of its matrix products there (as FP32
 // values, MLP_TRACE per row): the BF16 standardised input, the BF16 activations a1 and a2, and the
 // FP32 pre-activation gradients d3, d2 and d1 before their BF16 rounding.
-__global__ __launch_bounds__(256) void k_mlp_grad(const float *__restrict__ prm, const float *__restrict__ norm,
-                                                  const float *__restrict__ feat, const int8_t *__restrict__ tags,
-                                                  int64_t n, float *__restrict__ part, float *__restrict__ trace)
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mlp_grad(
+    const float *__restrict__ prm, const float *__restrict__ norm, const float *__restrict__ feat,
+    const int8_t *__restrict__ tags, int64_t n, float *__restrict__ part, float *__restrict__ trace)
 {
-    __shared__ MlpShared S;
-    __shared__ float d3[TILE][NOUTP];
-    __shared__ float dsum[NH];
-    const int64_t r0 = (int64_t)blockIdx.x * TILE;
-    const int t = threadIdx.x, w = t >> 6, l = t & 63, li = l & 15, lk = (l >> 4) * 4;
-    float *out = part + (int64_t)blockIdx.x * (MLP_NPARAM + 1);
-    mlp_forward_tile(S, prm, norm, feat, n, r0);
-    if (trace) {
-        for (int e = t; e < TILE * (NIN + 2 * NH); e += blockDim.x) {
-            const int r = e / (NIN + 2 * NH), i = e % (NIN + 2 * NH);
-            if (r0 + r >= n) continue;
-            const uint16_t b = i < NIN ? S.x[r][i] : (i < NIN + NH ? S.a1[r][i - NIN] : S.a2[r][i - NIN - NH]);
-            trace[(r0 + r) * MLP_TRACE + i] = bf2f(b);
-        }
-    }
+    __shared__ MlpVectors V;
+    __shared__ __align__(16) MlpOperands S;
+    __shared__ MlpFragments F;
+    __shared__ float bias[GWAVES][2 * NH + NOUT + 1];
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), l = threadIdx.x & 63, li = l & 15, g = l >> 4;
+    const int64_t stride = (int64_t)gridDim.x * GROWS, first = (int64_t)blockIdx.x * GROWS + 16 * w + li;
+    MlpRow next = load_row(feat, first, n, g);
+    int next_tag = first < n ? tags[first] : 0;
+    load_fragments(F, prm, w, l);
+    const MlpLdsWeights W{F, l};
+    load_vectors(V, prm, norm);  // with a barrier
+    const f4_t zero = {0.f, 0.f, 0.f, 0.f};
+    const int ot = w >> 1, half = w & 1;
+    f4_t gw1[3] = {zero, zero, zero}, gw2[2] = {zero, zero}, gw3 = zero;
+    f4_t gb1[4] = {zero, zero, zero, zero}, gb2[4] = {zero, zero, zero, zero}, gb3 = zero;
+    float loss = 0.f;
     const float inv_n = 1.0f / (float)n;
-    // softmax cross-entropy per row
-    if (t < TILE) {
-        float lossr = 0.f;
-        float d[NOUT] = {0.f, 0.f, 0.f};
-        if (r0 + t < n) {
-            const int lab = (int)tags[r0 + t] + 1;  // COARSEN, KEEP, REFINE -> 0, 1, 2
-            const float zm = fmaxf(fmaxf(S.z3[t][0], S.z3[t][1]), S.z3[t][2]);
+    for (int64_t b = (int64_t)blockIdx.x * GROWS; b < n; b += stride) {
+        const int64_t row = b + 16 * w + li;
+        const bool in = row < n;
+        const MlpRow R = next;
+        const int lab = next_tag + 1;  // COARSEN, KEEP, REFINE -> 0, 1, 2
+        bf4_t x[6], a1[4], a2[4];
+        f4_t z1[4], z2[4], z3;
+        standardise(V, R, in, g, x);
+        mlp_layers(W, V, g, x, z1, a1, z2, a2, z3);
+        next = load_row(feat, row + stride, n, g);
+        next_tag = row + stride < n ? tags[row + stride] : 0;
+        // softmax cross-entropy of row li in the lanes g = 0
+        f4_t d3 = zero;
+        if (g == 0 && in) {
+            const float zm = fmaxf(fmaxf(z3[0], z3[1]), z3[2]);
             float e[NOUT], se = 0.f;
 #pragma unroll
             for (int j = 0; j < NOUT; ++j) {
-                e[j] = expf(S.z3[t][j] - zm);
+                e[j] = expf(z3[j] - zm);
                 se += e[j];
             }
-            lossr = -(S.z3[t][lab] - zm - logf(se));
+            const float zl = lab == 0 ? z3[0] : (lab == 1 ? z3[1] : z3[2]);
+            loss += -(zl - zm - logf(se));
 #pragma unroll
-            for (int j = 0; j < NOUT; ++j) d[j] = (e[j] / se - (j == lab ? 1.f : 0.f)) * inv_n;
+            for (int j = 0; j < NOUT; ++j) d3[j] = (e[j] / se - (j == lab ? 1.f : 0.f)) * inv_n;
         }
-        S.part[t] = lossr;
+        gb3 += d3;
+        const bf4_t d3b = pack4(d3);
+        // d2 = (W3^T d3) [z2 > 0], d1 = (W2^T d2) [z1 > 0]
+        bf4_t d2b[4], d1b[4];
+        f4_t d2[4], d1[4];
 #pragma unroll
-        for (int j = 0; j < NOUTP; ++j) {
-            d3[t][j] = j < NOUT ? d[j] : 0.f;
-            S.db[t][j] = j < NOUT ? f2bf(d[j]) : (uint16_t)0;
+        for (int t = 0; t < 4; ++t) {
+            d2[t] = mma(F.w3t[t][l], d3b, zero);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) d2[t][r] = z2[t][r] > 0.f ? d2[t][r] : 0.f;
+            gb2[t] += d2[t];
+            d2b[t] = pack4(d2[t]);
+            d1[t] = zero;
         }
-        if (trace && r0 + t < n)
 #pragma unroll
-            for (int j = 0; j < NOUT; ++j) trace[(r0 + t) * MLP_TRACE + NIN + 2 * NH + j] = d[j];
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) d1[t] = mma(F.w2t[t][c][l], d2b[c], d1[t]);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) d1[t][r] = z1[t][r] > 0.f ? d1[t][r] : 0.f;
+            gb1[t] += d1[t];
+            d1b[t] = pack4(d1[t]);
+        }
+        if (trace && in) {
+            float *tr = trace + row * MLP_TRACE;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+#pragma unroll
+                for (int c = 0; c < 6; ++c)
+                    if (16 * c + 4 * g + r < NIN) tr[16 * c + 4 * g + r] = bf2f((uint16_t)x[c][r]);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int h = 16 * t + 4 * g + r;
+                    tr[NIN + h] = bf2f((uint16_t)a1[t][r]);
+                    tr[NIN + NH + h] = bf2f((uint16_t)a2[t][r]);
+                    tr[NIN + 2 * NH + NOUT + h] = d2[t][r];
+                    tr[NIN + 3 * NH + NOUT + h] = d1[t][r];
+                }
+                if (g == 0 && r < NOUT) tr[NIN + 2 * NH + r] = d3[r];
+            }
+        }
+        // the operands of the weight gradients
+        const int at = 16 * w + li;
+#pragma unroll
+        for (int c = 0; c < 6; ++c) put_block(S.x, 16 * c + 4 * g, at, x[c]);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            put_block(S.a1, 16 * t + 4 * g, at, a1[t]);
+            put_block(S.a2, 16 * t + 4 * g, at, a2[t]);
+            put_block(S.d1, 16 * t + 4 * g, at, d1b[t]);
+            put_block(S.d2, 16 * t + 4 * g, at, d2b[t]);
+        }
+        put_block(S.d3, 4 * g, at, d3b);
+        __syncthreads();
+        // gW1 = d1 x^T, gW2 = d2 a1^T, gW3 = d3 a2^T over the pass's rows
+#pragma unroll
+        for (int k = 0; k < GROWS; k += 16) {
+            const bf4_t p1 = get_block(S.d1, 16 * ot + li, k + 4 * g), p2 = get_block(S.d2, 16 * ot + li, k + 4 * g);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) gw1[c] = mma(p1, get_block(S.x, 16 * (3 * half + c) + li, k + 4 * g), gw1[c]);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) gw2[c] = mma(p2, get_block(S.a1, 16 * (2 * half + c) + li, k + 4 * g), gw2[c]);
+            if (half == 0)
+                gw3 = mma(get_block(S.d3, li, k + 4 * g), get_block(S.a2, 16 * ot + li, k + 4 * g), gw3);
+        }
+        __syncthreads();  // the operands are read before the next pass writes its own
+    }
+    // the bias gradients and the loss: over the 16 lanes of a group, then over the waves, in order
+#pragma unroll
+    for (int m = 1; m < 16; m <<= 1) {
+        loss += __shfl_xor(loss, m);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            gb3[r] += __shfl_xor(gb3[r], m);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                gb1[t][r] += __shfl_xor(gb1[t][r], m);
+                gb2[t][r] += __shfl_xor(gb2[t][r], m);
+            }
+        }
+    }
+    if (li == 0) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                bias[w][16 * t + 4 * g + r] = gb1[t][r];
+                bias[w][NH + 16 * t + 4 * g + r] = gb2[t][r];
+            }
+        if (g == 0) {
+#pragma unroll
+            for (int j = 0; j < NOUT; ++j) bias[w][2 * NH + j] = gb3[j];
+            bias[w][2 * NH + NOUT] = loss;
+        }
+    }
+    float *out = part + (int64_t)blockIdx.x * (MLP_NPARAM + 1);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int o = 16 * ot + 4 * g + r;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const int i = 16 * (3 * half + c) + li;
+            if (i < NIN) out[OW1 + o * NIN + i] = gw1[c][r];
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c) out[OW2 + o * NH + 16 * (2 * half + c) + li] = gw2[c][r];
+        if (half == 0 && 4 * g + r < NOUT) out[OW3 + (4 * g + r) * NH + 16 * ot + li] = gw3[r];
     }
     __syncthreads();
-    if (t == 0) {
+    const int t = threadIdx.x;
+    if (t < 2 * NH + NOUT + 1) {
         float s = 0.f;
-        for (int r = 0; r < TILE; ++r) s += S.part[r];
-        out[MLP_NPARAM] = s;
-    }
-    if (t < NOUT) {
-        float s = 0.f;
-        for (int r = 0; r < TILE; ++r) s += d3[r][t];
-        out[OB3 + t] = s;
-    }
-    // gW3[j][h] = sum_rows d3b[row][j] a2[row][h]: wave w takes hidden units 16 w .. 16 w + 15
-    {
-        const f4_t c = mma_tile([&](int i, int k) { return S.db[k][i]; },
-                                [&](int k, int j) { return S.a2[k][16 * w + j]; }, TILE);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = lk + r, h = 16 * w + li;
-            if (j < NOUT) out[OW3 + j * NH + h] = c[r];
-        }
-    }
-    // d2 = (d3b W3) * [z2 > 0]
-    float d2v[4][4];
-    for (int hb = 0; hb < 4; ++hb) {
-        const f4_t c = mma_tile([&](int i, int k) { return S.db[16 * w + i][k]; },
-                                [&](int k, int j) { return S.w3[k][16 * hb + j]; }, NOUTP);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = 16 * w + lk + r, h = 16 * hb + li;
-            d2v[hb][r] = S.z2[row][h] > 0.f ? c[r] : 0.f;
-        }
-    }
-    __syncthreads();  // every wave is done reading d3b
-    for (int hb = 0; hb < 4; ++hb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = 16 * w + lk + r, h = 16 * hb + li;
-            S.z2[row][h] = d2v[hb][r];  // z2 is no longer needed: keep the FP32 d2 there
-            S.db[row][h] = f2bf(d2v[hb][r]);
-        }
-    __syncthreads();
-    if (t < NH) {
-        float s = 0.f;
-        for (int r = 0; r < TILE; ++r) s += S.z2[r][t];
-        dsum[t] = s;
-    }
-    if (trace)
-        for (int e = t; e < TILE * NH; e += blockDim.x) {
-            const int r = e / NH, h = e % NH;
-            if (r0 + r < n) trace[(r0 + r) * MLP_TRACE + NIN + 2 * NH + NOUT + h] = S.z2[r][h];
-        }
-    // gW2[o][i] = sum_rows d2b[row][o] a1[row][i]: 16 tiles, four per wave
-    for (int q = 0; q < 4; ++q) {
-        const int ob = w, ib = q;
-        const f4_t c = mma_tile([&](int i, int k) { return S.db[k][16 * ob + i]; },
-                                [&](int k, int j) { return S.a1[k][16 * ib + j]; }, TILE);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) out[OW2 + (16 * ob + lk + r) * NH + 16 * ib + li] = c[r];
-    }
-    __syncthreads();
-    if (t < NH) out[OB2 + t] = dsum[t];
-    // d1 = (d2b W2) * [z1 > 0]
-    float d1v[4][4];
-    for (int ib = 0; ib < 4; ++ib) {
-        const f4_t c = mma_tile([&](int i, int k) { return S.db[16 * w + i][k]; },
-                                [&](int k, int j) { return S.w2[k][16 * ib + j]; }, NH);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = 16 * w + lk + r, h = 16 * ib + li;
-            d1v[ib][r] = S.z1[row][h] > 0.f ? c[r] : 0.f;
-        }
-    }
-    __syncthreads();
-    for (int ib = 0; ib < 4; ++ib)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = 16 * w + lk + r, h = 16 * ib + li;
-            S.z1[row][h] = d1v[ib][r];
-            S.db[row][h] = f2bf(d1v[ib][r]);
-        }
-    __syncthreads();
-    if (t < NH) {
-        float s = 0.f;
-        for (int r = 0; r < TILE; ++r) s += S.z1[r][t];
-        out[OB1 + t] = s;
-    }
-    if (trace)
-        for (int e = t; e < TILE * NH; e += blockDim.x) {
-            const int r = e / NH, h = e % NH;
-            if (r0 + r < n) trace[(r0 + r) * MLP_TRACE + NIN + 3 * NH + NOUT + h] = S.z1[r][h];
-        }
-    // gW1[o][i] = sum_rows d1b[row][o] x[row][i]: 4 x 6 tiles, six per wave
-    for (int q = 0; q < 6; ++q) {
-        const int ob = w, ib = q;
-        const f4_t c = mma_tile([&](int i, int k) { return S.db[k][16 * ob + i]; },
-                                [&](int k, int j) { return S.x[k][16 * ib + j]; }, TILE);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int i = 16 * ib + li;
-            if (i < NIN) out[OW1 + (16 * ob + lk + r) * NIN + i] = c[r];
-        }
+        for (int k = 0; k < GWAVES; ++k) s += bias[k][t];
+        out[t < NH ? OB1 + t : (t < 2 * NH ? OB2 + t - NH : OB3 + t - 2 * NH)] = s;  // OB3 + NOUT is the loss
     }
 }
+static_assert(OB3 + NOUT == MLP_NPARAM, "the loss follows the last bias");
 
-// The per-tile partials are summed in two levels, each in a fixed order (deterministic): first the
-// tiles of each chunk of MLP_RCHUNK consecutive tiles, in place into the chunk's first row (every
-// column of a chunk's rows is read and written by one thread only), then the chunks' rows.  One
-// sequential sum over all tiles ran on a few dozen work-groups and took 0.9 ms for 3771 tiles.
-constexpr int MLP_RCHUNK = 64;
+// Work-groups of the gradient kernel: one per CU, or one per pass where that is fewer.
+constexpr int MLP_GRAD_BLOCKS = 256;
 
-__global__ void k_mlp_reduce_chunks(float *__restrict__ part, int32_t ntile)
+// grad[q] = the sum of the partials' column q (q = NPARAM: the loss, divided by n), in a fixed order:
+// four threads take a quarter of the rows each, then the quarters are added.
+__global__ __launch_bounds__(256) void k_mlp_reduce(const float *__restrict__ part, int32_t nblk, int64_t n,
+                                                    float *__restrict__ grad, float *__restrict__ loss)
 {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q > MLP_NPARAM) return;
-    const int32_t b0 = blockIdx.y * MLP_RCHUNK;
-    const int32_t b1 = min(b0 + MLP_RCHUNK, ntile);
+    __shared__ float quarter[4][64];
+    const int q = blockIdx.x * 64 + (threadIdx.x & 63), k = threadIdx.x >> 6;
+    const int b0 = nblk * k / 4, b1 = nblk * (k + 1) / 4;
     float s = 0.f;
-    for (int32_t b = b0; b < b1; ++b) s += part[(int64_t)b * (MLP_NPARAM + 1) + q];
-    part[(int64_t)b0 * (MLP_NPARAM + 1) + q] = s;
-}
-
-// grad[q] = the sum of the chunks' rows of column q (q = NPARAM: the loss, divided by n)
-__global__ void k_mlp_reduce(const float *__restrict__ part, int32_t ntile, int64_t n, float *__restrict__ grad,
-                             float *__restrict__ loss)
-{
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q > MLP_NPARAM) return;
-    float s = 0.f;
-    for (int32_t b = 0; b < ntile; b += MLP_RCHUNK) s += part[(int64_t)b * (MLP_NPARAM + 1) + q];
-    if (q < MLP_NPARAM) grad[q] = s;
-    else if (loss) *loss = s / (float)n;
+    if (q <= MLP_NPARAM) {
+#pragma unroll 8
+        for (int b = b0; b < b1; ++b) s += part[(int64_t)b * (MLP_NPARAM + 1) + q];
+    }
+    quarter[k][threadIdx.x & 63] = s;
+    __syncthreads();
+    if (k == 0 && q <= MLP_NPARAM) {
+        const int i = threadIdx.x;
+        const float t = (quarter[0][i] + quarter[1][i]) + (quarter[2][i] + quarter[3][i]);
+        if (q < MLP_NPARAM) grad[q] = t;
+        else if (loss) *loss = t / (float)n;
+    }
 }
 
 __global__ void k_mlp_adam(float *__restrict__ p, float *__restrict__ m, float *__restrict__ v,
@@ -478,24 +616,21 @@ hipError_t launch_mlp_forward(const float *prm, const float *norm, const float *
                               hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mlp_forward, dim3(mlp_tiles(n)), dim3(256), 0, st, prm, norm, feat, n, logits);
+    // waves of a few row blocks each once the chip is full (four work-groups per CU)
+    const int64_t nb = std::min<int64_t>(mlp_tiles(n), 1024);
+    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)nb), dim3(256), 0, st, prm, norm, feat, n, logits);
     return hipGetLastError();
 }
 
 hipError_t launch_mlp_grad(const float *prm, const float *norm, const float *feat, const int8_t *tags, int64_t n,
                            float *work, float *trace, float *grad, float *loss, hipStream_t st)
 {
-    const int32_t nt = mlp_tiles(n);
-    if ((nt + MLP_RCHUNK - 1) / MLP_RCHUNK > 65535) return hipErrorInvalidConfiguration;  // grid y of the reduction
-    hipLaunchKernelGGL(k_mlp_grad, dim3(nt), dim3(256), 0, st, prm, norm, feat, tags, n, work, trace);
+    const int32_t nt = mlp_tiles(n), nb = std::min((nt + GROWS / TILE - 1) / (GROWS / TILE), MLP_GRAD_BLOCKS);
+    if ((nt + 63) / 64 > 65535) return hipErrorInvalidConfiguration;  // 268 M rows
+    hipLaunchKernelGGL(k_mlp_grad, dim3(nb), dim3(64 * GWAVES), 0, st, prm, norm, feat, tags, n, work, trace);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const unsigned qb = (MLP_NPARAM + 1 + 255) / 256;
-    hipLaunchKernelGGL(k_mlp_reduce_chunks, dim3(qb, (unsigned)((nt + MLP_RCHUNK - 1) / MLP_RCHUNK)), dim3(256), 0, st,
-                       work, nt);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_mlp_reduce, dim3(qb), dim3(256), 0, st, work, nt, n, grad, loss);
+    hipLaunchKernelGGL(k_mlp_reduce, dim3((MLP_NPARAM + 1 + 63) / 64), dim3(256), 0, st, work, nb, n, grad, loss);
     return hipGetLastError();
 }
 
