@@ -541,87 +541,328 @@ __global__ __launch_bounds__(256) void k_rk4_ghost(int32_t s, double dt, const d
 }
 
 // ------------------------------------------------------------------ constraints
-// H = R + 2/3 K^2 - At_ij At^ij with R = phi^2 gt^ij R_ij;
+// H = phi^2 gt^ij R_ij + 2/3 K^2 - At_ij At^ij and
 // M_i = gt^kl (d_k At_li - Gt^m_li At_km - Gt^m_lk At_im - 3 At_ik P_l/phi) - 2/3 d_i K.
-// Only the first derivatives of D (Ricci tensor from the relations), P (Ricci tensor), At and K
-// (momentum constraint) enter: 28 slots.  One work-group per z-slab of a leaf stages them into LDS
-// in two rounds of 14 (the stage kernel's slab staging, own halos), forms each cell's FD4
-// differences from LDS, and takes the pointwise values of the staged slots from LDS too; the
-// other slots are read from the state, their loads in flight with the second round's copies.  Per-block partial sums (H^2, |M|^2, counted cells,
-// non-finite cells) in a fixed order for k_reduce_parts.
-constexpr int CONS_NB = 14;
-__global__ __launch_bounds__(256) void k_constraints_lds(const double *__restrict__ Q, double *__restrict__ HM,
-                                                         const PatchGeom *__restrict__ geom, int32_t npatch,
-                                                         double r_excise, double *__restrict__ part)
+// Only the trace of the Ricci tensor enters.  By the relations of App. B (D for the derivatives of gt,
+// P for that of phi, gt^ml gt_jl = delta^m_j)
+//   gt^ij R_ij = 2 S - 2 V^l W_l + 2 gt^ij D_i^ml D_jml + Gt^l D_l - gt^ij Gt^l_im Gt^m_lj
+//                + 4 (gt^ij d_i P_j - Gt^k P_k) / phi - 6 gt^ij P_i P_j / phi^2,
+//   S = (gt^bc gt^ad - gt^ab gt^cd) d_a D_bcd, V^l = D_m^ml, W_l = gt^ij Gt_l,ij, Gt^k = gt^kl W_l,
+//   D_l = gt^ij D_lij,
+// so that each derivative of D, P, At and K (28 slots) is contracted into one of five numbers as it is
+// formed, and nothing of it is kept.
+//
+// One work-group per leaf, one cell per lane: the leaf's nine planes and the four planes and rows at
+// distance two that a first difference reaches are staged once (a z-slab each, as the stage kernel
+// takes them, stages 60% more lines; and holding all 84 differences needed the whole register file at
+// one wave per SIMD).  Four slots at a time pass through two buffers, one in flight while the other is
+// read.  Bound by the staging: on 16^3 leaves 1.19 -> 0.74 ms (2.26 GB of algorithmic bytes, 0.41 ms at
+// the rate of a large read).
+namespace cons {
+constexpr int ROWS = 13;                    // staged rows of a plane, y = 1..13
+constexpr int PITCH = 18, PAIRS = PITCH / 2;  // a row's 16 doubles, the eighth pair repeated
+constexpr int PLANE = ROWS * PITCH;
+constexpr int OWN = PN * PLANE, OWN_PAIRS = PN * ROWS * PAIRS;
+constexpr int SLOT = OWN + 4 * PN * LDS_HROW;  // + interior rows (x = 2..11) of the planes z = 1, 2, 12, 13
+constexpr int SLOT_PAIRS = SLOT / 2;
+constexpr int LANES = 768, BATCH = 4, ROUNDS = 7;
+static_assert(SLOT_PAIRS > LANES && SLOT_PAIRS <= 2 * LANES && 2 * BATCH * SLOT * 8 <= 160 * 1024, "staging");
+
+// the slot staged as number j: D, P, At, K
+__device__ __forceinline__ constexpr int slot(int j)
 {
-    __shared__ double lds[CONS_NB * LDS_SLOT];
-    __shared__ double red[4][256];
-    const int64_t lb = xcd_logical_block(blockIdx.x, gridDim.x);
-    const int p = (int)(lb / 3);
-    const int tid = threadIdx.x;
-    double h2 = 0.0, m2 = 0.0, cnt = 0.0, bad = 0.0;
-    if (p < npatch) {  // uniform over the work-group
-        const int sl = (int)(lb % 3);
-        const PatchGeom g = geom[p];
-        int x, y, zl;
-        const bool act = slab_cell(tid, x, y, zl);
-        LdsCell<0> C;
-        C.s = lds;
-        const HaloSrc hs{};
-        lds_cell_offsets(C, x, y, zl, hs);
+    return j < 18 ? SD + j : (j < 21 ? SP + j - 18 : (j < 27 ? SAT + j - 21 : SK));
+}
+
+struct Cell {
+    int c, zo[5];    // LDS index of the cell; of its z-neighbours at offset k - 2
+    double i12[3];
+};
+
+// what the staged slots leave behind
+struct Sums {
+    double S, trdP, M[3];
+    double D[3][6], P[3], At[6], K;
+};
+
+template <int J>
+__device__ __forceinline__ void take(const double *__restrict__ f, const Cell &C, const double ig[6], Sums &X)
+{
+    constexpr int v = slot(J);
+    const double val = f[C.c];
+    double d[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        auto at = [&](int k) { return f[a == 0 ? C.c + k : (a == 1 ? C.c + k * PITCH : C.zo[k + 2])]; };
+        d[a] = (8.0 * (at(1) - at(-1)) - (at(2) - at(-2))) * C.i12[a];
+    }
+    if constexpr (v >= SD && v < SP) {
+        constexpr int b = (v - SD) / 6, s = (v - SD) % 6, c = sym_first(s), e = sym_second(s);
+        X.D[b][s] = val;
+        auto up = [&](int k) { return ig[sym(0, k)] * d[0] + ig[sym(1, k)] * d[1] + ig[sym(2, k)] * d[2]; };
+        X.S += c == e ? ig[sym(b, c)] * up(c) - ig[s] * up(b)
+                      : ig[sym(b, c)] * up(e) + ig[sym(b, e)] * up(c) - 2.0 * (ig[s] * up(b));
+    } else if constexpr (v >= SP && v < SK0) {
+        constexpr int j = v - SP;
+        X.P[j] = val;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) X.trdP += ig[sym(a, j)] * d[a];
+    } else if constexpr (v >= SAT && v < SAT + 6) {
+        constexpr int s = v - SAT, l = sym_first(s), i = sym_second(s);
+        X.At[s] = val;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            C.i12[a] = 1.0 / (12.0 * g.dx[a]);
-            C.koc[a] = 0.0;
+            X.M[i] += ig[sym(a, l)] * d[a];
+            if (l != i) X.M[l] += ig[sym(a, i)] * d[a];
         }
-        const double *qb = Q + (int64_t)p * PS;
-        const int z = zl + 3 + 3 * sl;
-        const int o = boff(x, y, z);
-        double q[NV], dq[3][NDIFF];
-        const int ra[CONS_NB] = {SD, SD + 1, SD + 2, SD + 3, SD + 4, SD + 5, SD + 6, SD + 7,
-                                 SD + 8, SD + 9, SD + 10, SD + 11, SD + 12, SD + 13};
-        const Stager sg = lds_stager<0>(qb, sl, hs);
-        lds_round(lds, ra, sg);
-        if (act)
+    } else {
+        X.K = val;
 #pragma unroll
-            for (int j = 0; j < CONS_NB; ++j) {
-                q[ra[j]] = lv(C, j, 0, 0);
+        for (int i = 0; i < 3; ++i) X.M[i] -= (2.0 / 3.0) * d[i];
+    }
+    // materialised here: the sums are used at the end only, and the compiler would otherwise move their
+    // arithmetic there and keep every stencil value until then
+    asm volatile("" : "+v"(X.S), "+v"(X.trdP), "+v"(X.M[0]), "+v"(X.M[1]), "+v"(X.M[2]) : : "memory");
+}
+
+// H and M_i from the sums, the metric's inverse and phi
+__device__ __forceinline__ void finish(const Sums &X, const double ig[6], double phi, double hm[4])
+{
+    auto mult = [](int s) { return s == 0 || s == 3 || s == 5 ? 1.0 : 2.0; };
+    const double (&D)[3][6] = X.D;
+    double V[3] = {0.0, 0.0, 0.0}, trD[3], W[3], Gv[3], DD = 0.0;
 #pragma unroll
-                for (int a = 0; a < 3; ++a) dq[a][ra[j] - DOFF] = fd(C, j, a);
+    for (int k = 0; k < 3; ++k) {
+        double Dm[3][3], Dup[6], t = 0.0;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int m = 0; m < 3; ++m)
+                Dm[i][m] = ig[sym(i, 0)] * D[k][sym(0, m)] + ig[sym(i, 1)] * D[k][sym(1, m)] + ig[sym(i, 2)] * D[k][sym(2, m)];
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = i; j < 3; ++j)
+                Dup[sym(i, j)] = Dm[i][0] * ig[sym(0, j)] + Dm[i][1] * ig[sym(1, j)] + Dm[i][2] * ig[sym(2, j)];
+#pragma unroll
+        for (int l = 0; l < 3; ++l) V[l] += Dup[sym(k, l)];
+        trD[k] = Dm[0][0] + Dm[1][1] + Dm[2][2];
+#pragma unroll
+        for (int s = 0; s < 6; ++s)
+            t += mult(s) * Dup[s] * (ig[sym(k, 0)] * D[0][s] + ig[sym(k, 1)] * D[1][s] + ig[sym(k, 2)] * D[2][s]);
+        DD += t;
+    }
+    double Gt[3][6];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = i; j < 3; ++j) {
+            double low[3];
+#pragma unroll
+            for (int l = 0; l < 3; ++l) low[l] = D[i][sym(j, l)] + D[j][sym(i, l)] - D[l][sym(i, j)];
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                Gt[k][sym(i, j)] = ig[sym(k, 0)] * low[0] + ig[sym(k, 1)] * low[1] + ig[sym(k, 2)] * low[2];
+        }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        Gv[k] = 0.0;
+#pragma unroll
+        for (int s = 0; s < 6; ++s) Gv[k] += mult(s) * ig[s] * Gt[k][s];
+    }
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {  // W_l = 2 gt^ij D_ijl - D_l
+        double t = 0.0;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) t += ig[sym(i, j)] * D[i][sym(j, l)];
+        W[l] = 2.0 * t - trD[l];
+    }
+    double GG = 0.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = i; j < 3; ++j) {
+            double t = 0.0;
+#pragma unroll
+            for (int l = 0; l < 3; ++l)
+#pragma unroll
+                for (int m = 0; m < 3; ++m) t += Gt[l][sym(i, m)] * Gt[m][sym(l, j)];
+            GG += mult(sym(i, j)) * ig[sym(i, j)] * t;
+        }
+    const double iphi = 1.0 / phi;
+    double Pp[3], Pu[3], Am[3][3];
+#pragma unroll
+    for (int l = 0; l < 3; ++l) Pp[l] = X.P[l] * iphi;
+#pragma unroll
+    for (int m = 0; m < 3; ++m) Pu[m] = ig[sym(m, 0)] * Pp[0] + ig[sym(m, 1)] * Pp[1] + ig[sym(m, 2)] * Pp[2];
+    const double VW = V[0] * W[0] + V[1] * W[1] + V[2] * W[2], GD = Gv[0] * trD[0] + Gv[1] * trD[1] + Gv[2] * trD[2];
+    const double GP = Gv[0] * Pp[0] + Gv[1] * Pp[1] + Gv[2] * Pp[2], PP = Pp[0] * Pu[0] + Pp[1] * Pu[1] + Pp[2] * Pu[2];
+    const double R = 2.0 * (X.S - VW + DD) + (GD - GG) + 4.0 * (X.trdP * iphi - GP) - 6.0 * PP;
+    double AA = 0.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            Am[i][j] = ig[sym(i, 0)] * X.At[sym(0, j)] + ig[sym(i, 1)] * X.At[sym(1, j)] + ig[sym(i, 2)] * X.At[sym(2, j)];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) AA += Am[i][j] * Am[j][i];
+    hm[0] = phi * phi * R + (2.0 / 3.0) * X.K * X.K - AA;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        double t = X.M[i];
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+#pragma unroll
+            for (int l = 0; l < 3; ++l) t -= Am[l][m] * Gt[m][sym(l, i)];
+            t -= Gv[m] * X.At[sym(i, m)];
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) t -= 3.0 * Pu[k] * X.At[sym(i, k)];
+        hm[1 + i] = t;
+    }
+}
+}  // namespace cons
+
+__global__ __launch_bounds__(cons::LANES) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_constraints_lds(
+    const double *__restrict__ Q, double *__restrict__ HM, const PatchGeom *__restrict__ geom, int32_t npatch,
+    double r_excise, double *__restrict__ part)
+{
+    using namespace cons;
+    __shared__ double bufa[BATCH * SLOT], bufb[BATCH * SLOT];
+    __shared__ double red[LANES / 64][4];
+    const int p = (int)xcd_logical_block(blockIdx.x, gridDim.x);
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    double h2 = 0.0, m2 = 0.0, cnt = 0.0, bad = 0.0;
+    if (p < npatch) {  // uniform over the work-group
+        const PatchBuf qb{Q + (int64_t)p * PS};
+        const bool act = tid < NCELL;
+        const int cc = act ? tid : NCELL - 1, m = cc / 9;
+        // rows in an order that spreads them over the LDS banks, as slab_row_y, planes of 13 rows
+        const int zl = m / 9, k9 = (m + 6 * zl) % 9, yr = k9 / 2 + (k9 % 2 ? 5 : 0), x = cc % 9 + 3;
+        const uint32_t ob = 8u * (uint32_t)boff(x, yr + 3, zl + 3);
+        // the slots that are only tested, and the metric and phi, first: they are used first
+        double g[6], other = 0.0, rest[SAT - 7 + SD - STHETA + 1];
+#pragma unroll
+        for (int v = 0; v < 6; ++v) g[v] = qb.load(ob, SG + v);
+        const double phi = qb.load(ob, SPHI);
+        {
+            int n = 0;
+#pragma unroll
+            for (int v = 6; v < SPHI; ++v) rest[n++] = qb.load(ob, v);
+#pragma unroll
+            for (int v = STHETA; v < SD; ++v) rest[n++] = qb.load(ob, v);
+            rest[n++] = qb.load(ob, SK0);
+        }
+        const double *src[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int q = min(i * LANES + tid, SLOT_PAIRS - 1);
+            int e;
+            if (q < OWN_PAIRS) {
+                const int r = q / PAIRS, j = q % PAIRS;
+                e = (3 + r / ROWS) * ZS + (r % ROWS + 1) * XS + 2 * (j < 8 ? j : 7);
+            } else {
+                const int h = q - OWN_PAIRS, hp = h / 45;
+                e = (hp < 2 ? 1 + hp : 10 + hp) * ZS + ((h / 5) % 9 + 3) * YS + 2 + 2 * (h % 5);
             }
-        const int rb[CONS_NB] = {SD + 14, SD + 15, SD + 16, SD + 17, SP, SP + 1, SP + 2,
-                                 SAT, SAT + 1, SAT + 2, SAT + 3, SAT + 4, SAT + 5, SK};
-        lds_issue(lds, rb, sg);
-        // the remaining slots pointwise (every slot takes part in the finiteness count), in
-        // flight together with the second round's copies; an idle lane reads cell 242's values
+            src[i] = qb.base + e;
+        }
+        const bool second = LANES + tid < SLOT_PAIRS;
+        auto issue = [&](double *buf, int round) {
+            double *dst = buf + wave * 128;
 #pragma unroll
-        for (int v = 0; v < SAT; ++v) q[v] = qb[v * CS + o];
+            for (int j = 0; j < BATCH; ++j)
+                __builtin_amdgcn_global_load_lds((const void *)(src[0] + slot(round * BATCH + j) * CS),
+                                                 (lds_void_t *)(dst + j * SLOT), 16, 0, 0);
+            if (second)
 #pragma unroll
-        for (int v = STHETA; v < SD; ++v) q[v] = qb[v * CS + o];
-        q[SK0] = qb[SK0 * CS + o];
-        lds_wait();
+                for (int j = 0; j < BATCH; ++j)
+                    __builtin_amdgcn_global_load_lds((const void *)(src[1] + slot(round * BATCH + j) * CS),
+                                                     (lds_void_t *)(dst + j * SLOT + 2 * LANES), 16, 0, 0);
+        };
+        issue(bufa, 0);
+        issue(bufb, 1);
+        const PatchGeom G = geom[p];
+        Cell C;
+        C.c = zl * PLANE + (yr + 2) * PITCH + x;
+#pragma unroll
+        for (int k = -2; k <= 2; ++k) {
+            const int z2 = zl + k;
+            C.zo[k + 2] = z2 >= 0 && z2 < PN ? C.c + k * PLANE
+                                             : OWN + (z2 < 0 ? z2 + 2 : z2 - PN + 2) * 90 + yr * LDS_HROW + (x - 2);
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) C.i12[a] = 1.0 / (12.0 * G.dx[a]);
+        double ig[6], detg;
+        metric_inverse(g, ig, detg);
+        // 0 times a finite number is 0, anything else is not
+#pragma unroll
+        for (int v = 0; v < 6; ++v) other += 0.0 * g[v];
+#pragma unroll
+        for (int n = 0; n < (int)(sizeof(rest) / sizeof(rest[0])); ++n) other += 0.0 * rest[n];
+        asm volatile("" : "+v"(other));
+        Sums X;
+        X.S = X.trdP = X.M[0] = X.M[1] = X.M[2] = 0.0;
+        // A barrier that orders the LDS accesses only: __syncthreads would wait for the copies in flight
+        // too.  Every LDS read before it has returned (lgkmcnt), and none is moved across (the clobbers).
+        auto barrier = [&]() {
+            asm volatile("" : : : "memory");
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" : : : "memory");
+        };
+        // the wave's copies of this round have landed (vmcnt: those of the next, one per slot and, where
+        // the wave has a second share, two, stay in flight), then those of all waves
+        auto wait = [&](bool more) {
+            if (!more) __builtin_amdgcn_s_waitcnt(0x0F70);
+            else if (wave * 64 + LANES < SLOT_PAIRS) __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * BATCH));
+            else __builtin_amdgcn_s_waitcnt(0x0F70 | BATCH);
+            barrier();
+        };
+#define CONS_ROUND(R, buf)                                       \
+    wait(R + 1 < ROUNDS);                                        \
+    take<BATCH * R + 0>(buf + 0 * SLOT, C, ig, X);               \
+    take<BATCH * R + 1>(buf + 1 * SLOT, C, ig, X);               \
+    take<BATCH * R + 2>(buf + 2 * SLOT, C, ig, X);               \
+    take<BATCH * R + 3>(buf + 3 * SLOT, C, ig, X);               \
+    if (R + 2 < ROUNDS) {                                        \
+        barrier();                                               \
+        issue(buf, R + 2);                                       \
+    }
+        CONS_ROUND(0, bufa)
+        CONS_ROUND(1, bufb)
+        CONS_ROUND(2, bufa)
+        CONS_ROUND(3, bufb)
+        CONS_ROUND(4, bufa)
+        CONS_ROUND(5, bufb)
+        CONS_ROUND(6, bufa)
+#undef CONS_ROUND
+        double hm[4];
+        finish(X, ig, phi, hm);
         if (act) {
 #pragma unroll
-            for (int j = 0; j < CONS_NB; ++j) {
-                q[rb[j]] = lv(C, j, 0, 0);
+            for (int i = 0; i < 3; ++i) {
+                other += 0.0 * X.P[i];
 #pragma unroll
-                for (int a = 0; a < 3; ++a) dq[a][rb[j] - DOFF] = fd(C, j, a);
+                for (int s = 0; s < 6; ++s) other += 0.0 * X.D[i][s];
             }
-            bool fin = true;
 #pragma unroll
-            for (int v = 0; v < NV; ++v) fin = fin && isfinite(q[v]);
-            double hm[4];
-            constraints_algebra(q, dq, hm);
+            for (int s = 0; s < 6; ++s) other += 0.0 * X.At[s];
+            other += 0.0 * X.K + 0.0 * phi;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) fin = fin && isfinite(hm[j]);
-            const int c = sl * NFACE + (zl * 9 + y - 3) * 9 + x - 3;
+            for (int j = 0; j < 4; ++j) other += 0.0 * hm[j];
+            const int c = (zl * 9 + yr) * 9 + x - 3;
             if (HM)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) HM[((int64_t)p * 4 + j) * NCELL + c] = hm[j];
-            const double X = g.org[0] + (x - 2.5) * g.dx[0], Y = g.org[1] + (y - 2.5) * g.dx[1],
-                         Z = g.org[2] + (z - 2.5) * g.dx[2];
-            const double r = sqrt(X * X + Y * Y + Z * Z);
-            if (!fin) bad = 1.0;
+            const double X0 = G.org[0] + (x - 2.5) * G.dx[0], Y0 = G.org[1] + (yr + 0.5) * G.dx[1],
+                         Z0 = G.org[2] + (zl + 0.5) * G.dx[2];
+            const double r = sqrt(X0 * X0 + Y0 * Y0 + Z0 * Z0);
+            if (!(other == 0.0)) bad = 1.0;
             else if (r >= r_excise) {
                 h2 = hm[0] * hm[0];
                 m2 = hm[1] * hm[1] + hm[2] * hm[2] + hm[3] * hm[3];
@@ -629,40 +870,57 @@ __global__ __launch_bounds__(256) void k_constraints_lds(const double *__restric
             }
         }
     }
-    // block reduction (deterministic order)
-    red[0][tid] = h2;
-    red[1][tid] = m2;
-    red[2][tid] = cnt;
-    red[3][tid] = bad;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (tid < s)
-            for (int j = 0; j < 4; ++j) red[j][tid] += red[j][tid + s];
-        __syncthreads();
+    // the work-group's sums, in a fixed order: lanes, then waves
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) {
+        h2 += __shfl_down(h2, s);
+        m2 += __shfl_down(m2, s);
+        cnt += __shfl_down(cnt, s);
+        bad += __shfl_down(bad, s);
     }
-    if (tid == 0)
-        for (int j = 0; j < 4; ++j) part[(int64_t)blockIdx.x * 4 + j] = red[j][0];
+    if ((tid & 63) == 0) {
+        red[wave][0] = h2;
+        red[wave][1] = m2;
+        red[wave][2] = cnt;
+        red[wave][3] = bad;
+    }
+    __syncthreads();
+    if (tid < 4) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < LANES / 64; ++w) t += red[w][tid];
+        part[(int64_t)blockIdx.x * 4 + tid] = t;
+    }
 }
 
-__global__ void k_reduce_parts(const double *__restrict__ part, int64_t nblk, double *__restrict__ out)
+// The norms from the work-groups' sums (four numbers each): one work-group, every lane a strided share
+// with eight rows in flight, then a tree; in a fixed order.
+__global__ __launch_bounds__(1024) void k_reduce_parts(const double *__restrict__ part, int64_t nblk,
+                                                       double *__restrict__ out)
 {
-    // one block of 256 threads: strided partial sums, then a tree
-    __shared__ double red[4][256];
-    double s[4] = {0, 0, 0, 0};
-    for (int64_t b = threadIdx.x; b < nblk; b += 256)
+    __shared__ double red[16][4];
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+    for (int64_t b = threadIdx.x; b < nblk; b += 1024)
+#pragma unroll
         for (int j = 0; j < 4; ++j) s[j] += part[b * 4 + j];
-    for (int j = 0; j < 4; ++j) red[j][threadIdx.x] = s[j];
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[j] += __shfl_down(s[j], d);
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) red[threadIdx.x >> 6][j] = s[j];
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            for (int j = 0; j < 4; ++j) red[j][threadIdx.x] += red[j][threadIdx.x + w];
-        __syncthreads();
-    }
     if (threadIdx.x == 0) {
-        const double n = red[2][0];
+#pragma unroll
+        for (int w = 1; w < 16; ++w)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) red[0][j] += red[w][j];
+        const double n = red[0][2];
         out[0] = n > 0 ? sqrt(red[0][0] / n) : 0.0;
-        out[1] = n > 0 ? sqrt(red[1][0] / n) : 0.0;
-        out[2] = red[3][0];
+        out[1] = n > 0 ? sqrt(red[0][1] / n) : 0.0;
+        out[2] = red[0][3];
     }
 }
 
@@ -1168,17 +1426,17 @@ hipError_t launch_rk4(int32_t s, double dt, const double *Qn, const double *K, d
     return hipGetLastError();
 }
 
-// one work-group per z-slab, a multiple of 8 for the XCD block order (at least 8)
-int64_t constraints_blocks(int32_t npatch) { return std::max<int64_t>(8, ((int64_t)npatch * 3 + 7) / 8 * 8); }
+// one work-group per leaf, a multiple of 8 for the XCD block order (at least 8)
+int64_t constraints_blocks(int32_t npatch) { return std::max<int64_t>(8, ((int64_t)npatch + 7) / 8 * 8); }
 
 hipError_t launch_constraints(const double *Q, double *HM, const PatchGeom *geom, int32_t npatch,
                               double r_excise, double *part, double *out3, hipStream_t st)
 {
     const int64_t nb = constraints_blocks(npatch);
-    hipLaunchKernelGGL(k_constraints_lds, dim3((unsigned)nb), dim3(256), 0, st, Q, HM, geom, npatch, r_excise, part);
+    hipLaunchKernelGGL(k_constraints_lds, dim3((unsigned)nb), dim3(cons::LANES), 0, st, Q, HM, geom, npatch, r_excise, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_reduce_parts, dim3(1), dim3(256), 0, st, part, nb, out3);
+    hipLaunchKernelGGL(k_reduce_parts, dim3(1), dim3(1024), 0, st, part, nb, out3);
     return hipGetLastError();
 }
 
