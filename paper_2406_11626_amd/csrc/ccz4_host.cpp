@@ -85,14 +85,15 @@ struct ccz4_ctx {
     std::vector<PatchGeom> geom;
     std::vector<TrackBox> tbox;           // cubes of the leaves and of their parents
     DevBuf<TrackBox> d_tbox;
-    std::vector<FaceTask> ph_copy, ph_neu, ph_res, ph_pro;  // fill tasks by kind (restrict before prolong)
+    std::vector<FaceTask> ph_neu, ph_res, ph_pro;  // fill tasks by kind (restrict before prolong)
+    int64_t ncopy = 0;                        // same-level faces (nbr)
     std::vector<int32_t> nbr;                 // [leaf][6] same-level face neighbour or -1
     std::vector<BoundaryFace> bface;
     std::vector<int32_t> pface;               // per leaf and face 2 axis + (side > 0): index into bface or -1
     std::vector<uint8_t> bmask;
     std::vector<int32_t> sib;
     DevBuf<PatchGeom> d_geom;
-    DevBuf<FaceTask> d_phc, d_phn, d_phr, d_php;
+    DevBuf<FaceTask> d_phn, d_phr, d_php;
     DevBuf<int32_t> d_nbr;
     DevBuf<int32_t> d_order;                  // KV_ORDERS leaf permutations, npatch each
     DevBuf<BoundaryFace> d_bf;
@@ -187,7 +188,7 @@ ccz4_status build_plan(ccz4_ctx *c, const ccz4_grid_desc *g)
         }
     }
     // face tasks
-    c->ph_copy.clear();
+    c->ncopy = 0;
     c->ph_neu.clear();
     c->ph_res.clear();
     c->ph_pro.clear();
@@ -222,9 +223,7 @@ ccz4_status build_plan(ccz4_ctx *c, const ccz4_grid_desc *g)
                 }
                 const int nb = find(lev, n[0], n[1], n[2]);
                 if (nb >= 0) {
-                    t.kind = FK_COPY;
-                    t.src[0] = nb;
-                    c->ph_copy.push_back(t);
+                    ++c->ncopy;
                     c->nbr[p * 6 + 2 * a + (side > 0 ? 1 : 0)] = nb;
                     continue;
                 }
@@ -399,7 +398,6 @@ ccz4_status ccz4_create(ccz4_ctx **out, const ccz4_grid_desc *g, const ccz4_para
     hipError_t e = hipSuccess;
     if (e == hipSuccess) e = c->d_geom.upload(c->geom);
     if (e == hipSuccess) e = c->d_tbox.upload(c->tbox);
-    if (e == hipSuccess) e = c->d_phc.upload(c->ph_copy);
     if (e == hipSuccess) e = c->d_phn.upload(c->ph_neu);
     if (e == hipSuccess) e = c->d_phr.upload(c->ph_res);
     if (e == hipSuccess) e = c->d_php.upload(c->ph_pro);
@@ -434,7 +432,6 @@ void ccz4_destroy(ccz4_ctx *c)
     (void)hipDeviceSynchronize();
     c->d_geom.release();
     c->d_tbox.release();
-    c->d_phc.release();
     c->d_phn.release();
     c->d_phr.release();
     c->d_php.release();
@@ -526,7 +523,8 @@ ccz4_status ccz4_fill_halos_kinds(ccz4_ctx *c, double *Q, int32_t kinds, void *s
     ccz4_status st = check_ptr(Q, "Q");
     if (st) return st;
     if (kinds & ~CCZ4_FILL_ALL) return fail(CCZ4_EINVAL, "unknown fill kinds");
-    if (kinds & CCZ4_FILL_SAME_LEVEL) HIP_TRY(launch_fill(Q, c->d_phc.p, (int32_t)c->ph_copy.size(), c->prm.transfer, S(stream)));
+    if ((kinds & CCZ4_FILL_SAME_LEVEL) && c->ncopy > 0)
+        HIP_TRY(launch_copy_faces(Q, c->d_nbr.p, (int32_t)c->leaf.size(), S(stream)));
     if (kinds & CCZ4_FILL_NEUMANN) HIP_TRY(launch_fill(Q, c->d_phn.p, (int32_t)c->ph_neu.size(), c->prm.transfer, S(stream)));
     if (kinds & CCZ4_FILL_LEVELS) {
         HIP_TRY(launch_fill(Q, c->d_phr.p, (int32_t)c->ph_res.size(), c->prm.transfer, S(stream)));
@@ -538,7 +536,7 @@ ccz4_status ccz4_fill_halos_kinds(ccz4_ctx *c, double *Q, int32_t kinds, void *s
 ccz4_status ccz4_plan_counts(const ccz4_ctx *c, int64_t *counts)
 {
     if (!c || !counts) return fail(CCZ4_EINVAL, "ctx or counts is NULL");
-    counts[0] = (int64_t)c->ph_copy.size();
+    counts[0] = c->ncopy;
     counts[1] = (int64_t)c->ph_neu.size();
     counts[2] = (int64_t)c->ph_res.size();
     counts[3] = (int64_t)c->ph_pro.size();

@@ -146,40 +146,86 @@ __device__ __forceinline__ void ppar(int F, int &l, double &w0, double &w1)
     w0 = 1.0 - w1;
 }
 
-// One block per (face task, batch of eight slots), one thread per slab cell; a copy issues all
-// loads of its batch before its stores, since source and destination share the state array.
+// Same-level faces: a work-group takes two slots of one leaf.  Its lanes read the leaf's interior once
+// and copy it into the neighbours' y and z face halos; the x halos, three cells at either end of the
+// leaf's own rows, are gathered, both ends of a row by one instruction.  Sources are interior cells and
+// destinations ghosts, each written by one lane.  Bound by the partial lines that are written (24 and
+// 72 of 128 bytes: 189 a slot and leaf, which memory reads and writes back): on 16^3 leaves 3.93 ms by
+// one block per face and eight slots -> 2.44 ms; every face gathered 2.79 ms, every face copied out
+// 2.47 ms, y and z copies not streamed past the caches 2.64 ms, eight slots a work-group 2.50 ms.
+constexpr int COPY_LANES = 768, COPY_SLOTS = 2, COPY_BATCHES = (NV + COPY_SLOTS - 1) / COPY_SLOTS;
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_fill(
-    double *__restrict__ Q, const FaceTask *__restrict__ tasks, int32_t ntask, int32_t transfer)
+__global__ __launch_bounds__(COPY_LANES) void k_copy_faces(double *__restrict__ Q, const int32_t *__restrict__ nbr,
+                                                           int32_t npatch)
 {
+    const int64_t lb = xcd_logical_block(blockIdx.x, gridDim.x);
+    const int p = (int)(lb / COPY_BATCHES);
+    if (p >= npatch) return;
+    const int v0 = (int)(lb % COPY_BATCHES) * COPY_SLOTS;
+    double *Qp = Q + (int64_t)p * PS + (int64_t)v0 * CS;
+    const int i = (int)threadIdx.x;
+    int64_t pd[3] = {0, 0, 0};
+    const int x = i % 9 + 3, y = (i / 9) % 9 + 3, z = i / 81 + 3, o = boff(x, y, z);
+    if (i < NCELL) push_offsets(nbr, p, x, y, z, o, pd, 6);
+    const bool push = pd[1] != 0 || pd[2] != 0;
+    // x ghost cell k (0..2 low, 3..5 high) of row i / 6
+    const int row = i / 6, k = i % 6, og = boff(k < 3 ? k : k + 9, row % 9 + 3, row / 9 + 3);
+    const int q = i < 6 * PN * PN ? nbr[6 * p + (k < 3 ? 0 : 1)] : -1;
+    const int64_t xd = (int64_t)(q - p) * PS + og + (k < 3 ? 9 : -9);
+    double own[COPY_SLOTS], gh[COPY_SLOTS];
+#pragma unroll
+    for (int j = 0; j < COPY_SLOTS; ++j)
+        if (v0 + j < NV) {
+            if (push) own[j] = Qp[j * CS + o];
+            if (q >= 0) gh[j] = Qp[j * CS + xd];
+        }
+#pragma unroll
+    for (int j = 0; j < COPY_SLOTS; ++j)
+        if (v0 + j < NV) {
+            if (q >= 0) Qp[j * CS + og] = gh[j];
+#pragma unroll
+            for (int a = 1; a < 3; ++a)
+                if (pd[a] != 0) __builtin_nontemporal_store(own[j], Qp + j * CS + o + pd[a]);
+        }
+}
+
+// The other kinds: one block per (face task, batch of slots), one thread per slab cell.  The operators of
+// two and nine points go through four slots a block (a level pair's fills are bound by the partial lines
+// they touch: 0.33 ms on 5760 leaves of two levels, 136 coarse faces, with four slots or eight).  The
+// higher-order prolongation reads 27 cells per slot, whose loads need the registers: one slot a block
+// (1.09 -> 0.40 ms on three levels of 5760 leaves; two slots 0.50).
+template <int HIGHER>
+constexpr int FILL_SLOTS = HIGHER ? 1 : 4;
+
+template <int HIGHER>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_fill(
+    double *__restrict__ Q, const FaceTask *__restrict__ tasks, int32_t ntask)
+{
+    constexpr int SLOTS = FILL_SLOTS<HIGHER>;
     const int ti = blockIdx.x;
     const int idx = threadIdx.x;
     if (ti >= ntask || idx >= NFACE) return;
-    // blockIdx.y picks a batch of eight slots, so that a task's slots are filled in parallel
-    const int v_lo = (int)blockIdx.y * SB8, v_hi = v_lo + SB8 < NV ? v_lo + SB8 : NV;
+    // blockIdx.y picks the batch, so that a task's slots are filled in parallel
+    const int v_lo = (int)blockIdx.y * SLOTS, v_hi = v_lo + SLOTS < NV ? v_lo + SLOTS : NV;
     const FaceTask tk = tasks[ti];
     int L, t1, t2;
     slab_coords(tk.axis, idx, L, t1, t2);
     double *dst = Q + (int64_t)tk.patch * PS + slab_off(tk.axis, ghost_c(tk.side, L), t1, t2);
-    const bool inject = tk.kind == FK_RESTRICT && transfer == 1;
-    if (tk.kind == FK_COPY || tk.kind == FK_NEUMANN || inject) {
+    if (tk.kind == FK_NEUMANN || (HIGHER && tk.kind == FK_RESTRICT)) {
         // copies; with the higher-order operators the restriction is one too: coarse ghost c_{2+L}
         // takes the fine cell with the same centre, tangentially the middle of the three fine
         // cells under it, along the normal the fine interior depth 3L - 1
         const int F1 = 3 * t1 + 1, F2 = 3 * t2 + 1;
-        const double *src =
-            tk.kind == FK_COPY ? Q + (int64_t)tk.src[0] * PS + slab_off(tk.axis, depth_c(-tk.side, L), t1, t2)
-            : inject ? Q + (int64_t)tk.src[(F2 / 9) * 3 + F1 / 9] * PS +
-                           slab_off(tk.axis, depth_c(-tk.side, 3 * L - 1), F1 % 9, F2 % 9)
-                     : Q + (int64_t)tk.patch * PS + slab_off(tk.axis, depth_c(tk.side, 1), t1, t2);
-        {
-            double r[SB8];
+        const double *src = tk.kind == FK_RESTRICT
+                                ? Q + (int64_t)tk.src[(F2 / 9) * 3 + F1 / 9] * PS +
+                                      slab_off(tk.axis, depth_c(-tk.side, 3 * L - 1), F1 % 9, F2 % 9)
+                                : Q + (int64_t)tk.patch * PS + slab_off(tk.axis, depth_c(tk.side, 1), t1, t2);
+        double r[SLOTS];
 #pragma unroll
-            for (int j = 0; j < SB8; ++j) r[j] = (v_lo + j < v_hi) ? src[(v_lo + j) * CS] : 0.0;
+        for (int i = 0; i < SLOTS; ++i) r[i] = (v_lo + i < v_hi) ? src[(v_lo + i) * CS] : 0.0;
 #pragma unroll
-            for (int j = 0; j < SB8; ++j)
-                if (v_lo + j < v_hi) dst[(v_lo + j) * CS] = r[j];
-        }
+        for (int i = 0; i < SLOTS; ++i)
+            if (v_lo + i < v_hi) dst[(v_lo + i) * CS] = r[i];
     } else if (tk.kind == FK_RESTRICT) {
         // coarse ghost c_{2+L}; fine interior layers f3..f5 = depth 1..3 from the kid's face -side;
         // R_perp rows (1/3,1/3,1/3), (0,-2,3), (0,-5,6) over (f3,f4,f5); R_avg over 3x3 fine cells
@@ -206,7 +252,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             }
             dst[v * CS] = acc;
         }
-    } else if (transfer == 1) {  // FK_PROLONG, higher order
+    } else if constexpr (HIGHER) {  // FK_PROLONG
         // three-point Lagrange quadratics along every axis.  Tangentially fine cell F sits at
         // coarse coordinate u = (F + 1/2)/3 - 1/2, taken from the coarse centres l-1, l, l+1 with
         // l the nearest one kept in 1..7; along the normal fine ghost L sits s = 1/2 - (L - 1/2)/3
@@ -1314,7 +1360,20 @@ hipError_t launch_init(double *Q, const PatchGeom *geom, const uint8_t *bmask, i
 hipError_t launch_fill(double *Q, const FaceTask *tasks, int32_t ntask, int32_t transfer, hipStream_t st)
 {
     if (ntask <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fill, dim3(ntask, (NV + SB8 - 1) / SB8), dim3(256), 0, st, Q, tasks, ntask, transfer);
+    if (transfer == 1)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_fill<1>), dim3(ntask, (NV + FILL_SLOTS<1> - 1) / FILL_SLOTS<1>), dim3(256), 0,
+                           st, Q, tasks, ntask);
+    else
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_fill<0>), dim3(ntask, (NV + FILL_SLOTS<0> - 1) / FILL_SLOTS<0>), dim3(256), 0,
+                           st, Q, tasks, ntask);
+    return hipGetLastError();
+}
+
+hipError_t launch_copy_faces(double *Q, const int32_t *nbr, int32_t npatch, hipStream_t st)
+{
+    if (npatch <= 0) return hipSuccess;
+    const int64_t nb = ((int64_t)npatch + 7) / 8 * 8 * COPY_BATCHES;  // a multiple of 8 for the XCD block order
+    hipLaunchKernelGGL(k_copy_faces, dim3((unsigned)nb), dim3(COPY_LANES), 0, st, Q, nbr, npatch);
     return hipGetLastError();
 }
 

@@ -14,6 +14,7 @@ struct InitArgs {
 hipError_t launch_init(double *Q, const PatchGeom *geom, const uint8_t *bmask, int32_t npatch, int32_t scen,
                        const InitArgs &a, hipStream_t st);
 hipError_t launch_fill(double *Q, const FaceTask *tasks, int32_t ntask, int32_t transfer, hipStream_t st);
+hipError_t launch_copy_faces(double *Q, const int32_t *nbr, int32_t npatch, hipStream_t st);
 // right-hand side / fused stage launch configurations: bit 0 selects the LDS-staged kernel (else
 // the phased one), bit 1 the plain block order (else the XCD-grouped order), bits 2-3 the order in
 // which the launch walks the leaves (the permutations of the context, KV_ORDERS of them)

@@ -64,15 +64,15 @@ __host__ __device__ constexpr int acc_ghost(int axis, int side, int idx)
     return ACC_GHOST + (2 * axis + (side > 0 ? 1 : 0)) * NFACE + idx;
 }
 
-// face-task kinds of the halo fill
-enum FaceKind : int32_t { FK_COPY = 0, FK_NEUMANN = 1, FK_RESTRICT = 2, FK_PROLONG = 3 };
+// face-task kinds of the halo fill (same-level faces go by the neighbour table)
+enum FaceKind : int32_t { FK_NEUMANN = 1, FK_RESTRICT = 2, FK_PROLONG = 3 };
 
 struct FaceTask {
     int32_t kind;
     int32_t patch;     // destination leaf
     int32_t axis;      // 0, 1, 2
     int32_t side;      // -1 or +1
-    int32_t src[9];    // COPY: src[0]; RESTRICT: 9 fine leaves [u2*3+u1]; PROLONG: src[0] coarse leaf
+    int32_t src[9];    // RESTRICT: 9 fine leaves [u2*3+u1]; PROLONG: src[0] coarse leaf
     int32_t o1, o2;    // PROLONG: position of the fine patch inside the coarse face
 };
 
