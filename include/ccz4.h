@@ -347,6 +347,13 @@ ccz4_status ccz4_regrid_plan(const ccz4_ctx *ctx, const int8_t *tags_host, int32
 ccz4_status ccz4_regrid_transfer(const ccz4_ctx *old_ctx, const double *Qold, const ccz4_ctx *new_ctx,
                                  double *Qnew, void *stream);
 
+/* ccz4_regrid_transfer into a state that holds nothing yet: Qnew becomes what ccz4_init_patches on a
+   zeroed Qnew followed by the transfer leave there (interpolated and averaged leaves: zero outside the
+   interior, the initial data on their Sommerfeld ghosts), and new_ctx records the Sommerfeld
+   background.  Synchronises `stream`. */
+ccz4_status ccz4_regrid_state(const ccz4_ctx *old_ctx, const double *Qold, ccz4_ctx *new_ctx, double *Qnew,
+                              int32_t scenario, const double *scen, int32_t n_scen, void *stream);
+
 /* ---------------------------------------------------------------------------------------
    Learned refinement indicator (a project addition on the refinement-criterion hook of the
    paper's Sec. 3.6): a small perceptron, trained on tags of the plain criterion, that can add

@@ -113,6 +113,7 @@ def lib():
             "ccz4_step_graph_destroy": (None, [P]),
             "ccz4_regrid_plan": (i32, [P, P, i32, P, i64, ctypes.POINTER(i64)]),
             "ccz4_regrid_transfer": (i32, [P, P, P, P, P]),
+            "ccz4_regrid_state": (i32, [P, P, P, P, i32, P, i32, P]),
             "ccz4_features": (i32, [P, P, P, P, P]),
             "ccz4_mlp_forward": (i32, [P, P, P, i64, P, P]),
             "ccz4_mlp_workspace": (i32, [i64, ctypes.POINTER(i64)]),
@@ -317,6 +318,12 @@ def ccz4_regrid_transfer(h_old, Qold, h_new, Qnew, stream=None):
     return _check(lib().ccz4_regrid_transfer(h_old, _ptr(Qold), h_new, _ptr(Qnew), _stream(stream)))
 
 
+def ccz4_regrid_state(h_old, Qold, h_new, Qnew, scenario, scen, stream=None):
+    arr = (ctypes.c_double * max(len(scen), 1))(*[float(v) for v in scen])
+    return _check(lib().ccz4_regrid_state(h_old, _ptr(Qold), h_new, _ptr(Qnew), int(scenario),
+                                          ctypes.cast(arr, ctypes.c_void_p), len(scen), _stream(stream)))
+
+
 def ccz4_features(h, Q, HM, feat, stream=None):
     return _check(lib().ccz4_features(h, _ptr(Q), _ptr(HM), _ptr(feat), _stream(stream)))
 
@@ -471,15 +478,15 @@ class Context:
         return ccz4_plan_counts(self.h)
 
     def regrid(self, Q, tags, max_level, scenario, scen, stream=None):
-        """(new context, new state) after the tags: plan, new mesh, the analytic initial data for
-        its background and new ghost slabs, the transfer of Q, and a full halo fill."""
+        """(new context, new state) after the tags: plan, new mesh, the transfer of Q with the analytic
+        initial data for the background and new ghost slabs, and a full halo fill."""
+        import torch
         refined = [tuple(int(v) for v in r) for r in ccz4_regrid_plan(self.h, tags, max_level)]
         new = Context(self.n0, self.origin, self.extent, self.bc, self.prm, refined)
         for prec in (PREC_FP64, PREC_MIXED):
             new.set_kernel(prec, self.get_kernel(prec))
-        Qn = new.new_state(0.0)
-        new.init_patches(Qn, scenario, scen, stream)
-        ccz4_regrid_transfer(self.h, Q, new.h, Qn, stream)
+        Qn = torch.empty((new.n_patches, NV, 15, 15, 16), dtype=torch.float64, device="cuda")
+        ccz4_regrid_state(self.h, Q, new.h, Qn, scenario, scen, stream)
         new.fill_halos(Qn, stream)
         return new, Qn
 

@@ -90,7 +90,6 @@ struct ccz4_ctx {
     std::vector<int32_t> nbr;                 // [leaf][6] same-level face neighbour or -1
     std::vector<BoundaryFace> bface;
     std::vector<int32_t> pface;               // per leaf and face 2 axis + (side > 0): index into bface or -1
-    std::vector<uint8_t> bmask;
     std::vector<int32_t> sib;
     DevBuf<PatchGeom> d_geom;
     DevBuf<FaceTask> d_phn, d_phr, d_php;
@@ -98,7 +97,6 @@ struct ccz4_ctx {
     DevBuf<int32_t> d_order;                  // KV_ORDERS leaf permutations, npatch each
     DevBuf<BoundaryFace> d_bf;
     DevBuf<int32_t> d_pface;
-    DevBuf<uint8_t> d_bmask;
     DevBuf<int32_t> d_sib;
     DevBuf<double> d_bg, d_part, d_out3, d_hm;
     DevBuf<int8_t> d_pre;                     // learned tags, first pass
@@ -194,7 +192,6 @@ ccz4_status build_plan(ccz4_ctx *c, const ccz4_grid_desc *g)
     c->ph_pro.clear();
     c->bface.clear();
     c->nbr.assign(leaves.size() * 6, -1);
-    c->bmask.assign(leaves.size(), 0);
     for (size_t p = 0; p < leaves.size(); ++p) {
         const int lev = leaves[p][0];
         for (int a = 0; a < 3; ++a)
@@ -217,7 +214,6 @@ ccz4_status build_plan(ccz4_ctx *c, const ccz4_grid_desc *g)
                     } else {
                         BoundaryFace b{(int)p, a, side, (int)c->bface.size()};
                         c->bface.push_back(b);
-                        c->bmask[p] |= (uint8_t)(1u << (2 * a + (side > 0 ? 1 : 0)));
                         continue;
                     }
                 }
@@ -411,7 +407,6 @@ ccz4_status ccz4_create(ccz4_ctx **out, const ccz4_grid_desc *g, const ccz4_para
         c->pface[(size_t)b.patch * 6 + 2 * b.axis + (b.side > 0 ? 1 : 0)] = (int32_t)i;
     }
     if (e == hipSuccess && !c->pface.empty()) e = c->d_pface.upload(c->pface);
-    if (e == hipSuccess) e = c->d_bmask.upload(c->bmask);
     if (e == hipSuccess) e = c->d_sib.upload(c->sib);
     if (e == hipSuccess) e = c->d_bg.alloc(nbf * NV * NFACE);
     if (e == hipSuccess) e = c->d_part.alloc((size_t)nblk * 4);
@@ -440,7 +435,6 @@ void ccz4_destroy(ccz4_ctx *c)
     c->d_pre.release();
     c->d_bf.release();
     c->d_pface.release();
-    c->d_bmask.release();
     c->d_sib.release();
     c->d_bg.release();
     c->d_part.release();
@@ -483,18 +477,25 @@ ccz4_status ccz4_patch_table(const ccz4_ctx *c, int32_t *ids, double *geom)
     return CCZ4_OK;
 }
 
-ccz4_status ccz4_init_patches(ccz4_ctx *c, double *Q, int32_t scen, const double *sp, int32_t nsp, void *stream)
+static ccz4_status init_args(int32_t scen, const double *sp, int32_t nsp, InitArgs &a)
 {
-    if (!c) return fail(CCZ4_EINVAL, "ctx is NULL");
-    ccz4_status st = check_ptr(Q, "Q");
-    if (st) return st;
     const int need = scen == CCZ4_SCEN_GAUGE_WAVE ? 2 : (scen == CCZ4_SCEN_PUNCTURE ? 5 : (scen == CCZ4_SCEN_BL_BY ? 14 : -1));
     if (need < 0) return fail(CCZ4_EINVAL, "unknown scenario");
     if (nsp < need || !sp) return fail(CCZ4_EINVAL, "too few scenario parameters");
-    InitArgs a{};
     for (int i = 0; i < need; ++i) a.sp[i] = sp[i];
-    HIP_TRY(launch_init(Q, c->d_geom.p, c->d_bmask.p, (int32_t)c->leaf.size(), scen, a, S(stream)));
-    HIP_TRY(launch_capture_bg(Q, c->d_bf.p, c->d_bg.p, (int32_t)c->bface.size(), S(stream)));
+    return CCZ4_OK;
+}
+
+ccz4_status ccz4_init_patches(ccz4_ctx *c, double *Q, int32_t scen, const double *sp, int32_t nsp, void *stream)
+{
+    if (!c) return fail(CCZ4_EINVAL, "ctx is NULL");
+    InitArgs a{};
+    ccz4_status st = check_ptr(Q, "Q");
+    if (!st) st = init_args(scen, sp, nsp, a);
+    if (st) return st;
+    HIP_TRY(launch_init(Q, c->d_geom.p, (int32_t)c->leaf.size(), scen, a, S(stream)));
+    HIP_TRY(launch_init_ghosts(Q, c->d_geom.p, c->d_bf.p, c->d_bg.p, (int32_t)c->bface.size(), nullptr, scen, a,
+                               S(stream)));
     c->bg_valid = true;
     return CCZ4_OK;
 }
@@ -1017,7 +1018,9 @@ ccz4_status ccz4_regrid_plan(const ccz4_ctx *c, const int8_t *tags, int32_t max_
     return CCZ4_OK;
 }
 
-ccz4_status ccz4_regrid_transfer(const ccz4_ctx *co, const double *Qo, const ccz4_ctx *cn, double *Qn, void *stream)
+// where the leaves of a new mesh take their data from, after checking the two
+static ccz4_status regrid_tasks(const ccz4_ctx *co, const double *Qo, const ccz4_ctx *cn, const double *Qn,
+                                std::vector<RegridTask> &tasks)
 {
     if (!co || !cn) return fail(CCZ4_EINVAL, "ctx is NULL");
     ccz4_status st = check_ptr(Qo, "Qold");
@@ -1031,7 +1034,7 @@ ccz4_status ccz4_regrid_transfer(const ccz4_ctx *co, const double *Qo, const ccz
         auto it = co->index.find(key(l, i, j, k));
         return it == co->index.end() ? -1 : it->second;
     };
-    std::vector<RegridTask> tasks(cn->leaf.size());
+    tasks.resize(cn->leaf.size());
     for (size_t p = 0; p < cn->leaf.size(); ++p) {
         const auto &lf = cn->leaf[p];
         RegridTask &t = tasks[p];
@@ -1058,9 +1061,37 @@ ccz4_status ccz4_regrid_transfer(const ccz4_ctx *co, const double *Qo, const ccz
                     t.kid[w * 9 + v * 3 + u] = kid;
                 }
     }
+    return CCZ4_OK;
+}
+
+ccz4_status ccz4_regrid_transfer(const ccz4_ctx *co, const double *Qo, const ccz4_ctx *cn, double *Qn, void *stream)
+{
+    std::vector<RegridTask> tasks;
+    const ccz4_status st = regrid_tasks(co, Qo, cn, Qn, tasks);
+    if (st) return st;
     DevBuf<RegridTask> d;
     HIP_TRY(d.upload(tasks));
-    HIP_TRY(launch_regrid(Qo, Qn, d.p, (int32_t)tasks.size(), S(stream)));
+    HIP_TRY(launch_regrid(Qo, Qn, d.p, (int32_t)tasks.size(), 0, S(stream)));
+    HIP_TRY(hipStreamSynchronize(S(stream)));  // the task table is released on return
+    return CCZ4_OK;
+}
+
+// The interior of the new state is covered by the transfer, so of the initial data only the Sommerfeld
+// ghosts and their background are formed, and only what the transfer does not write is zeroed.
+ccz4_status ccz4_regrid_state(const ccz4_ctx *co, const double *Qo, ccz4_ctx *cn, double *Qn, int32_t scen,
+                              const double *sp, int32_t nsp, void *stream)
+{
+    std::vector<RegridTask> tasks;
+    InitArgs a{};
+    ccz4_status st = regrid_tasks(co, Qo, cn, Qn, tasks);
+    if (!st) st = init_args(scen, sp, nsp, a);
+    if (st) return st;
+    DevBuf<RegridTask> d;
+    HIP_TRY(d.upload(tasks));
+    HIP_TRY(launch_regrid(Qo, Qn, d.p, (int32_t)tasks.size(), 1, S(stream)));
+    HIP_TRY(launch_init_ghosts(Qn, cn->d_geom.p, cn->d_bf.p, cn->d_bg.p, (int32_t)cn->bface.size(), d.p, scen, a,
+                               S(stream)));
+    cn->bg_valid = true;
     HIP_TRY(hipStreamSynchronize(S(stream)));  // the task table is released on return
     return CCZ4_OK;
 }

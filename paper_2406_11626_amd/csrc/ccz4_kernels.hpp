@@ -11,8 +11,9 @@ struct InitArgs {
     double sp[16];
 };
 
-hipError_t launch_init(double *Q, const PatchGeom *geom, const uint8_t *bmask, int32_t npatch, int32_t scen,
-                       const InitArgs &a, hipStream_t st);
+hipError_t launch_init(double *Q, const PatchGeom *geom, int32_t npatch, int32_t scen, const InitArgs &a, hipStream_t st);
+hipError_t launch_init_ghosts(double *Q, const PatchGeom *geom, const BoundaryFace *bf, double *bg, int32_t nbf,
+                              const RegridTask *tasks, int32_t scen, const InitArgs &a, hipStream_t st);
 hipError_t launch_fill(double *Q, const FaceTask *tasks, int32_t ntask, int32_t transfer, hipStream_t st);
 hipError_t launch_copy_faces(double *Q, const int32_t *nbr, int32_t npatch, hipStream_t st);
 // right-hand side / fused stage launch configurations: bit 0 selects the LDS-staged kernel (else
@@ -75,7 +76,7 @@ hipError_t launch_rhs_sommerfeld(const double *Q, double *K, const PatchGeom *ge
 hipError_t launch_capture_bg(const double *Q, const BoundaryFace *bf, double *bg, int32_t nbf, hipStream_t st);
 hipError_t launch_rk4(int32_t s, double dt, const double *Qn, const double *K, double *acc, double *Qx,
                       int32_t npatch, const BoundaryFace *bf, int32_t nbf, hipStream_t st);
-hipError_t launch_regrid(const double *Qo, double *Qn, const RegridTask *tasks, int32_t n, hipStream_t st);
+hipError_t launch_regrid(const double *Qo, double *Qn, const RegridTask *tasks, int32_t n, int32_t blank, hipStream_t st);
 hipError_t launch_reconstruct(double *Q, const PatchGeom *geom, int32_t npatch, const int32_t *nbr, int32_t paxes,
                               int32_t gaxes, hipStream_t st);
 hipError_t launch_tracers(const double *Q, const PatchGeom *geom, int32_t npatch, int64_t n, double *pos,
