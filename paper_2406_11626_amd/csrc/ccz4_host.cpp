@@ -154,6 +154,7 @@ ccz4_status build_plan(ccz4_ctx *c, const ccz4_grid_desc *g)
     c->leaf = leaves;
     std::unordered_map<uint64_t, int> &index = c->index;
     index.clear();
+    index.reserve(leaves.size());
     for (size_t p = 0; p < leaves.size(); ++p)
         index[key(leaves[p][0], leaves[p][1], leaves[p][2], leaves[p][3])] = (int)p;
     auto find = [&](int l, int i, int j, int k) -> int {
@@ -252,19 +253,17 @@ ccz4_status build_plan(ccz4_ctx *c, const ccz4_grid_desc *g)
                 c->ph_pro.push_back(t);
             }
     }
-    // siblings
+    // siblings, a family at a time: every leaf above level 0 is a child of a refined cube
     c->sib.assign(leaves.size() * 27, -1);
-    for (size_t p = 0; p < leaves.size(); ++p) {
-        const int lev = leaves[p][0];
-        if (lev == 0) {
-            c->sib[p * 27] = -2;
-            continue;
-        }
-        const int pi = leaves[p][1] / 3, pj = leaves[p][2] / 3, pk = leaves[p][3] / 3;
+    for (size_t p = 0; p < leaves.size() && leaves[p][0] == 0; ++p) c->sib[p * 27] = -2;
+    for (const auto &cu : c->refined) {
+        int32_t fam[27];
         for (int w = 0; w < 3; ++w)
             for (int v = 0; v < 3; ++v)
                 for (int u = 0; u < 3; ++u)
-                    c->sib[p * 27 + (w * 3 + v) * 3 + u] = find(lev, 3 * pi + u, 3 * pj + v, 3 * pk + w);
+                    fam[(w * 3 + v) * 3 + u] = find(cu[0] + 1, 3 * cu[1] + u, 3 * cu[2] + v, 3 * cu[3] + w);
+        for (int n = 0; n < 27; ++n)
+            if (fam[n] >= 0) std::copy(fam, fam + 27, c->sib.begin() + (size_t)fam[n] * 27);
     }
     (void)maxlev;
     return CCZ4_OK;
@@ -329,30 +328,41 @@ const char *ccz4_last_error(void) { return g_err.c_str(); }
 static std::vector<int32_t> leaf_orders(const std::vector<std::array<int, 4>> &leaf)
 {
     const size_t n = leaf.size();
-    std::vector<int32_t> out(KV_ORDERS * n);
-    auto morton = [](uint32_t i, uint32_t j, uint32_t k) {
-        uint64_t m = 0;
-        for (int b = 0; b < 20; ++b)
-            m |= (uint64_t)((i >> b) & 1) << (3 * b) | (uint64_t)((j >> b) & 1) << (3 * b + 1) |
-                 (uint64_t)((k >> b) & 1) << (3 * b + 2);
-        return m;
+    std::vector<int32_t> out(KV_ORDERS * n), tmp(n);
+    auto spread = [](uint64_t v) {  // bit b of the low 20 to bit 3 b
+        v &= 0xfffff;
+        v = (v | v << 32) & 0x1f00000000ffffull;
+        v = (v | v << 16) & 0x1f0000ff0000ffull;
+        v = (v | v << 8) & 0x100f00f00f00f00full;
+        v = (v | v << 4) & 0x10c30c30c30c30c3ull;
+        return (v | v << 2) & 0x1249249249249249ull;
     };
+    // the leaves come in order 0, level by level; the others are stable radix sorts of each level, a
+    // byte at a time from the lowest, that pass over the bytes in which no two leaves differ (12^3 and
+    // 16^3 leaves on two levels: 0.2 ms, of which comparison sorts of all four orders took 1.9)
+    std::vector<uint64_t> key(n);
     for (int o = 0; o < KV_ORDERS; ++o) {
-        std::vector<std::pair<std::array<uint64_t, 3>, int32_t>> key(n);
+        int32_t *ord = out.data() + o * n;
+        for (size_t q = 0; q < n; ++q) ord[q] = (int32_t)q;
+        if (o == 0) continue;
         for (size_t p = 0; p < n; ++p) {
-            const uint64_t l = (uint64_t)leaf[p][0], i = (uint64_t)leaf[p][1], j = (uint64_t)leaf[p][2],
-                           k = (uint64_t)leaf[p][3];
-            std::array<uint64_t, 3> kk{l, 0, 0};
-            if (o == 0) kk[1] = (k << 40) | (j << 20) | i;
-            else if (o == 1) kk[1] = (i << 40) | (j << 20) | k;
-            else if (o == 2) {
-                kk[1] = ((k >> 2) << 40) | ((j >> 2) << 20) | (i >> 2);
-                kk[2] = ((k & 3) << 4) | ((j & 3) << 2) | (i & 3);
-            } else kk[1] = morton((uint32_t)i, (uint32_t)j, (uint32_t)k);
-            key[p] = {kk, (int32_t)p};
+            const uint64_t i = (uint64_t)leaf[p][1], j = (uint64_t)leaf[p][2], k = (uint64_t)leaf[p][3];
+            key[p] = o == 1 ? (i << 40) | (j << 20) | k
+                   : o == 2 ? ((k >> 2) << 40) | ((j >> 2) << 20) | (i >> 2)  // inside a brick as order 0
+                            : spread(i) | spread(j) << 1 | spread(k) << 2;
         }
-        std::sort(key.begin(), key.end());
-        for (size_t q = 0; q < n; ++q) out[o * n + q] = key[q].second;
+        for (size_t a = 0, b; a < n; a = b) {
+            uint64_t any = 0;
+            for (b = a; b < n && leaf[b][0] == leaf[a][0]; ++b) any |= key[b] ^ key[a];
+            for (int sh = 0; sh < 64; sh += 8) {
+                if (!((any >> sh) & 255)) continue;
+                uint32_t at[257] = {};
+                for (size_t q = a; q < b; ++q) ++at[((key[q] >> sh) & 255) + 1];
+                for (int d = 0; d < 256; ++d) at[d + 1] += at[d];
+                for (size_t q = a; q < b; ++q) tmp[at[(key[ord[q]] >> sh) & 255]++] = ord[q];
+                std::copy(tmp.begin(), tmp.begin() + (b - a), ord + a);
+            }
+        }
     }
     return out;
 }
