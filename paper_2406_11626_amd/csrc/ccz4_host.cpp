@@ -589,7 +589,7 @@ ccz4_status ccz4_rk4_stage(ccz4_ctx *c, int32_t s, double dt, const double *Qn, 
     if (!st) st = check_ptr(Qnext, "Qnext");
     if (st) return st;
     if (s < 3 && Qnext == Qn) return fail(CCZ4_EINVAL, "Qnext may alias Qn only at s = 3");
-    HIP_TRY(launch_rk4(s, dt, Qn, k, acc, Qnext, (int32_t)c->leaf.size(), c->d_bf.p, (int32_t)c->bface.size(),
+    HIP_TRY(launch_rk4(s, dt, Qn, k, acc, Qnext, (int32_t)c->leaf.size(), c->bface.empty() ? nullptr : c->d_pface.p,
                        S(stream)));
     return CCZ4_OK;
 }

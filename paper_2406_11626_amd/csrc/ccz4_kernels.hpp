@@ -75,7 +75,7 @@ hipError_t launch_rhs_sommerfeld(const double *Q, double *K, const PatchGeom *ge
                                  const double *bg, int32_t nbf, int32_t frozen, hipStream_t st);
 hipError_t launch_capture_bg(const double *Q, const BoundaryFace *bf, double *bg, int32_t nbf, hipStream_t st);
 hipError_t launch_rk4(int32_t s, double dt, const double *Qn, const double *K, double *acc, double *Qx,
-                      int32_t npatch, const BoundaryFace *bf, int32_t nbf, hipStream_t st);
+                      int32_t npatch, const int32_t *pface, hipStream_t st);
 hipError_t launch_regrid(const double *Qo, double *Qn, const RegridTask *tasks, int32_t n, int32_t blank, hipStream_t st);
 hipError_t launch_reconstruct(double *Q, const PatchGeom *geom, int32_t npatch, const int32_t *nbr, int32_t paxes,
                               int32_t gaxes, hipStream_t st);
