@@ -88,6 +88,19 @@ __device__ __forceinline__ void push_offsets(const int32_t *__restrict__ nbr, in
     }
 }
 
+// Whole rows.  A row's nine interior cells are 72 of its line's 128 bytes, and a line written in part
+// costs memory 2.4 times a whole one (rows of 4 GiB: 1.81 against 0.75 ms; it is read back to be
+// completed).  Where the output is a work buffer of a closed step, whose same-level x halos nobody reads,
+// the first seven lanes of a row therefore store their value once more, over the row's other seven
+// elements (x halo and padding): this returns where, relative to the lane's own cell at x.  The ghosts
+// of a Sommerfeld face are evolved and stay out of it; those that a fill writes are filled afterwards.
+__device__ __forceinline__ int row_rest(int x, const int32_t *__restrict__ pface, int p)
+{
+    const int k = x - 3, to = k < 3 ? k : k + 9;  // 0, 1, 2, 12, 13, 14, 15
+    if (k >= 7 || (pface && to < 15 && pface[6 * p + (k < 3 ? 0 : 1)] >= 0)) return 0;
+    return to - x;
+}
+
 // Fused stage on the Sommerfeld ghosts of boundary face fi: G_L of Qs combined at once into
 // stage s (one thread per ghost cell, all slots).
 __device__ __forceinline__ void stage_ghost_face(int fi, int idx, int32_t s, double dt, const double *__restrict__ Qs,

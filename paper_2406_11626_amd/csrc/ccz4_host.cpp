@@ -520,6 +520,19 @@ ccz4_status ccz4_set_background(ccz4_ctx *c, const double *Q, void *stream)
     return CCZ4_OK;
 }
 
+// the Neumann and level faces of the kinds asked for, slots v0..v1 - 1
+static hipError_t launch_fills(const ccz4_ctx *c, double *Q, int32_t kinds, int32_t v0, int32_t v1, hipStream_t st)
+{
+    const int32_t t = c->prm.transfer;
+    hipError_t e = hipSuccess;
+    if (kinds & CCZ4_FILL_NEUMANN) e = launch_fill(Q, c->d_phn.p, (int32_t)c->ph_neu.size(), t, v0, v1, st);
+    if (e == hipSuccess && (kinds & CCZ4_FILL_LEVELS)) {
+        e = launch_fill(Q, c->d_phr.p, (int32_t)c->ph_res.size(), t, v0, v1, st);
+        if (e == hipSuccess) e = launch_fill(Q, c->d_php.p, (int32_t)c->ph_pro.size(), t, v0, v1, st);
+    }
+    return e;
+}
+
 ccz4_status ccz4_fill_halos(ccz4_ctx *c, double *Q, void *stream)
 {
     if (!c) return fail(CCZ4_EINVAL, "ctx is NULL");
@@ -536,11 +549,7 @@ ccz4_status ccz4_fill_halos_kinds(ccz4_ctx *c, double *Q, int32_t kinds, void *s
     if (kinds & ~CCZ4_FILL_ALL) return fail(CCZ4_EINVAL, "unknown fill kinds");
     if ((kinds & CCZ4_FILL_SAME_LEVEL) && c->ncopy > 0)
         HIP_TRY(launch_copy_faces(Q, c->d_nbr.p, (int32_t)c->leaf.size(), S(stream)));
-    if (kinds & CCZ4_FILL_NEUMANN) HIP_TRY(launch_fill(Q, c->d_phn.p, (int32_t)c->ph_neu.size(), c->prm.transfer, S(stream)));
-    if (kinds & CCZ4_FILL_LEVELS) {
-        HIP_TRY(launch_fill(Q, c->d_phr.p, (int32_t)c->ph_res.size(), c->prm.transfer, S(stream)));
-        HIP_TRY(launch_fill(Q, c->d_php.p, (int32_t)c->ph_pro.size(), c->prm.transfer, S(stream)));
-    }
+    HIP_TRY(launch_fills(c, Q, kinds, 0, NV, S(stream)));
     return CCZ4_OK;
 }
 
@@ -632,7 +641,8 @@ static StageHalos step_halos(int32_t v, int32_t s)
 
 static hipError_t launch_reconstruct_halos(const ccz4_ctx *c, double *Q, const StageHalos &h, hipStream_t st)
 {
-    return launch_reconstruct(Q, c->d_geom.p, (int32_t)c->leaf.size(), c->d_nbr.p, h.paxes, h.gaxes, st);
+    return launch_reconstruct(Q, c->d_geom.p, (int32_t)c->leaf.size(), c->d_nbr.p, h.paxes, h.gaxes,
+                              c->bface.empty() ? nullptr : c->d_pface.p, st);
 }
 
 // One fused stage launch with the halo handling h.
@@ -651,21 +661,20 @@ static hipError_t launch_step(const ccz4_ctx *c, double *Qn, double *Q1, double 
 {
     double *src[4] = {Qn, Q1, Q2, Q1}, *dst[4] = {Q1, Q2, Q1, Qn};
     const int32_t v = c->kernel[precision];
-    auto fill = [&](double *Q) {
-        hipError_t e = launch_fill(Q, c->d_phn.p, (int32_t)c->ph_neu.size(), c->prm.transfer, st);
-        if (e == hipSuccess) e = launch_fill(Q, c->d_phr.p, (int32_t)c->ph_res.size(), c->prm.transfer, st);
-        if (e == hipSuccess) e = launch_fill(Q, c->d_php.p, (int32_t)c->ph_pro.size(), c->prm.transfer, st);
-        return e;
+    auto fill = [&](double *Q, int32_t v0, int32_t v1) {
+        return launch_fills(c, Q, CCZ4_FILL_NEUMANN | CCZ4_FILL_LEVELS, v0, v1, st);
     };
     hipError_t e = hipSuccess;
     for (int s = 0; s < 4 && e == hipSuccess; ++s) {
         const StageHalos h = step_halos(v, s);
         e = launch_stage_halos(c, s, dt, src[s], Qn, acc, dst[s], precision, v, h, st);
-        if (e == hipSuccess) e = fill(dst[s]);
-        if (c->prm.formulation == CCZ4_FORMULATION_SECOND_ORDER) {
-            // Algorithm 2: the auxiliaries of the new state from its primaries, then their halos
+        const bool so = c->prm.formulation == CCZ4_FORMULATION_SECOND_ORDER;
+        if (e == hipSuccess) e = fill(dst[s], 0, so ? SPHI + 1 : NV);
+        if (so) {
+            // Algorithm 2: the auxiliaries of the new state from its primaries gt, alpha, beta and phi
+            // (whose halos are in place now), then the halos of all other slots
             if (e == hipSuccess) e = launch_reconstruct_halos(c, dst[s], h, st);
-            if (e == hipSuccess) e = fill(dst[s]);
+            if (e == hipSuccess) e = fill(dst[s], SPHI + 1, NV);
         }
     }
     return e;

@@ -213,14 +213,14 @@ constexpr int FILL_SLOTS = HIGHER ? 1 : 4;
 
 template <int HIGHER>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_fill(
-    double *__restrict__ Q, const FaceTask *__restrict__ tasks, int32_t ntask)
+    double *__restrict__ Q, const FaceTask *__restrict__ tasks, int32_t ntask, int32_t v_first, int32_t v_end)
 {
     constexpr int SLOTS = FILL_SLOTS<HIGHER>;
     const int ti = blockIdx.x;
     const int idx = threadIdx.x;
     if (ti >= ntask || idx >= NFACE) return;
     // blockIdx.y picks the batch, so that a task's slots are filled in parallel
-    const int v_lo = (int)blockIdx.y * SLOTS, v_hi = v_lo + SLOTS < NV ? v_lo + SLOTS : NV;
+    const int v_lo = v_first + (int)blockIdx.y * SLOTS, v_hi = min(v_lo + SLOTS, v_end);
     const FaceTask tk = tasks[ti];
     int L, t1, t2;
     slab_coords(tk.axis, idx, L, t1, t2);
@@ -1159,7 +1159,7 @@ __global__ __launch_bounds__(256) void k_regrid(const double *__restrict__ Qo, d
 // Differences of primaries V0..V1-1, staged in LDS buffers 0.., into the auxiliaries of the cell.
 template <int V0, int V1, int XG>
 __device__ __forceinline__ void reconstruct_from_lds(const LdsCell<XG> &C, double *__restrict__ qb, int o,
-                                                     const int64_t (&pd)[3])
+                                                     const int64_t (&pd)[3], int rest)
 {
 #pragma unroll
     for (int v = V0; v < V1; ++v)
@@ -1174,6 +1174,7 @@ __device__ __forceinline__ void reconstruct_from_lds(const LdsCell<XG> &C, doubl
             const double u = v < SALPHA ? 0.5 * d : d;
             const int64_t e = (int64_t)dst * CS + o;
             qb[e] = u;
+            if (rest != 0) qb[e + rest] = u;
             if (pd[0] != 0) qb[e + pd[0]] = u;
 #pragma unroll
             for (int k = 1; k < 3; ++k)  // streamed, as the stage sink's y and z copies
@@ -1192,11 +1193,13 @@ __device__ __forceinline__ void reconstruct_from_lds(const LdsCell<XG> &C, doubl
 // primaries' halos must be filled, except the face halos normal to an axis of gaxes and shared with a
 // same-level leaf, which are read from that leaf's interior.  Every value within
 // three layers of a face shared with a same-level leaf and normal to an axis of paxes is also
-// written into that leaf's face halo (as the stage push does).
+// written into that leaf's face halo (as the stage push does).  Inside a step (XG, no copies) whole rows
+// are written (row_rest): a step of the second-order formulation on 16^3 leaves 17.43 -> 17.18 ms.
 template <int XG>
 __global__ __launch_bounds__(256) void k_reconstruct_lds(double *__restrict__ Q, const PatchGeom *__restrict__ geom,
                                                          int32_t npatch, const int32_t *__restrict__ nbr,
-                                                         int32_t paxes, int32_t gaxes)
+                                                         int32_t paxes, int32_t gaxes,
+                                                         const int32_t *__restrict__ pface)
 {
     __shared__ double lds[(SPHI + 1) * LDS_SLOT];
     const int64_t lb = xcd_logical_block(blockIdx.x, gridDim.x);
@@ -1222,21 +1225,21 @@ __global__ __launch_bounds__(256) void k_reconstruct_lds(double *__restrict__ Q,
     push_offsets(paxes ? nbr : nullptr, p, x, y, z, o, pd, paxes);
     const int slots[SPHI + 1] = {0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10};
     lds_round(lds, slots, lds_stager<XG>(qb, sl, hs));
-    if (act) reconstruct_from_lds<0, SPHI + 1, XG>(C, qb, o, pd);
+    if (act) reconstruct_from_lds<0, SPHI + 1, XG>(C, qb, o, pd, XG && !paxes ? row_rest(x, pface, p) : 0);
 }
 
 
 hipError_t launch_reconstruct(double *Q, const PatchGeom *geom, int32_t npatch, const int32_t *nbr, int32_t paxes,
-                              int32_t gaxes, hipStream_t st)
+                              int32_t gaxes, const int32_t *pface, hipStream_t st)
 {
     if (npatch <= 0) return hipSuccess;
     const int64_t nb = ((int64_t)npatch * 3 + 7) / 8 * 8;  // a multiple of 8 for the XCD block order
     if (gaxes & 1)
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_reconstruct_lds<1>), dim3((unsigned)nb), dim3(256), 0, st, Q, geom, npatch,
-                           nbr, paxes, gaxes);
+                           nbr, paxes, gaxes, pface);
     else
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_reconstruct_lds<0>), dim3((unsigned)nb), dim3(256), 0, st, Q, geom, npatch,
-                           nbr, paxes, gaxes);
+                           nbr, paxes, gaxes, pface);
     return hipGetLastError();
 }
 
@@ -1431,15 +1434,17 @@ hipError_t launch_init_ghosts(double *Q, const PatchGeom *geom, const BoundaryFa
     return hipGetLastError();
 }
 
-hipError_t launch_fill(double *Q, const FaceTask *tasks, int32_t ntask, int32_t transfer, hipStream_t st)
+hipError_t launch_fill(double *Q, const FaceTask *tasks, int32_t ntask, int32_t transfer, int32_t v0, int32_t v1,
+                       hipStream_t st)
 {
-    if (ntask <= 0) return hipSuccess;
+    if (ntask <= 0 || v1 <= v0) return hipSuccess;
+    auto batches = [&](int n) { return (unsigned)((v1 - v0 + n - 1) / n); };
     if (transfer == 1)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_fill<1>), dim3(ntask, (NV + FILL_SLOTS<1> - 1) / FILL_SLOTS<1>), dim3(256), 0,
-                           st, Q, tasks, ntask);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_fill<1>), dim3(ntask, batches(FILL_SLOTS<1>)), dim3(256), 0, st, Q, tasks,
+                           ntask, v0, v1);
     else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_fill<0>), dim3(ntask, (NV + FILL_SLOTS<0> - 1) / FILL_SLOTS<0>), dim3(256), 0,
-                           st, Q, tasks, ntask);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_fill<0>), dim3(ntask, batches(FILL_SLOTS<0>)), dim3(256), 0, st, Q, tasks,
+                           ntask, v0, v1);
     return hipGetLastError();
 }
 

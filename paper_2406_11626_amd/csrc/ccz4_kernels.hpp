@@ -14,7 +14,9 @@ struct InitArgs {
 hipError_t launch_init(double *Q, const PatchGeom *geom, int32_t npatch, int32_t scen, const InitArgs &a, hipStream_t st);
 hipError_t launch_init_ghosts(double *Q, const PatchGeom *geom, const BoundaryFace *bf, double *bg, int32_t nbf,
                               const RegridTask *tasks, int32_t scen, const InitArgs &a, hipStream_t st);
-hipError_t launch_fill(double *Q, const FaceTask *tasks, int32_t ntask, int32_t transfer, hipStream_t st);
+// the faces of a task list, slots v0..v1 - 1
+hipError_t launch_fill(double *Q, const FaceTask *tasks, int32_t ntask, int32_t transfer, int32_t v0, int32_t v1,
+                       hipStream_t st);
 hipError_t launch_copy_faces(double *Q, const int32_t *nbr, int32_t npatch, hipStream_t st);
 // right-hand side / fused stage launch configurations: bit 0 selects the LDS-staged kernel (else
 // the phased one), bit 1 the plain block order (else the XCD-grouped order), bits 2-3 the order in
@@ -78,7 +80,7 @@ hipError_t launch_rk4(int32_t s, double dt, const double *Qn, const double *K, d
                       int32_t npatch, const int32_t *pface, hipStream_t st);
 hipError_t launch_regrid(const double *Qo, double *Qn, const RegridTask *tasks, int32_t n, int32_t blank, hipStream_t st);
 hipError_t launch_reconstruct(double *Q, const PatchGeom *geom, int32_t npatch, const int32_t *nbr, int32_t paxes,
-                              int32_t gaxes, hipStream_t st);
+                              int32_t gaxes, const int32_t *pface, hipStream_t st);
 hipError_t launch_tracers(const double *Q, const PatchGeom *geom, int32_t npatch, int64_t n, double *pos,
                           const TracerSlots &sl, const LeafLookup &lk, double *out, double dt, int32_t advance, hipStream_t st);
 hipError_t launch_tag_tracers(const TrackBox *box, int32_t npatch, int64_t n, const double *pos, const TrackRadii &R,
