@@ -1201,7 +1201,7 @@ __global__ __launch_bounds__(256) void k_reconstruct_lds(double *__restrict__ Q,
                                                          int32_t paxes, int32_t gaxes,
                                                          const int32_t *__restrict__ pface)
 {
-    __shared__ double lds[(SPHI + 1) * LDS_SLOT];
+    __shared__ double lds[LDS_A], ldsb[(SPHI + 1 - LDS_NA) * LDS_SLOT];
     const int64_t lb = xcd_logical_block(blockIdx.x, gridDim.x);
     const int p = (int)(lb / 3);
     if (p >= npatch) return;  // uniform over the work-group
@@ -1212,6 +1212,7 @@ __global__ __launch_bounds__(256) void k_reconstruct_lds(double *__restrict__ Q,
     const HaloSrc hs = halo_sources(nbr, p, gaxes);
     LdsCell<XG> C;
     C.s = lds;
+    C.sb = ldsb;
     lds_cell_offsets(C, x, y, zl, hs);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -1223,8 +1224,12 @@ __global__ __launch_bounds__(256) void k_reconstruct_lds(double *__restrict__ Q,
     const int o = boff(x, y, z);
     int64_t pd[3];
     push_offsets(paxes ? nbr : nullptr, p, x, y, z, o, pd, paxes);
-    const int slots[SPHI + 1] = {0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10};
-    lds_round(lds, slots, lds_stager<XG>(qb, sl, hs));
+    const int slots[LDS_NA] = {0, 1, 2, 3, 4, 5, 6, 7, 8}, slotsb[SPHI + 1 - LDS_NA] = {9, 10};
+    const Stager sg = lds_stager<XG>(qb, sl, hs);
+    lds_issue(lds, slots, sg);
+    lds_issue(ldsb, slotsb, sg);
+    wait_memory<0>();
+    lds_swap();
     if (act) reconstruct_from_lds<0, SPHI + 1, XG>(C, qb, o, pd, XG && !paxes ? row_rest(x, pface, p) : 0);
 }
 

@@ -2,8 +2,8 @@
 // (3 x 9 x 9 = 243 cells, one work-group of 256 threads).
 //
 // Every evolved slot is copied once per evaluation from the patch box into LDS with gfx950's
-// direct global->LDS loads (16 bytes per lane, no registers involved), at most 15 slots per
-// round.  A slot occupies, in LDS, the slab's three planes in box layout (3 x 15 x 18 doubles,
+// direct global->LDS loads (16 bytes per lane, no registers involved), in parts of at most nine
+// slots.  A slot occupies, in LDS, the slab's three planes in box layout (3 x 15 x 18 doubles,
 // carrying the x and y halos) followed by the interior rows of the three planes below and the
 // three planes above the slab (6 x 9 rows x 10 doubles, columns x = 2..11).  Each face
 // halo is read either from the patch's own halo or straight from the interior of the same-level
@@ -11,18 +11,27 @@
 // derivative and Kreiss-Oliger sum is then read from LDS; a per-lane table maps the seven
 // z-neighbours of a cell into the own planes or the halo rows.
 //
+// There is room for fifteen slots and for one work-group per CU, one wave per SIMD, so nothing but the
+// work-group's own next copies can fill the time it computes.  The buffers therefore form two groups, of
+// nine and six slots, that take turns: while the lanes work on one group, the next part of the slots is
+// copied into the other (all fifteen buffers filled, waited for and used in turn before: right-hand side
+// of 1287 leaves 1.02 -> 0.98 ms, step on 4096 leaves 15.77 -> 15.27 ms, in mixed precision 15.25 ->
+// 14.75 ms, of the second-order formulation 17.2 -> 16.6 ms).
+//
 // The order of the equations is chosen so that each slot is staged exactly once:
-//   round 1: At, B      -> d tr(At), the shift-derivative contractions, the non-advective part of
+//   round 1: B | At     -> d tr(At), the shift-derivative contractions, the non-advective part of
 //                          the D equations, advection + KO of At and B (kept in registers)
-//   round 2: D (15)     -> contractions G1, H, U, E of d D; outputs of those D slots
-//   round 3: D (3), P, A, Ghat, K, Theta
+//   round 2: D (9 | 6)  -> contractions G1, H, U, E of d D; outputs of those D slots
+//   round 3: D (3), P, A | Ghat, K, Theta
 //                       -> last contractions and D outputs; Ricci tensor, nabla nabla alpha and
 //                          the Z terms; outputs At, K, Theta, Ghat, A, P; B and b without d b
-//   round 4: b, gt, alpha, beta, phi
+//   round 4: b, gt | alpha, beta, phi
 //                       -> outputs B, b, gt, alpha, beta, phi and K_0 = 0
 // The algebra is the one of ccz4_rhs_phased.hpp, term for term (App. B); T is double, or float
 // for the mixed-precision mode with the same split between FP64 and FP32 parts.
 #pragma once
+#include <type_traits>
+
 #include "ccz4_rhs_phased.hpp"
 
 namespace ccz4 {
@@ -48,7 +57,10 @@ constexpr int LDS_HROW = 10;                      // halo row: x = 2..11 (16-byt
 constexpr int LDS_HALO = 6 * 9 * LDS_HROW;        // 540 doubles
 constexpr int LDS_SLOT = LDS_OWN + LDS_HALO;      // 1350 doubles
 constexpr int LDS_NBUF = 15;
-constexpr int LDS_DOUBLES = LDS_NBUF * LDS_SLOT;  // 162000 bytes
+// The buffers lie in two LDS variables, 0..8 and 9..14: a wait for the copies into one then leaves those
+// into the other in flight (the compiler tracks them by variable).
+constexpr int LDS_NA = 9, LDS_NB = LDS_NBUF - LDS_NA;
+constexpr int LDS_A = LDS_NA * LDS_SLOT, LDS_B = LDS_NB * LDS_SLOT;  // 97200 and 64800 bytes
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 
@@ -155,12 +167,11 @@ __device__ __forceinline__ Stager lds_stager(const double *__restrict__ qp, int 
     return g;
 }
 
-// Issue the direct global->LDS copies of a round's N slots into buffers 0..N-1 once every wave is
-// done with the previous round's buffers; returns without waiting for them.
+// Issue the direct global->LDS copies of N slots into the buffers at `lds`, which no wave reads any
+// more (lds_swap); returns without waiting for them.
 template <int N>
 __device__ __forceinline__ void lds_issue(double *lds, const int (&slots)[N], const Stager &g)
 {
-    __syncthreads();
     double *dst = lds + g.wave * 128;
 #pragma unroll
     for (int j = 0; j < N; ++j)
@@ -175,26 +186,30 @@ __device__ __forceinline__ void lds_issue(double *lds, const int (&slots)[N], co
                                              (lds_void_t *)(dst + j * LDS_SLOT + (LDS_COPIES - 1) * 512), 16, 0, 0);
 }
 
-// Wait for every outstanding memory operation of the lane and make the staged slots visible to
-// the work-group.
-__device__ __forceinline__ void lds_wait()
+// Wait until at most N (0..63) memory operations of the wave are outstanding: all but its last N, in the
+// order of their issue, have landed.
+template <int N>
+__device__ __forceinline__ void wait_memory()
 {
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((N & 15) | (N >> 4) << 14 | 0x0f70);
+    asm volatile("" ::: "memory");
 }
 
-// Stage the N slots of a round and wait for them.
-template <int N>
-__device__ __forceinline__ void lds_round(double *lds, const int (&slots)[N], const Stager &g)
+// Work-group barrier that orders LDS reads and copies only: each wave's LDS reads are done, and the
+// copies that it waited for have landed for all (__syncthreads would wait for everything in flight).
+__device__ __forceinline__ void lds_swap()
 {
-    lds_issue(lds, slots, g);
-    lds_wait();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // LDS reads
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 }
 
 // One cell's view of the staged slab.
 template <int XG>
 struct LdsCell {
-    const double *s;  // LDS base
+    const double *s, *sb;  // LDS buffers 0..8, and the others
     int c;            // index of the cell in the own planes: zl * LPLANE + y * LROW + x (+ 2 with XG)
     int xo[7];        // with XG, index of the x-neighbour at offset k - 3
     int zo[7];        // index of the z-neighbour at offset k - 3
@@ -205,7 +220,7 @@ struct LdsCell {
 template <int XG>
 __device__ __forceinline__ double lv(const LdsCell<XG> &c, int b, int a, int k)
 {
-    const double *f = c.s + b * LDS_SLOT;
+    const double *f = b < LDS_NA ? c.s + b * LDS_SLOT : c.sb + (b - LDS_NA) * LDS_SLOT;
     return k == 0 ? f[c.c]
                   : (a == 0 ? f[XG ? c.xo[k + 3] : c.c + k] : (a == 1 ? f[c.c + k * LROW] : f[c.zo[k + 3]]));
 }
@@ -370,7 +385,7 @@ __device__ __forceinline__ void load_metric_with(Ld ld, double gd[6], double igd
 // The LDS buffer that holds slot v during round r of rhs_slab_lds, or -1 (see the round lists).
 __device__ __forceinline__ constexpr int round_buffer(int r, int v)
 {
-    if (r == 1) return (v >= SAT && v < SAT + 6) ? v - SAT : ((v >= SB && v < SB + 9) ? 6 + v - SB : -1);
+    if (r == 1) return (v >= SAT && v < SAT + 6) ? LDS_NA + v - SAT : -1;  // At's part: B's buffers are reused
     if (r == 2) return v >= SD && v < SD + 15 ? v - SD : -1;
     if (r == 3)
         return (v >= SD + 15 && v < SD + 18) ? v - SD - 15
@@ -396,7 +411,7 @@ template <int R, int XG>
 __device__ __forceinline__ double pw(const PatchBuf &qp, uint32_t ob, const LdsCell<XG> &C, int v)
 {
     const int b = round_buffer(R, v);
-    if (b >= 0) return C.s[b * LDS_SLOT + C.c];
+    if (b >= 0) return lv(C, b, 0, 0);
     return qp.load(ob, v);
 }
 
@@ -533,8 +548,6 @@ __device__ __forceinline__ void ghat_sector(const LdsCell<XG> &C, const RhsParam
 }
 
 // Output slots of rounds 2, 3 and 4, in the order of the round's output buffer.
-__device__ constexpr int R2_OUT[15] = {SD, SD + 1, SD + 2, SD + 3, SD + 4, SD + 5, SD + 6, SD + 7,
-                                       SD + 8, SD + 9, SD + 10, SD + 11, SD + 12, SD + 13, SD + 14};
 __device__ constexpr int R3_OUT[20] = {SD + 15, SD + 16, SD + 17, SAT, SAT + 1, SAT + 2, SAT + 3,
                                        SAT + 4, SAT + 5, SK, STHETA, SGHAT, SGHAT + 1, SGHAT + 2,
                                        SA, SA + 1, SA + 2, SP, SP + 1, SP + 2};
@@ -542,14 +555,13 @@ __device__ constexpr int R4_OUT[24] = {SB, SB + 1, SB + 2, SB + 3, SB + 4, SB + 
                                        SB + 8, SBB, SBB + 1, SBB + 2, SG, SG + 1, SG + 2, SG + 3,
                                        SG + 4, SG + 5, SALPHA, SBETA, SBETA + 1, SBETA + 2, SPHI, SK0};
 
-// A round's outputs go to the sink in two halves: its global loads (the RK4 combine reads Q^n
-// and the accumulator), issued together, and its stores.  Between the two the caller issues the
-// staging of the following round, so that those copies and the sink's loads are in flight
-// together, and waits for both; the stores are then left in flight over the next barrier.
+// Outputs go to the sink in two halves: the global loads (the RK4 combine reads Q^n and the accumulator),
+// issued together before the buffers of the outputs' slots are given up, and the stores, made while the
+// next part is computed or copied.
 // Right-hand side of the lane's cell of slab sl of the patch at qp.  Every lane of the
 // work-group must call this (staging and barriers); only lanes with act = true compute.
 template <typename T, int LOP, int XG, typename Sink>
-__device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, double *lds, int sl, bool act, uint32_t o0,
+__device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, double *lds, double *ldsb, int sl, bool act, uint32_t o0,
                                              const LdsCell<XG> &C0, const RhsParams &p, Sink &snk, const HaloSrc &hs)
 {
     const Stager sg = lds_stager<XG>(qp, sl, hs);
@@ -589,18 +601,19 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
 #pragma unroll
         for (int k = 0; k < 6; ++k) gd0[k] = qb.load(o, SG + k);
     }
-    T al0, At0[HOLD_ALL ? 6 : 1], B0[HOLD_ALL ? 9 : 1], D0[HOLD_ALL ? 18 : 1];
+    T al0, At0[HOLD_ALL ? 6 : 1], B0[9], D0[HOLD_ALL ? 18 : 1];
     auto held_metric = [&](double gd[6], double igd[6], double &detg, T g[6], T ig[6]) {
         load_metric_with<T>([&](int v) -> double { return fresh(gd0[v - SG]); }, gd, igd, detg, g, ig);
     };
-    double ro2[15], ro3[20], ro4[24];  // each round's outputs, handed to the sink after the round
+    double ro2a[9], ro2b[6], ro3[20], ro4[24];  // each round's outputs, handed to the sink after the round
 
     // ------------------------------------------------------------ round 1: At, B
-    {
-        const int r1[15] = {SAT, SAT + 1, SAT + 2, SAT + 3, SAT + 4, SAT + 5, SB, SB + 1, SB + 2,
-                            SB + 3, SB + 4, SB + 5, SB + 6, SB + 7, SB + 8};
-        lds_round(lds, r1, sg);
-    }
+    const int rB[9] = {SB, SB + 1, SB + 2, SB + 3, SB + 4, SB + 5, SB + 6, SB + 7, SB + 8};
+    const int rAt[6] = {SAT, SAT + 1, SAT + 2, SAT + 3, SAT + 4, SAT + 5};
+    lds_issue(lds, rB, sg);
+    lds_issue(ldsb, rAt, sg);
+    wait_memory<2 * 6>();  // B has landed
+    lds_swap();
     if (act) {
         {  // B: advection + KO, GB^i = gt^kl d_(k B_l)^i, sdBtr_k = d_(k B_l)^l, and the shift
            // terms of the D equations
@@ -615,7 +628,8 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
             for (int l = 0; l < 3; ++l)
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
-                    const SlotDeriv sd = stencils<LOP>(C, 6 + 3 * l + i, be, p.advection);
+                    const SlotDeriv sd = stencils<LOP>(C, 3 * l + i, be, p.advection);
+                    B0[3 * l + i] = fresh(cvt<T>(lv(C, 3 * l + i, 0, 0)));
                     advkoB[3 * l + i] = gdrv ? sd.a + sd.k : 0.0;
 #pragma unroll
                     for (int k = 0; k < 3; ++k) dB[l][i][k] = sd.d[k];
@@ -651,7 +665,12 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
                     }
             }
         }
-        CCZ4_PHASE_BARRIER();
+    }
+    wait_memory<0>();  // At has landed
+    lds_swap();
+    const int rDa[9] = {SD, SD + 1, SD + 2, SD + 3, SD + 4, SD + 5, SD + 6, SD + 7, SD + 8};
+    lds_issue(lds, rDa, sg);
+    if (act) {
         {  // At: advection + KO, d_k tr(At), and the rest of the D equations
             const LdsCell<XG> C = fresh(C0);
             const uint32_t o = fresh(o0);
@@ -659,7 +678,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
             double dA[6][3];
 #pragma unroll
             for (int s = 0; s < 6; ++s) {
-                const SlotDeriv sd = stencils<LOP>(C, s, be, p.advection);
+                const SlotDeriv sd = stencils<LOP>(C, LDS_NA + s, be, p.advection);
                 advkoAt[s] = sd.a + sd.k;
 #pragma unroll
                 for (int k = 0; k < 3; ++k) dA[s][k] = sd.d[k];
@@ -676,7 +695,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
 #pragma unroll
                 for (int s = 0; s < 6; ++s) D[k][s] = cvt<T>(q(SD + 6 * k + s));
 #pragma unroll
-                for (int i = 0; i < 3; ++i) Bm[k][i] = cvt<T>(q(SB + 3 * k + i));
+                for (int i = 0; i < 3; ++i) Bm[k][i] = fresh(B0[3 * k + i]);
             }
             const T trB = Bm[0][0] + Bm[1][1] + Bm[2][2];
             const T trAt = tr6(ig, At);
@@ -687,8 +706,6 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
                 for (int s = 0; s < 6; ++s) At0[s] = fresh(At[s]);
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
-#pragma unroll
-                    for (int i = 0; i < 3; ++i) B0[3 * k + i] = fresh(Bm[k][i]);
 #pragma unroll
                     for (int s = 0; s < 6; ++s) D0[6 * k + s] = fresh(D[k][s]);
                 }
@@ -733,47 +750,53 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
     }
 
     // ------------------------------------------------------------ round 2: D_x.., D_y.., D_zxx..D_zxz
-    {
-        const int r2[15] = {SD, SD + 1, SD + 2, SD + 3, SD + 4, SD + 5, SD + 6, SD + 7,
-                            SD + 8, SD + 9, SD + 10, SD + 11, SD + 12, SD + 13, SD + 14};
-        lds_round(lds, r2, sg);
-    }
-    if (act) {
+    wait_memory<0>();
+    lds_swap();
+    const int rDb[6] = {SD + 9, SD + 10, SD + 11, SD + 12, SD + 13, SD + 14};
+    lds_issue(ldsb, rDb, sg);
+    auto D_slots = [&](auto first, auto count, double *out) {
         const LdsCell<XG> C = fresh(C0);
         double gd[6], igd[6], detg;
         T g[6], ig[6];
         held_metric(gd, igd, detg, g, ig);
+#pragma unroll
+        for (int n = 0; n < count.value; ++n) {
+            const int j = first.value + n;
+            const SlotDeriv sd = stencils<LOP>(C, j, be, p.advection);
+            dD_accumulate<T>(sd.d, j, ig, G1, H, U, E);
+            keep(out[n], sd.a + static_cast<double>(partD[j / 6][j % 6]) + sd.k);
+        }
+    };
+    if (act) {
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
 #pragma unroll
             for (int j = 0; j < 3; ++j) G1[i][j] = H[i][j] = U[i][j] = T(0);
             E[i] = E[i + 3] = T(0);
         }
-#pragma unroll
-        for (int j = 0; j < 15; ++j) {
-            const SlotDeriv sd = stencils<LOP>(C, j, be, p.advection);
-            dD_accumulate<T>(sd.d, j, ig, G1, H, U, E);
-            keep(ro2[j], sd.a + static_cast<double>(partD[j / 6][j % 6]) + sd.k);
-        }
+        D_slots(std::integral_constant<int, 0>{}, std::integral_constant<int, 9>{}, ro2a);
     }
-
-    {
-        const int r3[14] = {SD + 15, SD + 16, SD + 17, SP, SP + 1, SP + 2, SA, SA + 1, SA + 2,
-                            SGHAT, SGHAT + 1, SGHAT + 2, SK, STHETA};
-        double qa[15], qc[15];
-        if (act) snk.load(R2_OUT, qa, qc, [&](int v) -> double { return pw<2>(qb, o0, C0, v); });
-        lds_issue(lds, r3, sg);
-        __builtin_amdgcn_s_waitcnt(0);  // the sink's loads and this wave's copies have landed
-        if (act) snk.store(R2_OUT, ro2, qa, qc);
-    }
-    __syncthreads();  // every wave's copies have landed; the stores may still be in flight
+    const int r2a[9] = {SD, SD + 1, SD + 2, SD + 3, SD + 4, SD + 5, SD + 6, SD + 7, SD + 8};
+    const int r2b[6] = {SD + 9, SD + 10, SD + 11, SD + 12, SD + 13, SD + 14};
+    double qa[9], qc[9], qb6[6], qd6[6];
+    wait_memory<0>();
+    if (act) snk.load(r2a, qa, qc, [&](int v) -> double { return pw<2>(qb, o0, C0, v); });
+    lds_swap();
+    const int r3a[9] = {SD + 15, SD + 16, SD + 17, SP, SP + 1, SP + 2, SA, SA + 1, SA + 2};
+    lds_issue(lds, r3a, sg);
+    if (act) D_slots(std::integral_constant<int, 9>{}, std::integral_constant<int, 6>{}, ro2b);
+    wait_memory<0>();
+    if (act) snk.load(r2b, qb6, qd6, [&](int v) -> double { return pw<2>(qb, o0, C0, v); });
+    lds_swap();
+    const int r3b[5] = {SGHAT, SGHAT + 1, SGHAT + 2, SK, STHETA};
+    lds_issue(ldsb, r3b, sg);
+    if (act) snk.store(r2a, ro2a, qa, qc);
 
     // ------------------------------------------------------------ round 3
     // buffers: 0..2 D_zyy, D_zyz, D_zzz; 3..5 P; 6..8 A; 9..11 Ghat; 12 K; 13 Theta
     if (act) {
-        const LdsCell<XG> C = fresh(C0);
-        const uint32_t o = fresh(o0);
         {
+            const LdsCell<XG> C = fresh(C0);
             double gd[6], igd[6], detg;
             T g[6], ig[6];
             held_metric(gd, igd, detg, g, ig);
@@ -784,6 +807,13 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
                 keep(ro3[j], sd.a + static_cast<double>(partD[2][3 + j]) + sd.k);
             }
         }
+        snk.store(r2b, ro2b, qb6, qd6);
+    }
+    wait_memory<0>();
+    lds_swap();
+    if (act) {
+        const LdsCell<XG> C = fresh(C0);
+        const uint32_t o = fresh(o0);
         {  // ---- Ricci sector: At, K, Theta; the curl term of B
             const uint32_t o1 = fresh(o);
             auto q1 = [&](int v) -> double { return pw<3>(qb, o1, C, v); };
@@ -1096,15 +1126,17 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
     }
 
     {
-        const int r4[14] = {SBB, SBB + 1, SBB + 2, SG, SG + 1, SG + 2, SG + 3, SG + 4, SG + 5,
-                            SALPHA, SBETA, SBETA + 1, SBETA + 2, SPHI};
-        double qa[20], qc[20];
-        if (act) snk.load(R3_OUT, qa, qc, [&](int v) -> double { return pw<3>(qb, o0, C0, v); });
-        lds_issue(lds, r4, sg);
-        __builtin_amdgcn_s_waitcnt(0);  // the sink's loads and this wave's copies have landed
-        if (act) snk.store(R3_OUT, ro3, qa, qc);
+        const int r4a[9] = {SBB, SBB + 1, SBB + 2, SG, SG + 1, SG + 2, SG + 3, SG + 4, SG + 5};
+        const int r4b[5] = {SALPHA, SBETA, SBETA + 1, SBETA + 2, SPHI};
+        double qa3[20], qc3[20];
+        if (act) snk.load(R3_OUT, qa3, qc3, [&](int v) -> double { return pw<3>(qb, o0, C0, v); });
+        lds_swap();
+        lds_issue(lds, r4a, sg);
+        lds_issue(ldsb, r4b, sg);
+        wait_memory<2 * 5>();
+        if (act) snk.store(R3_OUT, ro3, qa3, qc3);
     }
-    __syncthreads();  // every wave's copies have landed; the stores may still be in flight
+    lds_swap();
 
     // ------------------------------------------------------------ round 4
     // buffers: 0..2 b; 3..8 gt; 9 alpha; 10..12 beta; 13 phi
@@ -1136,6 +1168,13 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
         // gt_ij, alpha, beta^i, phi: the pointwise parts from round 3 and the KO sums; K_0: 0
 #pragma unroll
         for (int s = 0; s < 6; ++s) keep(ro4[12 + s], pwG[s] + stencils(C, 3 + s).k);
+    }
+    wait_memory<0>();
+    lds_swap();
+    if (act) {
+        const LdsCell<XG> C = fresh(C0);
+        const uint32_t o = fresh(o0);
+        auto q = [&](int v) -> double { return pw<4>(qb, o, C, v); };
         keep(ro4[18], pwA + stencils(C, 9).k);
 #pragma unroll
         for (int i = 0; i < 3; ++i) {

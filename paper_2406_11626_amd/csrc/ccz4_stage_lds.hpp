@@ -13,12 +13,13 @@ namespace ccz4 {
 // LDS-staged variants: one work-group per (patch, z-slab), every lane takes part in staging;
 // the 151 KB of LDS leave one work-group per CU, so the waves may use the whole register file.
 template <int XG>
-__device__ __forceinline__ void lds_cell_setup(double *lds, int sl, const PatchGeom &g, const RhsParams &prm,
+__device__ __forceinline__ void lds_cell_setup(double *lds, double *ldsb, int sl, const PatchGeom &g, const RhsParams &prm,
                                                const HaloSrc &hs, LdsCell<XG> &C, uint32_t &ob, bool &act)
 {
     int x, y, zl;
     act = slab_cell((int)threadIdx.x, x, y, zl);
     C.s = lds;
+    C.sb = ldsb;
     lds_cell_offsets(C, x, y, zl, hs);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -34,7 +35,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     RhsParams prm, const BoundaryFace *__restrict__ bf, const double *__restrict__ bg,
     const int32_t *__restrict__ pface, int32_t linear, const int32_t *__restrict__ order)
 {
-    __shared__ double lds[LDS_DOUBLES];
+    __shared__ double lds[LDS_A], ldsb[LDS_B];
     const int64_t lb = linear ? (int64_t)blockIdx.x : xcd_logical_block(blockIdx.x, gridDim.x);
     if (lb / 3 >= npatch) return;  // uniform over the work-group
     const int p = __builtin_amdgcn_readfirstlane(order[lb / 3]);
@@ -44,9 +45,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     uint32_t ob;
     bool act;
     const HaloSrc hs{};
-    lds_cell_setup(lds, sl, g, prm, hs, C, ob, act);
+    lds_cell_setup(lds, ldsb, sl, g, prm, hs, C, ob, act);
     LdsRhsSink snk{PatchBuf{K + (int64_t)p * PS}, ob, prm.formulation};
-    rhs_slab_lds<T, LOP, 0>(Q + (int64_t)p * PS, lds, sl, act, ob, C, prm, snk, hs);
+    rhs_slab_lds<T, LOP, 0>(Q + (int64_t)p * PS, lds, ldsb, sl, act, ob, C, prm, snk, hs);
     if (pface) {
         const int32_t frozen = prm.shift == 0;
         ghost_slab_cells(p, sl, pface, [&](int fi, int idx) { rhs_ghost_cell(fi, idx, Q, K, geom, bf, bg, frozen); });
@@ -227,7 +228,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int32_t *__restrict__ nbr, int32_t paxes, int32_t gaxes, int32_t linear,
     const int32_t *__restrict__ order)
 {
-    __shared__ double lds[LDS_DOUBLES];
+    __shared__ double lds[LDS_A], ldsb[LDS_B];
     const int64_t lb = linear ? (int64_t)blockIdx.x : xcd_logical_block(blockIdx.x, nb_slab);
     if (lb / 3 >= npatch) return;  // uniform over the work-group
     const int p = __builtin_amdgcn_readfirstlane(order[lb / 3]);
@@ -237,7 +238,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     uint32_t ob;
     bool act;
     const HaloSrc hs = halo_sources(nbr, p, gaxes);
-    lds_cell_setup(lds, sl, g, prm, hs, C, ob, act);
+    lds_cell_setup(lds, ldsb, sl, g, prm, hs, C, ob, act);
     LdsStageSink<CLOSED> snk;
     snk.qn.base = Qn + (int64_t)p * PS;
     snk.acc.base = acc + (int64_t)p * PS;
@@ -252,7 +253,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         (void)slab_cell((int)threadIdx.x, x, y, zl);
         push_offsets(paxes ? nbr : nullptr, p, x, y, zl + 3 + 3 * sl, (int)(ob >> 3), snk.pd, paxes);
     }
-    rhs_slab_lds<T, LOP, CLOSED>(Qs + (int64_t)p * PS, lds, sl, act, ob, C, prm, snk, hs);
+    rhs_slab_lds<T, LOP, CLOSED>(Qs + (int64_t)p * PS, lds, ldsb, sl, act, ob, C, prm, snk, hs);
     if (pface) {
         const int32_t frozen = prm.shift == 0;
         ghost_slab_cells(p, sl, pface, [&](int fi, int idx) {
