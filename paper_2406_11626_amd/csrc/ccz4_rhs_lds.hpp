@@ -255,14 +255,64 @@ __device__ __forceinline__ void lds_cell_offsets(LdsCell<XG> &C, int x, int y, i
     }
 }
 
+// The 19 points that the differences of one staged slot take, read from LDS at once (the compiler barrier
+// keeps the reads of one slot from being hoisted above those of the one before).
+struct Points {
+    double q[3][6], own;
+    double i12[3], koc[3];  // of the cell
+};
+
 template <int XG>
-__device__ __forceinline__ double fd(const LdsCell<XG> &c, int b, int a)
+__device__ __forceinline__ Points points(const LdsCell<XG> &c, int b)
+{
+    Points r;
+    r.own = lv(c, b, 0, 0);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) r.q[a][k] = lv(c, b, a, k < 3 ? k - 3 : k - 2);
+        r.i12[a] = c.i12[a];
+        r.koc[a] = c.koc[a];
+    }
+    asm volatile("" ::: "memory");
+    return r;
+}
+__device__ __forceinline__ double lv(const Points &p, int, int a, int k)
+{
+    return k == 0 ? p.own : p.q[a][k < 0 ? k + 3 : k + 2];
+}
+
+// Calls f(n, points of buffer b + n) for n = 0..N - 1, a slot's points read while the one before it is
+// worked on, one read to three vector instructions: the work-group's four waves leave every barrier
+// together and would otherwise take turns, all queueing at the LDS and then all computing (right-hand
+// side of 1287 leaves 0.98 -> 0.96 ms; a fused stage, bound by memory, gains nothing).
+template <int N, int XG, typename F>
+__device__ __forceinline__ void each_slot(const LdsCell<XG> &C, int b, F f)
+{
+    Points cur = points(C, b);
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        Points next = cur;
+        if (n + 1 < N) next = points(C, b + n + 1);
+        f(n, cur);
+#pragma unroll
+        for (int k = 0; k < 17; ++k) {  // one LDS read, three vector instructions
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        cur = next;
+    }
+}
+
+template <typename Cell>
+__device__ __forceinline__ double fd(const Cell &c, int b, int a)
 {
     return (8.0 * (lv(c, b, a, 1) - lv(c, b, a, -1)) - (lv(c, b, a, 2) - lv(c, b, a, -2))) * c.i12[a];
 }
 
-template <int XG>
-__device__ __forceinline__ double ko_axis_lds(const LdsCell<XG> &c, int b, int a)
+template <typename Cell>
+__device__ __forceinline__ double ko_axis_lds(const Cell &c, int b, int a)
 {
 #if CCZ4_KO_PRINTED_ORDER
 #pragma clang fp contract(off)
@@ -275,8 +325,8 @@ __device__ __forceinline__ double ko_axis_lds(const LdsCell<XG> &c, int b, int a
 #endif
 }
 
-template <int XG>
-__device__ __forceinline__ double ko(const LdsCell<XG> &c, int b)
+template <typename Cell>
+__device__ __forceinline__ double ko(const Cell &c, int b)
 {
     const double kx = c.koc[0] * ko_axis_lds(c, b, 0), ky = c.koc[1] * ko_axis_lds(c, b, 1),
                  kz = c.koc[2] * ko_axis_lds(c, b, 2);
@@ -424,8 +474,8 @@ struct SlotDeriv {
     double a;  // advection beta^k d_k (central or lopsided), with the 4-argument form only
 };
 
-template <int XG>
-__device__ __forceinline__ SlotDeriv stencils(const LdsCell<XG> &c, int b)
+template <typename Cell>
+__device__ __forceinline__ SlotDeriv stencils(const Cell &c, int b = 0)
 {
     SlotDeriv r;
 #pragma unroll
@@ -439,8 +489,8 @@ __device__ __forceinline__ SlotDeriv stencils(const LdsCell<XG> &c, int b)
 // ... and the advection term with shift be: the central derivatives (LOP = 0), or the lopsided
 // stencils of App. D (LOP = 1, pairing `mode` as RhsParams::advection) from the same staged
 // points.  LOP is a template parameter so that the central kernel carries no lopsided code.
-template <int LOP, int XG>
-__device__ __forceinline__ SlotDeriv stencils(const LdsCell<XG> &c, int b, const double be[3], int32_t mode)
+template <int LOP, typename Cell>
+__device__ __forceinline__ SlotDeriv stencils(const Cell &c, int b, const double be[3], int32_t mode)
 {
     SlotDeriv r;
 #pragma unroll
@@ -624,16 +674,13 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
             double dB[3][3][3];  // dB[l][i][k] = d_k B_l^i
 #pragma unroll
             for (int i = 0; i < 3; ++i) GB[i] = sdBtr[i] = T(0);
+            each_slot<9>(C, 0, [&](int n, const Points &q) {
+                const SlotDeriv sd = stencils<LOP>(q, 0, be, p.advection);
+                B0[n] = fresh(cvt<T>(q.own));
+                keep(advkoB[n], gdrv ? sd.a + sd.k : 0.0);
 #pragma unroll
-            for (int l = 0; l < 3; ++l)
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    const SlotDeriv sd = stencils<LOP>(C, 3 * l + i, be, p.advection);
-                    B0[3 * l + i] = fresh(cvt<T>(lv(C, 3 * l + i, 0, 0)));
-                    advkoB[3 * l + i] = gdrv ? sd.a + sd.k : 0.0;
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) dB[l][i][k] = sd.d[k];
-                }
+                for (int k = 0; k < 3; ++k) keep(dB[n / 3][n % 3][k], sd.d[k]);
+            });
 #pragma unroll
             for (int k = 0; k < 3; ++k)
 #pragma unroll
@@ -676,13 +723,12 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
             const uint32_t o = fresh(o0);
             auto q = [&](int v) -> double { return pw<1>(qb, o, C, v); };
             double dA[6][3];
+            each_slot<6>(C, LDS_NA, [&](int s, const Points &q) {
+                const SlotDeriv sd = stencils<LOP>(q, 0, be, p.advection);
+                keep(advkoAt[s], sd.a + sd.k);
 #pragma unroll
-            for (int s = 0; s < 6; ++s) {
-                const SlotDeriv sd = stencils<LOP>(C, LDS_NA + s, be, p.advection);
-                advkoAt[s] = sd.a + sd.k;
-#pragma unroll
-                for (int k = 0; k < 3; ++k) dA[s][k] = sd.d[k];
-            }
+                for (int k = 0; k < 3; ++k) keep(dA[s][k], sd.d[k]);
+            });
             double gd[6], igd[6], detg;
             T g[6], ig[6];
             held_metric(gd, igd, detg, g, ig);
@@ -759,13 +805,12 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
         double gd[6], igd[6], detg;
         T g[6], ig[6];
         held_metric(gd, igd, detg, g, ig);
-#pragma unroll
-        for (int n = 0; n < count.value; ++n) {
+        each_slot<count.value>(C, first.value, [&](int n, const Points &q) {
             const int j = first.value + n;
-            const SlotDeriv sd = stencils<LOP>(C, j, be, p.advection);
+            const SlotDeriv sd = stencils<LOP>(q, 0, be, p.advection);
             dD_accumulate<T>(sd.d, j, ig, G1, H, U, E);
             keep(out[n], sd.a + static_cast<double>(partD[j / 6][j % 6]) + sd.k);
-        }
+        });
     };
     if (act) {
 #pragma unroll
@@ -800,12 +845,11 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
             double gd[6], igd[6], detg;
             T g[6], ig[6];
             held_metric(gd, igd, detg, g, ig);
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                const SlotDeriv sd = stencils<LOP>(C, j, be, p.advection);
+            each_slot<3>(C, 0, [&](int j, const Points &q) {
+                const SlotDeriv sd = stencils<LOP>(q, 0, be, p.advection);
                 dD_accumulate<T>(sd.d, 15 + j, ig, G1, H, U, E);
                 keep(ro3[j], sd.a + static_cast<double>(partD[2][3 + j]) + sd.k);
-            }
+            });
         }
         snk.store(r2b, ro2b, qb6, qd6);
     }
@@ -1142,14 +1186,11 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
     // buffers: 0..2 b; 3..8 gt; 9 alpha; 10..12 beta; 13 phi
     if (act) {
         const LdsCell<XG> C = fresh(C0);
-        const uint32_t o = fresh(o0);
-        auto q = [&](int v) -> double { return pw<4>(qb, o, C, v); };
         // B_k^i and b^i
         if (gdrv) {
             const T ff = cvt<T>(p.f);
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const SlotDeriv sb = stencils<LOP>(C, i, be, p.advection);
+            each_slot<3>(C, 0, [&](int i, const Points &pt) {
+                const SlotDeriv sb = stencils<LOP>(pt, 0, be, p.advection);
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
                     T t = ff * cvt<T>(sb.d[k]);
@@ -1157,8 +1198,8 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
                     t += curl[k][i];
                     keep(ro4[3 * k + i], advkoB[3 * k + i] + static_cast<double>(t));
                 }
-                keep(ro4[9 + i], rGb[i] + sb.a - p.eta * q(SBB + i) + sb.k);
-            }
+                keep(ro4[9 + i], rGb[i] + sb.a - p.eta * pt.own + sb.k);
+            });
         } else {
 #pragma unroll
             for (int s = 0; s < 9; ++s) keep(ro4[s], 0.0);
@@ -1166,8 +1207,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
             for (int i = 0; i < 3; ++i) keep(ro4[9 + i], 0.0);
         }
         // gt_ij, alpha, beta^i, phi: the pointwise parts from round 3 and the KO sums; K_0: 0
-#pragma unroll
-        for (int s = 0; s < 6; ++s) keep(ro4[12 + s], pwG[s] + stencils(C, 3 + s).k);
+        each_slot<6>(C, 3, [&](int s, const Points &pt) { keep(ro4[12 + s], pwG[s] + ko(pt, 0)); });
     }
     wait_memory<0>();
     lds_swap();
@@ -1175,16 +1215,13 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
         const LdsCell<XG> C = fresh(C0);
         const uint32_t o = fresh(o0);
         auto q = [&](int v) -> double { return pw<4>(qb, o, C, v); };
-        keep(ro4[18], pwA + stencils(C, 9).k);
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            if (gdrv)
-                keep(ro4[19 + i], (static_cast<double>(bB[i] + cvt<T>(p.f) * cvt<T>(q(SBB + i))) +
-                                   stencils(C, 10 + i).k));
-            else
-                keep(ro4[19 + i], 0.0);
-        }
-        keep(ro4[22], pwPhi + stencils(C, 13).k);
+        each_slot<5>(C, LDS_NA, [&](int n, const Points &pt) {
+            const double k = ko(pt, 0);
+            if (n == 0) keep(ro4[18], pwA + k);
+            else if (n == 4) keep(ro4[22], pwPhi + k);
+            else if (gdrv) keep(ro4[18 + n], static_cast<double>(bB[n - 1] + cvt<T>(p.f) * cvt<T>(q(SBB + n - 1))) + k);
+            else keep(ro4[18 + n], 0.0);
+        });
         keep(ro4[23], 0.0);
     }
     {
