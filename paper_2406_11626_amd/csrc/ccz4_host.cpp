@@ -1213,14 +1213,13 @@ ccz4_status ccz4_tag_refine(ccz4_ctx *c, const double *Q, double theta_r, double
     if (st) return st;
     if (!tags) return fail(CCZ4_EINVAL, "tags is NULL");
     const size_t np = c->leaf.size();
-    if (c->d_hm.n < np * 4 * NCELL) HIP_TRY(c->d_hm.alloc(np * 4 * NCELL));
+    if (c->d_hm.n < np * NCELL) HIP_TRY(c->d_hm.alloc(np * NCELL));
     double *ind = indicator;
     DevBuf<double> tmp;
     if (!ind) {
         HIP_TRY(tmp.alloc(np * 3));
         ind = tmp.p;
     }
-    HIP_TRY(launch_constraints(Q, c->d_hm.p, c->d_geom.p, (int32_t)np, 0.0, c->d_part.p, c->d_out3.p, S(stream)));
     HIP_TRY(launch_tags(Q, c->d_hm.p, c->d_geom.p, c->d_sib.p, (int32_t)np, theta_r, theta_c, max_level, tags, ind,
                         S(stream)));
     if (tmp.p) {

@@ -625,8 +625,10 @@ constexpr int PLANE = ROWS * PITCH;
 constexpr int OWN = PN * PLANE, OWN_PAIRS = PN * ROWS * PAIRS;
 constexpr int SLOT = OWN + 4 * PN * LDS_HROW;  // + interior rows (x = 2..11) of the planes z = 1, 2, 12, 13
 constexpr int SLOT_PAIRS = SLOT / 2;
-constexpr int LANES = 768, BATCH = 4, ROUNDS = 7;
-static_assert(SLOT_PAIRS > LANES && SLOT_PAIRS <= 2 * LANES && 2 * BATCH * SLOT * 8 <= 160 * 1024, "staging");
+constexpr int LANES = 768, ROUNDS = 7;
+template <int H_ONLY>
+constexpr int BATCH = H_ONLY ? 3 : 4;  // slots a round: D and P, or all of them
+static_assert(SLOT_PAIRS > LANES && SLOT_PAIRS <= 2 * LANES && 2 * BATCH<0> * SLOT * 8 <= 160 * 1024, "staging");
 
 // the slot staged as number j: D, P, At, K
 __device__ __forceinline__ constexpr int slot(int j)
@@ -685,7 +687,8 @@ __device__ __forceinline__ void take(const double *__restrict__ f, const Cell &C
     asm volatile("" : "+v"(X.S), "+v"(X.trdP), "+v"(X.M[0]), "+v"(X.M[1]), "+v"(X.M[2]) : : "memory");
 }
 
-// H and M_i from the sums, the metric's inverse and phi
+// H and M_i (or H only) from the sums, the metric's inverse and phi
+template <int H_ONLY>
 __device__ __forceinline__ void finish(const Sums &X, const double ig[6], double phi, double hm[4])
 {
     auto mult = [](int s) { return s == 0 || s == 3 || s == 5 ? 1.0 : 2.0; };
@@ -771,6 +774,7 @@ __device__ __forceinline__ void finish(const Sums &X, const double ig[6], double
 #pragma unroll
         for (int j = 0; j < 3; ++j) AA += Am[i][j] * Am[j][i];
     hm[0] = phi * phi * R + (2.0 / 3.0) * X.K * X.K - AA;
+    if (H_ONLY) return;
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         double t = X.M[i];
@@ -787,11 +791,16 @@ __device__ __forceinline__ void finish(const Sums &X, const double ig[6], double
 }
 }  // namespace cons
 
+// H_ONLY: what the refinement criterion takes, H of every cell (HM: one value a cell) and nothing else: At
+// and K are read pointwise, the slots that are only tested for finiteness not at all, and no norms are
+// summed: 4390 lines a leaf instead of 6980.
+template <int H_ONLY>
 __global__ __launch_bounds__(cons::LANES) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_constraints_lds(
     const double *__restrict__ Q, double *__restrict__ HM, const PatchGeom *__restrict__ geom, int32_t npatch,
     double r_excise, double *__restrict__ part)
 {
     using namespace cons;
+    constexpr int BATCH = cons::BATCH<H_ONLY>;
     __shared__ double bufa[BATCH * SLOT], bufb[BATCH * SLOT];
     __shared__ double red[LANES / 64][4];
     const int p = (int)xcd_logical_block(blockIdx.x, gridDim.x);
@@ -805,11 +814,14 @@ __global__ __launch_bounds__(cons::LANES) __attribute__((amdgpu_waves_per_eu(3, 
         const int zl = m / 9, k9 = (m + 6 * zl) % 9, yr = k9 / 2 + (k9 % 2 ? 5 : 0), x = cc % 9 + 3;
         const uint32_t ob = 8u * (uint32_t)boff(x, yr + 3, zl + 3);
         // the slots that are only tested, and the metric and phi, first: they are used first
-        double g[6], other = 0.0, rest[SAT - 7 + SD - STHETA + 1];
+        double g[6], other = 0.0, rest[H_ONLY ? 7 : SAT - 7 + SD - STHETA + 1];
 #pragma unroll
         for (int v = 0; v < 6; ++v) g[v] = qb.load(ob, SG + v);
         const double phi = qb.load(ob, SPHI);
-        {
+        if constexpr (H_ONLY) {
+#pragma unroll
+            for (int s = 0; s < 7; ++s) rest[s] = qb.load(ob, s < 6 ? SAT + s : SK);
+        } else {
             int n = 0;
 #pragma unroll
             for (int v = 6; v < SPHI; ++v) rest[n++] = qb.load(ob, v);
@@ -859,13 +871,19 @@ __global__ __launch_bounds__(cons::LANES) __attribute__((amdgpu_waves_per_eu(3, 
         for (int a = 0; a < 3; ++a) C.i12[a] = 1.0 / (12.0 * G.dx[a]);
         double ig[6], detg;
         metric_inverse(g, ig, detg);
-        // 0 times a finite number is 0, anything else is not
-#pragma unroll
-        for (int v = 0; v < 6; ++v) other += 0.0 * g[v];
-#pragma unroll
-        for (int n = 0; n < (int)(sizeof(rest) / sizeof(rest[0])); ++n) other += 0.0 * rest[n];
-        asm volatile("" : "+v"(other));
         Sums X;
+        if constexpr (H_ONLY) {
+#pragma unroll
+            for (int s = 0; s < 6; ++s) X.At[s] = rest[s];
+            X.K = rest[6];
+        } else {
+            // 0 times a finite number is 0, anything else is not
+#pragma unroll
+            for (int v = 0; v < 6; ++v) other += 0.0 * g[v];
+#pragma unroll
+            for (int n = 0; n < (int)(sizeof(rest) / sizeof(rest[0])); ++n) other += 0.0 * rest[n];
+            asm volatile("" : "+v"(other));
+        }
         X.S = X.trdP = X.M[0] = X.M[1] = X.M[2] = 0.0;
         // A barrier that orders the LDS accesses only: __syncthreads would wait for the copies in flight
         // too.  Every LDS read before it has returned (lgkmcnt), and none is moved across (the clobbers).
@@ -888,7 +906,7 @@ __global__ __launch_bounds__(cons::LANES) __attribute__((amdgpu_waves_per_eu(3, 
     take<BATCH * R + 0>(buf + 0 * SLOT, C, ig, X);               \
     take<BATCH * R + 1>(buf + 1 * SLOT, C, ig, X);               \
     take<BATCH * R + 2>(buf + 2 * SLOT, C, ig, X);               \
-    take<BATCH * R + 3>(buf + 3 * SLOT, C, ig, X);               \
+    if constexpr (!H_ONLY) take<4 * R + 3>(buf + 3 * SLOT, C, ig, X); \
     if (R + 2 < ROUNDS) {                                        \
         barrier();                                               \
         issue(buf, R + 2);                                       \
@@ -902,8 +920,10 @@ __global__ __launch_bounds__(cons::LANES) __attribute__((amdgpu_waves_per_eu(3, 
         CONS_ROUND(6, bufa)
 #undef CONS_ROUND
         double hm[4];
-        finish(X, ig, phi, hm);
-        if (act) {
+        finish<H_ONLY>(X, ig, phi, hm);
+        if constexpr (H_ONLY) {
+            if (act) HM[(int64_t)p * NCELL + (zl * 9 + yr) * 9 + x - 3] = hm[0];
+        } else if (act) {
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
                 other += 0.0 * X.P[i];
@@ -930,6 +950,7 @@ __global__ __launch_bounds__(cons::LANES) __attribute__((amdgpu_waves_per_eu(3, 
             }
         }
     }
+    if (H_ONLY) return;
     // the work-group's sums, in a fixed order: lanes, then waves
 #pragma unroll
     for (int s = 32; s > 0; s >>= 1) {
@@ -985,8 +1006,8 @@ __global__ __launch_bounds__(1024) void k_reduce_parts(const double *__restrict_
 }
 
 // ------------------------------------------------------------------ refinement tags
-// one block (256 threads) per leaf; HM must hold this leaf's H
-__global__ void k_tag_indicator(const double *__restrict__ Q, const double *__restrict__ HM,
+// one block (256 threads) per leaf; H: one value a cell
+__global__ void k_tag_indicator(const double *__restrict__ Q, const double *__restrict__ H,
                                 const PatchGeom *__restrict__ geom, double *__restrict__ ind)
 {
     const int p = blockIdx.x;
@@ -1005,7 +1026,7 @@ __global__ void k_tag_indicator(const double *__restrict__ Q, const double *__re
             gc = fmax(gc, fabs(ph2 * ph2 - chi));
             ga = fmax(ga, fabs(Qp[SALPHA * CS + o + st[a]] - al));
         }
-        hm = fmax(hm, fabs(HM[(int64_t)p * 4 * NCELL + c]));
+        hm = fmax(hm, fabs(H[(int64_t)p * NCELL + c]));
     }
     __shared__ double red[3][256];
     red[0][threadIdx.x] = gc;
@@ -1571,19 +1592,24 @@ hipError_t launch_constraints(const double *Q, double *HM, const PatchGeom *geom
                               double r_excise, double *part, double *out3, hipStream_t st)
 {
     const int64_t nb = constraints_blocks(npatch);
-    hipLaunchKernelGGL(k_constraints_lds, dim3((unsigned)nb), dim3(cons::LANES), 0, st, Q, HM, geom, npatch, r_excise, part);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_constraints_lds<0>), dim3((unsigned)nb), dim3(cons::LANES), 0, st, Q, HM, geom,
+                       npatch, r_excise, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_reduce_parts, dim3(1), dim3(1024), 0, st, part, nb, out3);
     return hipGetLastError();
 }
 
-hipError_t launch_tags(const double *Q, const double *HM, const PatchGeom *geom, const int32_t *sib,
+hipError_t launch_tags(const double *Q, double *H, const PatchGeom *geom, const int32_t *sib,
                        int32_t npatch, double theta_r, double theta_c, int32_t max_level, int8_t *tags,
                        double *ind, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_tag_indicator, dim3(npatch), dim3(256), 0, st, Q, HM, geom, ind);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_constraints_lds<1>), dim3((unsigned)constraints_blocks(npatch)), dim3(cons::LANES),
+                       0, st, Q, H, geom, npatch, 0.0, nullptr);
     hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_tag_indicator, dim3(npatch), dim3(256), 0, st, Q, H, geom, ind);
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_tag_decide, dim3((npatch + 127) / 128), dim3(128), 0, st, ind, sib, geom, npatch,
                        theta_r, theta_c, max_level, tags);

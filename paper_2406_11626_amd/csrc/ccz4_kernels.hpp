@@ -88,7 +88,7 @@ hipError_t launch_tag_tracers(const TrackBox *box, int32_t npatch, int64_t n, co
 int64_t constraints_blocks(int32_t npatch);
 hipError_t launch_constraints(const double *Q, double *HM, const PatchGeom *geom, int32_t npatch,
                               double r_excise, double *part, double *out3, hipStream_t st);
-hipError_t launch_tags(const double *Q, const double *HM, const PatchGeom *geom, const int32_t *sib,
+hipError_t launch_tags(const double *Q, double *H, const PatchGeom *geom, const int32_t *sib,
                        int32_t npatch, double theta_r, double theta_c, int32_t max_level, int8_t *tags,
                        double *ind, hipStream_t st);
 
