@@ -639,9 +639,9 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
     T bB[3];
     // Values of the cell that several rounds use, held in registers from round 1 on instead of read
     // again from memory in each round (the lines have left L2 by then: such reads were a third of a
-    // stage's L2 misses).  With FP64 algebra the register file takes the shift and the metric (a step
-    // on 4096 leaves: 16.19 -> 15.79 ms; with alpha and At, or the nine B, too it spills: 15.88 and
-    // 16.04 ms); with FP32 algebra alpha, At, B and D fit as well, as FP32 values (16.62 -> 15.28 ms).
+    // stage's L2 misses).  With FP64 algebra the register file takes the shift, the metric, alpha and At
+    // (a step on 4096 leaves: 16.19 -> 15.79 ms by the first two, 14.98 -> 14.79 ms by the others); with
+    // the nine B too it spills.  With FP32 algebra B and D fit as well, as FP32 values (16.62 -> 15.28 ms).
     constexpr bool HOLD_ALL = sizeof(T) == 4;
     double be[3], gd0[6];  // loaded while round 1 is staged
     {
@@ -651,7 +651,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
 #pragma unroll
         for (int k = 0; k < 6; ++k) gd0[k] = qb.load(o, SG + k);
     }
-    T al0, At0[HOLD_ALL ? 6 : 1], B0[9], D0[HOLD_ALL ? 18 : 1];
+    T al0, At0[6], B0[9], D0[HOLD_ALL ? 18 : 1];
     auto held_metric = [&](double gd[6], double igd[6], double &detg, T g[6], T ig[6]) {
         load_metric_with<T>([&](int v) -> double { return fresh(gd0[v - SG]); }, gd, igd, detg, g, ig);
     };
@@ -746,10 +746,10 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
             const T trB = Bm[0][0] + Bm[1][1] + Bm[2][2];
             const T trAt = tr6(ig, At);
             const T al = cvt<T>(q(SALPHA));
-            if constexpr (HOLD_ALL) {
-                al0 = fresh(al);
+            al0 = fresh(al);
 #pragma unroll
-                for (int s = 0; s < 6; ++s) At0[s] = fresh(At[s]);
+            for (int s = 0; s < 6; ++s) At0[s] = fresh(At[s]);
+            if constexpr (HOLD_ALL) {
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
 #pragma unroll
@@ -995,7 +995,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
                 for (int j = i; j < 3; ++j)
                     DDa[sym(i, j)] = T(0.5) * cvt<T>(fd(C, 6 + j, i) + fd(C, 6 + i, j)) -
                                      (Gam[0][sym(i, j)] * A[0] + Gam[1][sym(i, j)] * A[1] + Gam[2][sym(i, j)] * A[2]);
-            const T al = HOLD_ALL ? fresh(al0) : cvt<T>(q1(SALPHA)), Kt = cvt<T>(q1(SK)), Th = cvt<T>(q1(STHETA));
+            const T al = fresh(al0), Kt = cvt<T>(q1(SK)), Th = cvt<T>(q1(STHETA));
             T X[6];
 #pragma unroll
             for (int s = 0; s < 6; ++s) X[s] = -DDa[s] + al * RZ[s];
@@ -1005,7 +1005,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
             const T lapal = phi2 * tr6(ig, DDa);
             T At[6];
 #pragma unroll
-            for (int s = 0; s < 6; ++s) At[s] = HOLD_ALL ? fresh(At0[HOLD_ALL ? s : 0]) : cvt<T>(q1(SAT + s));
+            for (int s = 0; s < 6; ++s) At[s] = fresh(At0[s]);
             T Am[3][3];
 #pragma unroll
             for (int i = 0; i < 3; ++i)
@@ -1092,7 +1092,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
 #pragma unroll
                 for (int s = 0; s < 6; ++s) D[k][s] = HOLD_ALL ? fresh(D0[HOLD_ALL ? 6 * k + s : 0]) : cvt<T>(q1(SD + 6 * k + s));
 #pragma unroll
-            for (int s = 0; s < 6; ++s) At[s] = HOLD_ALL ? fresh(At0[HOLD_ALL ? s : 0]) : cvt<T>(q1(SAT + s));
+            for (int s = 0; s < 6; ++s) At[s] = fresh(At0[s]);
             T Dup[3][6], Gl[3][6], Gt[3][6], Gtv[3];
             raise_D(ig, D, Dup);
             christoffel(ig, D, Gl, Gt, Gtv);
@@ -1112,7 +1112,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
                 for (int i = 0; i < 3; ++i) Bm[k][i] = HOLD_ALL ? fresh(B0[HOLD_ALL ? 3 * k + i : 0]) : cvt<T>(q1(SB + 3 * k + i));
             }
             const T trB = Bm[0][0] + Bm[1][1] + Bm[2][2];
-            const T al = HOLD_ALL ? fresh(al0) : cvt<T>(q1(SALPHA)), Kt = cvt<T>(q1(SK)), Th = cvt<T>(q1(STHETA));
+            const T al = fresh(al0), Kt = cvt<T>(q1(SK)), Th = cvt<T>(q1(STHETA));
             T dG[3], Zl[3];
 #pragma unroll
             for (int i = 0; i < 3; ++i) dG[i] = cvt<T>(q1(SGHAT + i)) - Gtv[i];
@@ -1135,7 +1135,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
                 for (int i = 0; i < 3; ++i) Bm[k][i] = HOLD_ALL ? fresh(B0[HOLD_ALL ? 3 * k + i : 0]) : cvt<T>(q1(SB + 3 * k + i));
             }
             const T trB = Bm[0][0] + Bm[1][1] + Bm[2][2];
-            const T al = HOLD_ALL ? fresh(al0) : cvt<T>(q1(SALPHA)), Kt = cvt<T>(q1(SK)), Th = cvt<T>(q1(STHETA)), K0 = cvt<T>(q1(SK0));
+            const T al = fresh(al0), Kt = cvt<T>(q1(SK)), Th = cvt<T>(q1(STHETA)), K0 = cvt<T>(q1(SK0));
             const double phid = q1(SPHI);
             const bool onelog = p.slicing == 1;
             const T ga = onelog ? T(2) / al : T(1);
@@ -1173,7 +1173,11 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
         const int r4a[9] = {SBB, SBB + 1, SBB + 2, SG, SG + 1, SG + 2, SG + 3, SG + 4, SG + 5};
         const int r4b[5] = {SALPHA, SBETA, SBETA + 1, SBETA + 2, SPHI};
         double qa3[20], qc3[20];
-        if (act) snk.load(R3_OUT, qa3, qc3, [&](int v) -> double { return pw<3>(qb, o0, C0, v); });
+        if (act)
+            snk.load(R3_OUT, qa3, qc3, [&](int v) -> double {
+                if (sizeof(T) == 8 && v >= SAT && v < SAT + 6) return static_cast<double>(At0[v - SAT]);
+                return pw<3>(qb, o0, C0, v);
+            });
         lds_swap();
         lds_issue(lds, r4a, sg);
         lds_issue(ldsb, r4b, sg);
