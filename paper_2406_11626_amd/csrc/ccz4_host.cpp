@@ -45,6 +45,10 @@ template <typename T>
 struct DevBuf {
     T *p = nullptr;
     size_t n = 0;
+    DevBuf() = default;
+    DevBuf(const DevBuf &) = delete;
+    DevBuf &operator=(const DevBuf &) = delete;
+    ~DevBuf() { release(); }  // the table of a regrid goes with the call
     hipError_t upload(const std::vector<T> &v)
     {
         release();
