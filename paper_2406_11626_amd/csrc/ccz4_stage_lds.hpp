@@ -66,7 +66,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // so that acc (= A) is written by s = 1 and read by s = 3 only: two of its three writes and two of its
 // three reads go, and Q_s itself is at hand in LDS for most slots.  The differences are of nearly
 // equal numbers (exact up to the roundings of Q1..Q3), so the rounding is that of the other form.
-template <int CLOSED>
+// The line between the two (STREAM): 256 MB of last-level cache, 157 leaves.  Steps with ordinary and with
+// nontemporal stores: 27 leaves 0.203 and 0.213 ms, 100 leaves 0.602 and 0.613, 125 leaves 0.692 and 0.692,
+// 150 leaves 0.741 and 0.730, 4096 leaves 14.82 and 14.62, three levels in mixed precision 20.97 and 20.58.
+constexpr int64_t STREAM_LEAVES = (int64_t)256 * 1024 * 1024 / (PS * 8);
+
+template <int CLOSED, int STREAM>
 struct LdsStageSink {
     PatchBuf qn, acc, qx;
     uint32_t ob, oc;   // byte offsets of the cell in a slot of the state and of the accumulator
@@ -104,9 +109,10 @@ struct LdsStageSink {
     // flight together, then the combines and stores.  The acc stream, and
     // Q^n at s > 0, are touched once per launch, so they go through the caches as nontemporal:
     // the lines the slab staging shares between work-groups stay in L2 longer (2-3% per stage).
-    // At s = 0, Q^n is Q_s and its loads hit the lines just staged, which must stay.  Q_next
-    // keeps ordinary stores: its rows are partial lines that merge in L2 with the copies the
-    // neighbours push into the same lines.
+    // At s = 0, Q^n is Q_s and its loads hit the lines just staged, which must stay.  Q_next keeps
+    // ordinary stores where neighbours push copies into its rows, which merge in L2.  Stages 0..2 of a
+    // closed step push none: their stores are nontemporal too once a state no longer fits the last-level
+    // cache, where the next stage would find it (STREAM_LEAVES).
     template <int N, typename Use, typename Own>
     __device__ __forceinline__ void load_some(const int (&slots)[N], double (&a)[N], double (&b)[N], Own own,
                                               Use use) const
@@ -166,7 +172,7 @@ struct LdsStageSink {
             }
 #pragma unroll
             for (int j = 0; j < N; ++j)
-                if (use(slots[j])) qx.store(r[j], ob, slots[j]);
+                if (use(slots[j])) qx.store<STREAM ? BUF_NT : BUF_DEFAULT>(r[j], ob, slots[j]);
             push(slots, r, use);
         } else {
             const double w = (1.0 / 6.0) * dt;
@@ -220,7 +226,7 @@ struct LdsStageSink {
     }
 };
 
-template <typename T, int LOP, int CLOSED>
+template <typename T, int LOP, int CLOSED, int STREAM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_stage_lds(
     const double *__restrict__ Qs, const double *__restrict__ Qn, double *__restrict__ acc, double *__restrict__ Qx,
     const PatchGeom *__restrict__ geom, int32_t npatch, int32_t nb_slab, RhsParams prm, int32_t s, double dt,
@@ -239,7 +245,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     bool act;
     const HaloSrc hs = halo_sources(nbr, p, gaxes);
     lds_cell_setup(lds, ldsb, sl, g, prm, hs, C, ob, act);
-    LdsStageSink<CLOSED> snk;
+    LdsStageSink<CLOSED, STREAM> snk;
     snk.qn.base = Qn + (int64_t)p * PS;
     snk.acc.base = acc + (int64_t)p * PS;
     snk.qx.base = Qx + (int64_t)p * PS;
@@ -274,12 +280,13 @@ template <typename T, int LOP>
 hipError_t launch_stage_lds(const StageLaunch &a, hipStream_t st)
 {
     const dim3 g((unsigned)a.blocks), b(256);
-    if (a.closed)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stage_lds<T, LOP, 1>), g, b, 0, st, a.Qs, a.Qn, a.acc, a.Qx, a.geom, a.npatch,
-                           a.blocks, a.p, a.s, a.dt, a.bf, a.bg, a.pface, a.nbr, a.paxes, a.gaxes, a.linear, a.order);
-    else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_stage_lds<T, LOP, 0>), g, b, 0, st, a.Qs, a.Qn, a.acc, a.Qx, a.geom, a.npatch,
-                           a.blocks, a.p, a.s, a.dt, a.bf, a.bg, a.pface, a.nbr, a.paxes, a.gaxes, a.linear, a.order);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, g, b, 0, st, a.Qs, a.Qn, a.acc, a.Qx, a.geom, a.npatch, a.blocks, a.p, a.s, a.dt, a.bf,
+                           a.bg, a.pface, a.nbr, a.paxes, a.gaxes, a.linear, a.order);
+    };
+    if (!a.closed) go(k_stage_lds<T, LOP, 0, 0>);
+    else if (a.s < 3 && a.npatch > STREAM_LEAVES) go(k_stage_lds<T, LOP, 1, 1>);
+    else go(k_stage_lds<T, LOP, 1, 0>);
     return hipGetLastError();
 }
 
