@@ -203,19 +203,20 @@ __global__ __launch_bounds__(COPY_LANES) void k_copy_faces(double *__restrict__ 
         }
 }
 
-// The other kinds: one block per (face task, batch of slots), one thread per slab cell.  The operators of
-// two and nine points go through four slots a block (a level pair's fills are bound by the partial lines
-// they touch: 0.33 ms on 5760 leaves of two levels, 136 coarse faces, with four slots or eight).  The
-// higher-order prolongation reads 27 cells per slot, whose loads need the registers: one slot a block
-// (1.09 -> 0.40 ms on three levels of 5760 leaves; two slots 0.50).
-template <int HIGHER>
-constexpr int FILL_SLOTS = HIGHER ? 1 : 4;
+// The other kinds: one block per (face task, batch of eight slots), one thread per slab cell.  Bound by the
+// partial lines that a level pair's fills touch, and by the loads in flight.  The higher-order prolongation
+// keeps 27 offsets and weights for all its slots, 198 registers: two waves per SIMD.  At four it spills 72
+// of them, and then one slot a block, which forms them for every slot anew, takes longest (144 coarse
+// faces, 0.40 ms at two waves; at four 1.08 ms, and 1.90 ms with one slot a block).  The operators of two
+// and nine points need few registers; more than four waves per SIMD only press on the caches (144 and 480
+// coarse faces, 0.350 and 1.11 ms; six waves 0.358 and 1.24 ms, four slots a block 0.376 and 1.21 ms).
+constexpr int FILL_SLOTS = 8;
 
 template <int HIGHER>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_fill(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HIGHER ? 2 : 4, HIGHER ? 2 : 4))) void k_fill(
     double *__restrict__ Q, const FaceTask *__restrict__ tasks, int32_t ntask, int32_t v_first, int32_t v_end)
 {
-    constexpr int SLOTS = FILL_SLOTS<HIGHER>;
+    constexpr int SLOTS = FILL_SLOTS;
     const int ti = blockIdx.x;
     const int idx = threadIdx.x;
     if (ti >= ntask || idx >= NFACE) return;
@@ -1496,12 +1497,12 @@ hipError_t launch_fill(double *Q, const FaceTask *tasks, int32_t ntask, int32_t 
                        hipStream_t st)
 {
     if (ntask <= 0 || v1 <= v0) return hipSuccess;
-    auto batches = [&](int n) { return (unsigned)((v1 - v0 + n - 1) / n); };
+    const unsigned batches = (unsigned)((v1 - v0 + FILL_SLOTS - 1) / FILL_SLOTS);
     if (transfer == 1)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_fill<1>), dim3(ntask, batches(FILL_SLOTS<1>)), dim3(256), 0, st, Q, tasks,
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_fill<1>), dim3(ntask, batches), dim3(256), 0, st, Q, tasks,
                            ntask, v0, v1);
     else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_fill<0>), dim3(ntask, batches(FILL_SLOTS<0>)), dim3(256), 0, st, Q, tasks,
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_fill<0>), dim3(ntask, batches), dim3(256), 0, st, Q, tasks,
                            ntask, v0, v1);
     return hipGetLastError();
 }
