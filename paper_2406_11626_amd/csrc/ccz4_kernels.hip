@@ -616,20 +616,25 @@ __global__ __launch_bounds__(RK4_LANES) void k_rk4(int32_t s, double dt, const d
 // One work-group per leaf, one cell per lane: the leaf's nine planes and the four planes and rows at
 // distance two that a first difference reaches are staged once (a z-slab each, as the stage kernel
 // takes them, stages 60% more lines; and holding all 84 differences needed the whole register file at
-// one wave per SIMD).  Four slots at a time pass through two buffers, one in flight while the other is
+// one wave per SIMD; small meshes take slabs all the same, below).  Four slots at a time pass through two buffers, one in flight while the other is
 // read.  Bound by the staging: on 16^3 leaves 1.19 -> 0.74 ms (2.26 GB of algorithmic bytes, 0.41 ms at
 // the rate of a large read).
 namespace cons {
 constexpr int ROWS = 13;                    // staged rows of a plane, y = 1..13
 constexpr int PITCH = 18, PAIRS = PITCH / 2;  // a row's 16 doubles, the eighth pair repeated
 constexpr int PLANE = ROWS * PITCH;
-constexpr int OWN = PN * PLANE, OWN_PAIRS = PN * ROWS * PAIRS;
-constexpr int SLOT = OWN + 4 * PN * LDS_HROW;  // + interior rows (x = 2..11) of the planes z = 1, 2, 12, 13
-constexpr int SLOT_PAIRS = SLOT / 2;
-constexpr int LANES = 768, ROUNDS = 7;
-template <int H_ONLY>
-constexpr int BATCH = H_ONLY ? 3 : 4;  // slots a round: D and P, or all of them
-static_assert(SLOT_PAIRS > LANES && SLOT_PAIRS <= 2 * LANES && 2 * BATCH<0> * SLOT * 8 <= 160 * 1024, "staging");
+// The staging of a work-group that takes NPL planes of a leaf: its own planes, then the interior rows
+// (x = 2..11) of the two planes below and the two above them.
+template <int H_ONLY, int NPL>
+struct Staging {
+    static constexpr int OWN = NPL * PLANE, OWN_PAIRS = NPL * ROWS * PAIRS;
+    static constexpr int SLOT = OWN + 4 * PN * LDS_HROW, SLOT_PAIRS = SLOT / 2;
+    static constexpr int CELLS = NPL * PN * PN, LANES = (CELLS + 63) / 64 * 64;
+    static constexpr int COPIES = (SLOT_PAIRS + LANES - 1) / LANES;  // per lane and slot; the last only of some
+    static constexpr int BATCH = H_ONLY ? 3 : (NPL == PN ? 4 : 7);    // slots a round: D and P, or all of them
+    static constexpr int ROUNDS = (H_ONLY ? 21 : 28) / BATCH;
+    static_assert(BATCH * ROUNDS == (H_ONLY ? 21 : 28) && 2 * BATCH * SLOT * 8 <= 159 * 1024, "staging");
+};
 
 // the slot staged as number j: D, P, At, K
 __device__ __forceinline__ constexpr int slot(int j)
@@ -711,6 +716,15 @@ __device__ __forceinline__ void take(const double *__restrict__ f, const Cell &C
     asm volatile("" : "+v"(X.S), "+v"(X.Se), "+v"(X.trdP), "+v"(X.trdPe) : : "memory");
 #pragma unroll
     for (int i = 0; i < 3; ++i) asm volatile("" : "+v"(X.M[i]), "+v"(X.Me[i]) : : "memory");
+}
+
+// slots J0..J0 + N - 1, each STRIDE doubles after the one before
+template <int J0, int N, int STRIDE>
+__device__ __forceinline__ void take_all(const double *__restrict__ f, const Cell &C, const double gd[6],
+                                         const double ig[6], Sums &X)
+{
+    take<J0>(f, C, gd, ig, X);
+    if constexpr (N > 1) take_all<J0 + 1, N - 1, STRIDE>(f + STRIDE, C, gd, ig, X);
 }
 
 // H and M_i (or H only) from the sums, the metric's inverse and phi
@@ -821,25 +835,33 @@ __device__ __forceinline__ void finish(const Sums &X, const double ig[6], double
 // H_ONLY: what the refinement criterion takes, H of every cell (HM: one value a cell) and nothing else: At
 // and K are read pointwise, the slots that are only tested for finiteness not at all, and no norms are
 // summed: 4390 lines a leaf instead of 6980.
-template <int H_ONLY>
-__global__ __launch_bounds__(cons::LANES) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_constraints_lds(
+//
+// NPL planes a work-group: the whole leaf, or, while all of a mesh's slabs of three planes run side by side
+// (three a leaf on 256 CUs), a slab.  There is then one round of work-groups and its length is the time: a
+// third of the LDS reads, seven slots a round instead of four.  See CONS_SLAB_LEAVES.
+template <int H_ONLY, int NPL>
+__global__ __launch_bounds__((cons::Staging<H_ONLY, NPL>::LANES))
+__attribute__((amdgpu_waves_per_eu(NPL / 3, NPL / 3))) void k_constraints_lds(
     const double *__restrict__ Q, double *__restrict__ HM, const PatchGeom *__restrict__ geom, int32_t npatch,
     double r_excise, double *__restrict__ part)
 {
     using namespace cons;
-    constexpr int BATCH = cons::BATCH<H_ONLY>;
+    typedef Staging<H_ONLY, NPL> St;
+    constexpr int SLOT = St::SLOT, SLOT_PAIRS = St::SLOT_PAIRS, LANES = St::LANES, COPIES = St::COPIES;
+    constexpr int BATCH = St::BATCH, ROUNDS = St::ROUNDS;
     __shared__ double bufa[BATCH * SLOT], bufb[BATCH * SLOT];
     __shared__ double red[LANES / 64][4];
-    const int p = (int)xcd_logical_block(blockIdx.x, gridDim.x);
+    const int lb = (int)xcd_logical_block(blockIdx.x, gridDim.x);
+    const int p = lb / (PN / NPL), zb = 3 + NPL * (lb % (PN / NPL));  // the leaf, and the first of the planes
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     double h2 = 0.0, m2 = 0.0, cnt = 0.0, bad = 0.0;
     if (p < npatch) {  // uniform over the work-group
         const PatchBuf qb{Q + (int64_t)p * PS};
-        const bool act = tid < NCELL;
-        const int cc = act ? tid : NCELL - 1, m = cc / 9;
+        const bool act = tid < St::CELLS;
+        const int cc = act ? tid : St::CELLS - 1, m = cc / 9;
         // rows in an order that spreads them over the LDS banks, as slab_row_y, planes of 13 rows
         const int zl = m / 9, k9 = (m + 6 * zl) % 9, yr = k9 / 2 + (k9 % 2 ? 5 : 0), x = cc % 9 + 3;
-        const uint32_t ob = 8u * (uint32_t)boff(x, yr + 3, zl + 3);
+        const uint32_t ob = 8u * (uint32_t)boff(x, yr + 3, zl + zb);
         // the slots that are only tested, and the metric and phi, first: they are used first
         double g[6], other = 0.0, rest[H_ONLY ? 7 : SAT - 7 + SD - STHETA + 1];
 #pragma unroll
@@ -856,32 +878,34 @@ __global__ __launch_bounds__(cons::LANES) __attribute__((amdgpu_waves_per_eu(3, 
             for (int v = STHETA; v < SD; ++v) rest[n++] = qb.load(ob, v);
             rest[n++] = qb.load(ob, SK0);
         }
-        const double *src[2];
+        const double *src[COPIES];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < COPIES; ++i) {
             const int q = min(i * LANES + tid, SLOT_PAIRS - 1);
             int e;
-            if (q < OWN_PAIRS) {
+            if (q < St::OWN_PAIRS) {
                 const int r = q / PAIRS, j = q % PAIRS;
-                e = (3 + r / ROWS) * ZS + (r % ROWS + 1) * XS + 2 * (j < 8 ? j : 7);
+                e = (zb + r / ROWS) * ZS + (r % ROWS + 1) * XS + 2 * (j < 8 ? j : 7);
             } else {
-                const int h = q - OWN_PAIRS, hp = h / 45;
-                e = (hp < 2 ? 1 + hp : 10 + hp) * ZS + ((h / 5) % 9 + 3) * YS + 2 + 2 * (h % 5);
+                const int h = q - St::OWN_PAIRS, hp = h / 45;
+                e = (hp < 2 ? zb - 2 + hp : zb + NPL - 2 + hp) * ZS + ((h / 5) % 9 + 3) * YS + 2 + 2 * (h % 5);
             }
             src[i] = qb.base + e;
         }
-        const bool second = LANES + tid < SLOT_PAIRS;
+        const bool last = (COPIES - 1) * LANES + tid < SLOT_PAIRS;
         auto issue = [&](double *buf, int round) {
             double *dst = buf + wave * 128;
 #pragma unroll
             for (int j = 0; j < BATCH; ++j)
-                __builtin_amdgcn_global_load_lds((const void *)(src[0] + slot(round * BATCH + j) * CS),
-                                                 (lds_void_t *)(dst + j * SLOT), 16, 0, 0);
-            if (second)
+#pragma unroll
+                for (int i = 0; i < COPIES - 1; ++i)
+                    __builtin_amdgcn_global_load_lds((const void *)(src[i] + slot(round * BATCH + j) * CS),
+                                                     (lds_void_t *)(dst + j * SLOT + i * 2 * LANES), 16, 0, 0);
+            if (last)
 #pragma unroll
                 for (int j = 0; j < BATCH; ++j)
-                    __builtin_amdgcn_global_load_lds((const void *)(src[1] + slot(round * BATCH + j) * CS),
-                                                     (lds_void_t *)(dst + j * SLOT + 2 * LANES), 16, 0, 0);
+                    __builtin_amdgcn_global_load_lds((const void *)(src[COPIES - 1] + slot(round * BATCH + j) * CS),
+                                                     (lds_void_t *)(dst + j * SLOT + (COPIES - 1) * 2 * LANES), 16, 0, 0);
         };
         issue(bufa, 0);
         issue(bufb, 1);
@@ -891,8 +915,8 @@ __global__ __launch_bounds__(cons::LANES) __attribute__((amdgpu_waves_per_eu(3, 
 #pragma unroll
         for (int k = -2; k <= 2; ++k) {
             const int z2 = zl + k;
-            C.zo[k + 2] = z2 >= 0 && z2 < PN ? C.c + k * PLANE
-                                             : OWN + (z2 < 0 ? z2 + 2 : z2 - PN + 2) * 90 + yr * LDS_HROW + (x - 2);
+            C.zo[k + 2] = z2 >= 0 && z2 < NPL ? C.c + k * PLANE
+                                              : St::OWN + (z2 < 0 ? z2 + 2 : z2 - NPL + 2) * 90 + yr * LDS_HROW + (x - 2);
         }
 #pragma unroll
         for (int a = 0; a < 3; ++a) C.i12[a] = 1.0 / (12.0 * G.dx[a]);
@@ -914,31 +938,21 @@ __global__ __launch_bounds__(cons::LANES) __attribute__((amdgpu_waves_per_eu(3, 
         X.S = X.Se = X.trdP = X.trdPe = 0.0;
 #pragma unroll
         for (int i = 0; i < 3; ++i) X.M[i] = X.Me[i] = 0.0;
-        // A barrier that orders the LDS accesses only: __syncthreads would wait for the copies in flight
-        // too.  Every LDS read before it has returned (lgkmcnt), and none is moved across (the clobbers).
-        auto barrier = [&]() {
-            asm volatile("" : : : "memory");
-            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" : : : "memory");
-        };
-        // the wave's copies of this round have landed (vmcnt: those of the next, one per slot and, where
-        // the wave has a second share, two, stay in flight), then those of all waves
+        // the wave's copies of this round have landed (those of the next stay in flight), then those of all waves
         auto wait = [&](bool more) {
-            if (!more) __builtin_amdgcn_s_waitcnt(0x0F70);
-            else if (wave * 64 + LANES < SLOT_PAIRS) __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * BATCH));
-            else __builtin_amdgcn_s_waitcnt(0x0F70 | BATCH);
-            barrier();
+            if (!more) wait_memory<0>();
+            else if (wave * 64 + (COPIES - 1) * LANES < SLOT_PAIRS) wait_memory<COPIES * BATCH>();
+            else wait_memory<(COPIES - 1) * BATCH>();
+            lds_swap();
         };
-#define CONS_ROUND(R, buf)                                               \
-    wait(R + 1 < ROUNDS);                                                \
-    take<BATCH * R + 0>(buf + 0 * SLOT, C, g, ig, X);                    \
-    take<BATCH * R + 1>(buf + 1 * SLOT, C, g, ig, X);                    \
-    take<BATCH * R + 2>(buf + 2 * SLOT, C, g, ig, X);                    \
-    if constexpr (!H_ONLY) take<4 * R + 3>(buf + 3 * SLOT, C, g, ig, X); \
-    if (R + 2 < ROUNDS) {                                                \
-        barrier();                                                       \
-        issue(buf, R + 2);                                               \
+#define CONS_ROUND(R, buf)                                                     \
+    if constexpr (R < ROUNDS) {                                                \
+        wait(R + 1 < ROUNDS);                                                  \
+        take_all<(R < ROUNDS ? R * BATCH : 0), BATCH, SLOT>(buf, C, g, ig, X); \
+        if (R + 2 < ROUNDS) {                                                  \
+            lds_swap();                                                        \
+            issue(buf, R + 2);                                                 \
+        }                                                                      \
     }
         CONS_ROUND(0, bufa)
         CONS_ROUND(1, bufb)
@@ -955,7 +969,7 @@ __global__ __launch_bounds__(cons::LANES) __attribute__((amdgpu_waves_per_eu(3, 
         double hm[4];
         finish<H_ONLY>(X, ig, phi, hm);
         if constexpr (H_ONLY) {
-            if (act) HM[(int64_t)p * NCELL + (zl * 9 + yr) * 9 + x - 3] = hm[0];
+            if (act) HM[(int64_t)p * NCELL + ((zb - 3 + zl) * 9 + yr) * 9 + x - 3] = hm[0];
         } else if (act) {
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
@@ -968,12 +982,12 @@ __global__ __launch_bounds__(cons::LANES) __attribute__((amdgpu_waves_per_eu(3, 
             other += 0.0 * X.K + 0.0 * phi;
 #pragma unroll
             for (int j = 0; j < 4; ++j) other += 0.0 * hm[j];
-            const int c = (zl * 9 + yr) * 9 + x - 3;
+            const int c = ((zb - 3 + zl) * 9 + yr) * 9 + x - 3;
             if (HM)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) HM[((int64_t)p * 4 + j) * NCELL + c] = hm[j];
             const double X0 = G.org[0] + (x - 2.5) * G.dx[0], Y0 = G.org[1] + (yr + 0.5) * G.dx[1],
-                         Z0 = G.org[2] + (zl + 0.5) * G.dx[2];
+                         Z0 = G.org[2] + (zb + zl - 2.5) * G.dx[2];
             const double r = sqrt(X0 * X0 + Y0 * Y0 + Z0 * Z0);
             if (!(other == 0.0)) bad = 1.0;
             else if (r >= r_excise) {
@@ -1618,15 +1632,23 @@ hipError_t launch_rk4(int32_t s, double dt, const double *Qn, const double *K, d
     return hipGetLastError();
 }
 
-// one work-group per leaf, a multiple of 8 for the XCD block order (at least 8)
-int64_t constraints_blocks(int32_t npatch) { return std::max<int64_t>(8, ((int64_t)npatch + 7) / 8 * 8); }
+// One work-group per leaf, or three where the slabs of all leaves run at once; a multiple of 8 for the XCD
+// block order (at least 8).  The line: 256 CUs, one work-group each.  H and M of 1 / 27 / 64 / 85 leaves by
+// leaves 28 / 30 / 31 / 32 us, by slabs 16 / 17 / 20 / 22 us, and 32 us by leaves just above it.
+constexpr int32_t CONS_SLAB_LEAVES = 256 / 3;
+static int64_t blocks_of(int64_t n) { return std::max<int64_t>(8, (n + 7) / 8 * 8); }
+int64_t constraints_blocks(int32_t npatch) { return blocks_of(npatch <= CONS_SLAB_LEAVES ? 3 * (int64_t)npatch : npatch); }
 
 hipError_t launch_constraints(const double *Q, double *HM, const PatchGeom *geom, int32_t npatch,
                               double r_excise, double *part, double *out3, hipStream_t st)
 {
     const int64_t nb = constraints_blocks(npatch);
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_constraints_lds<0>), dim3((unsigned)nb), dim3(cons::LANES), 0, st, Q, HM, geom,
-                       npatch, r_excise, part);
+    if (npatch <= CONS_SLAB_LEAVES)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_constraints_lds<0, 3>), dim3((unsigned)nb),
+                           dim3(cons::Staging<0, 3>::LANES), 0, st, Q, HM, geom, npatch, r_excise, part);
+    else
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_constraints_lds<0, PN>), dim3((unsigned)nb),
+                           dim3(cons::Staging<0, PN>::LANES), 0, st, Q, HM, geom, npatch, r_excise, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_reduce_parts, dim3(1), dim3(1024), 0, st, part, nb, out3);
@@ -1637,8 +1659,8 @@ hipError_t launch_tags(const double *Q, double *H, const PatchGeom *geom, const 
                        int32_t npatch, double theta_r, double theta_c, int32_t max_level, int8_t *tags,
                        double *ind, hipStream_t st)
 {
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_constraints_lds<1>), dim3((unsigned)constraints_blocks(npatch)), dim3(cons::LANES),
-                       0, st, Q, H, geom, npatch, 0.0, nullptr);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_constraints_lds<1, PN>), dim3((unsigned)blocks_of(npatch)),
+                       dim3(cons::Staging<1, PN>::LANES), 0, st, Q, H, geom, npatch, 0.0, nullptr);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_tag_indicator, dim3(npatch), dim3(256), 0, st, Q, H, geom, ind);
