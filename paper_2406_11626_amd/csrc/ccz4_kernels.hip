@@ -531,74 +531,88 @@ __global__ void k_capture_bg(const double *__restrict__ Q, const BoundaryFace *_
 }
 
 // ------------------------------------------------------------------ RK4 stage
-// classical RK4 in two-register form: weights of acc (b) and of the stage state (a)
-__device__ __forceinline__ void rk_one(int s, double dt, const double *__restrict__ qn, const double *__restrict__ kk,
-                                       double *__restrict__ acc, double *__restrict__ qx, int64_t e)
+// Classical RK4 in two-register form at N elements of a lane, e(0..N - 1), negative where there is none.
+// Every load comes first: the compiler cannot move a load past the store of another element by itself.
+template <int N, typename Element>
+__device__ __forceinline__ void rk_combine(int s, double dt, const double *__restrict__ qn, const double *__restrict__ kk,
+                                           double *__restrict__ acc, double *__restrict__ qx, Element e)
 {
-    const double kv = kk[e];
-    if (s == 0) {
-        const double q0 = qn[e];
-        acc[e] = q0 + (1.0 / 6.0) * dt * kv;
-        qx[e] = q0 + 0.5 * dt * kv;
-    } else if (s == 1) {
-        acc[e] = acc[e] + (1.0 / 3.0) * dt * kv;
-        qx[e] = qn[e] + 0.5 * dt * kv;
-    } else if (s == 2) {
-        acc[e] = acc[e] + (1.0 / 3.0) * dt * kv;
-        qx[e] = qn[e] + dt * kv;
-    } else {
-        qx[e] = acc[e] + (1.0 / 6.0) * dt * kv;
+    double k[N], q[N], a[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        if (e(j) < 0) continue;
+        k[j] = kk[e(j)];
+        if (s < 3) q[j] = qn[e(j)];
+        if (s > 0) a[j] = acc[e(j)];
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        if (e(j) < 0) continue;
+        if (s == 0) {
+            acc[e(j)] = q[j] + (1.0 / 6.0) * dt * k[j];
+            qx[e(j)] = q[j] + 0.5 * dt * k[j];
+        } else if (s < 3) {
+            acc[e(j)] = a[j] + (1.0 / 3.0) * dt * k[j];
+            qx[e(j)] = s == 1 ? q[j] + 0.5 * dt * k[j] : q[j] + dt * k[j];
+        } else {
+            qx[e(j)] = a[j] + (1.0 / 6.0) * dt * k[j];
+        }
     }
 }
 
-// RK4_PARTS work-groups per leaf, a run of slots each, the first with the slots that s = 3 projects
-// together.  A work-group combines the leaf's interior, one cell a lane, and then the Sommerfeld ghosts
-// of its boundary faces (not projected), whose x layers share their lines with the interior.  Bound by
-// memory, most of it the partial lines written: 720 leaves with 484 boundary faces 0.81 -> 0.76 ms a
-// stage, 16^3 leaves 4.2 -> 3.85 ms (a kernel over all cells and one over all ghosts before).
-constexpr int RK4_PARTS = 4, RK4_LANES = 768;
+// RK4_PARTS work-groups per leaf combine its interior, one cell a lane, a run of slots each, the first with
+// the slots that s = 3 projects together; RK4_CHUNKS more for each of its six faces combine the ghosts, where
+// the face is a Sommerfeld one (not projected).  Bound by memory, most of it the partial lines written, and on
+// few leaves by the chain of a work-group's loads, which is therefore kept to one or two batches.  Stages 0..3
+// together on 1 / 27 / 125 / 720 / 4096 leaves: 45 / 96 / 453 / 2560 / 13080 us; 142 / 132 / 493 / 2754 / 13800
+// us where the first work-groups took the ghosts too, face by face and slot by slot; 112 / 190 / 519 / 2980 /
+// 15120 us by a kernel over all cells and one over all ghosts.
+constexpr int RK4_PARTS = 4, RK4_CHUNKS = 4, RK4_LANES = 768;
 constexpr int RK4_HEAD = SAT + 6, RK4_REST = (NV - RK4_HEAD) / (RK4_PARTS - 1);
+constexpr int RK4_CHUNK = (NV + RK4_CHUNKS - 1) / RK4_CHUNKS;  // slots of a ghost work-group, every third a lane's
 static_assert(RK4_HEAD + (RK4_PARTS - 1) * RK4_REST == NV && RK4_LANES >= 3 * NFACE, "slots of the parts");
 
+template <int GHOSTS>
 __global__ __launch_bounds__(RK4_LANES) void k_rk4(int32_t s, double dt, const double *__restrict__ Qn,
                                                    const double *__restrict__ Kk, double *__restrict__ acc,
                                                    double *__restrict__ Qx, int32_t npatch,
                                                    const int32_t *__restrict__ pface)
 {
-    const int64_t lb = xcd_logical_block(blockIdx.x, gridDim.x);
-    const int p = (int)(lb / RK4_PARTS), part = (int)(lb % RK4_PARTS);
+    constexpr uint32_t WGS = RK4_PARTS + (GHOSTS ? 6 * RK4_CHUNKS : 0);
+    constexpr int BATCH = 6;  // slots of an interior cell together
+    const uint32_t lb = (uint32_t)xcd_logical_block(blockIdx.x, gridDim.x);
+    const int p = (int)(lb / WGS), part = (int)(lb % WGS), i = (int)threadIdx.x;
     if (p >= npatch) return;
-    const int v0 = part == 0 ? 0 : RK4_HEAD + (part - 1) * RK4_REST, v1 = RK4_HEAD + part * RK4_REST;
     const int64_t leaf = (int64_t)p * PS;
-    const int i = (int)threadIdx.x;
-    if (i < NCELL) {
-        const int64_t base = leaf + boff(i % 9 + 3, (i / 9) % 9 + 3, i / 81 + 3);
-        if (s < 3 || part > 0) {
-            for (int v = v0; v < v1; v += 4) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (v + j < v1) rk_one(s, dt, Qn, Kk, acc, Qx, base + (int64_t)(v + j) * CS);
-            }
-        } else {
-            double q[RK4_HEAD];
-#pragma unroll
-            for (int v = 0; v < RK4_HEAD; ++v) {
-                const int64_t e = base + (int64_t)v * CS;
-                q[v] = acc[e] + (1.0 / 6.0) * dt * Kk[e];
-            }
-            project_cell(q);
-#pragma unroll
-            for (int v = 0; v < RK4_HEAD; ++v) Qx[base + (int64_t)v * CS] = q[v];
-        }
-    }
-    if (!pface || i >= 3 * NFACE) return;
-    for (int f = 0; f < 6; ++f) {
-        if (pface[6 * p + f] < 0) continue;
+    if (GHOSTS && part >= RK4_PARTS) {
+        const int f = (part - RK4_PARTS) / RK4_CHUNKS, first = (part - RK4_PARTS) % RK4_CHUNKS * RK4_CHUNK;
+        if (pface[6 * p + f] < 0 || i >= 3 * NFACE) return;
         int L, t1, t2;
         slab_coords(f / 2, i % NFACE, L, t1, t2);
         const int64_t base = leaf + slab_off(f / 2, ghost_c(f % 2 ? 1 : -1, L), t1, t2);
-        for (int v = v0 + i / NFACE; v < v1; v += 3) rk_one(s, dt, Qn, Kk, acc, Qx, base + (int64_t)v * CS);
+        const int v = first + i / NFACE, end = min(first + RK4_CHUNK, NV);
+        rk_combine<(RK4_CHUNK + 2) / 3>(s, dt, Qn, Kk, acc, Qx,
+                                        [&](int j) { return v + 3 * j < end ? base + (int64_t)(v + 3 * j) * CS : -1; });
+        return;
     }
+    if (i >= NCELL) return;
+    const int v0 = part == 0 ? 0 : RK4_HEAD + (part - 1) * RK4_REST, v1 = RK4_HEAD + part * RK4_REST;
+    const int64_t base = leaf + boff(i % 9 + 3, (i / 9) % 9 + 3, i / 81 + 3);
+    if (s < 3 || part > 0) {
+        for (int v = v0; v < v1; v += BATCH)
+            rk_combine<BATCH>(s, dt, Qn, Kk, acc, Qx,
+                              [&](int j) { return v + j < v1 ? base + (int64_t)(v + j) * CS : -1; });
+        return;
+    }
+    double q[RK4_HEAD];
+#pragma unroll
+    for (int v = 0; v < RK4_HEAD; ++v) {
+        const int64_t e = base + (int64_t)v * CS;
+        q[v] = acc[e] + (1.0 / 6.0) * dt * Kk[e];
+    }
+    project_cell(q);
+#pragma unroll
+    for (int v = 0; v < RK4_HEAD; ++v) Qx[base + (int64_t)v * CS] = q[v];
 }
 
 // ------------------------------------------------------------------ constraints
@@ -1627,8 +1641,12 @@ hipError_t launch_rk4(int32_t s, double dt, const double *Qn, const double *K, d
                       int32_t npatch, const int32_t *pface, hipStream_t st)
 {
     if (npatch <= 0) return hipSuccess;
-    const int64_t nb = ((int64_t)npatch + 7) / 8 * 8 * RK4_PARTS;  // a multiple of 8 for the XCD block order
-    hipLaunchKernelGGL(k_rk4, dim3((unsigned)nb), dim3(RK4_LANES), 0, st, s, dt, Qn, K, acc, Qx, npatch, pface);
+    const unsigned n8 = ((unsigned)npatch + 7) / 8 * 8;  // a multiple of 8 for the XCD block order
+    auto go = [&](auto kernel, unsigned per_leaf) {
+        hipLaunchKernelGGL(kernel, dim3(n8 * per_leaf), dim3(RK4_LANES), 0, st, s, dt, Qn, K, acc, Qx, npatch, pface);
+    };
+    if (pface) go(k_rk4<1>, RK4_PARTS + 6 * RK4_CHUNKS);
+    else go(k_rk4<0>, RK4_PARTS);
     return hipGetLastError();
 }
 
