@@ -920,6 +920,7 @@ __attribute__((amdgpu_waves_per_eu(NPL / 3, NPL / 3))) void k_constraints_lds(
                 for (int j = 0; j < BATCH; ++j)
                     __builtin_amdgcn_global_load_lds((const void *)(src[COPIES - 1] + slot(round * BATCH + j) * CS),
                                                      (lds_void_t *)(dst + j * SLOT + (COPIES - 1) * 2 * LANES), 16, 0, 0);
+            copies_issued();
         };
         issue(bufa, 0);
         issue(bufb, 1);

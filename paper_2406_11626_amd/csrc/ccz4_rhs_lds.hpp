@@ -167,6 +167,10 @@ __device__ __forceinline__ Stager lds_stager(const double *__restrict__ qp, int 
     return g;
 }
 
+// Ends a group of copies: those issued after it stay after it, which the counts of wait_memory rest on (the
+// groups write different LDS variables, so nothing else keeps the compiler from mixing them).
+__device__ __forceinline__ void copies_issued() { asm volatile("" ::: "memory"); }
+
 // Issue the direct global->LDS copies of N slots into the buffers at `lds`, which no wave reads any
 // more (lds_swap); returns without waiting for them.
 template <int N>
@@ -184,6 +188,7 @@ __device__ __forceinline__ void lds_issue(double *lds, const int (&slots)[N], co
         for (int j = 0; j < N; ++j)
             __builtin_amdgcn_global_load_lds((const void *)(g.src[LDS_COPIES - 1] + slots[j] * CS),
                                              (lds_void_t *)(dst + j * LDS_SLOT + (LDS_COPIES - 1) * 512), 16, 0, 0);
+    copies_issued();
 }
 
 // Wait until at most N (0..63) memory operations of the wave are outstanding: all but its last N, in the
@@ -194,6 +199,14 @@ __device__ __forceinline__ void wait_memory()
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt((N & 15) | (N >> 4) << 14 | 0x0f70);
     asm volatile("" ::: "memory");
+}
+
+// Wait for every copy but those of the last group, of these slots (a wave without a share in the last chunk
+// issues LDS_COPIES - 1 a slot, the others more).
+template <int N>
+__device__ __forceinline__ void wait_all_but(const int (&)[N])
+{
+    wait_memory<(LDS_COPIES - 1) * N>();
 }
 
 // Work-group barrier that orders LDS reads and copies only: each wave's LDS reads are done, and the
@@ -662,7 +675,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
     const int rAt[6] = {SAT, SAT + 1, SAT + 2, SAT + 3, SAT + 4, SAT + 5};
     lds_issue(lds, rB, sg);
     lds_issue(ldsb, rAt, sg);
-    wait_memory<2 * 6>();  // B has landed
+    wait_all_but(rAt);  // B has landed
     lds_swap();
     if (act) {
         {  // B: advection + KO, GB^i = gt^kl d_(k B_l)^i, sdBtr_k = d_(k B_l)^l, and the shift
@@ -1181,7 +1194,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
         lds_swap();
         lds_issue(lds, r4a, sg);
         lds_issue(ldsb, r4b, sg);
-        wait_memory<2 * 5>();
+        wait_all_but(r4b);
         if (act) snk.store(R3_OUT, ro3, qa3, qc3);
     }
     lds_swap();
