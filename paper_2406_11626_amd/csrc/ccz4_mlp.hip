@@ -80,10 +80,12 @@ __device__ __forceinline__ void load_weights(MlpWeights &W, const float *__restr
     }
 }
 
-// The vectors that every row uses, zero where padded: normalisation and biases.
-struct MlpVectors {
+// The vectors that every row uses, zero where padded: normalisation and biases.  Read four at a time (vec4),
+// at multiples of 16 bytes.
+struct alignas(16) MlpVectors {
     float mu[NINP], is[NINP], b1[NH], b2[NH], b3[NOUTP];
 };
+static_assert(NINP % 4 == 0 && NH % 4 == 0 && NOUTP % 4 == 0, "whole groups of four");
 
 __device__ __forceinline__ void load_vectors(MlpVectors &V, const float *__restrict__ prm, const float *__restrict__ norm)
 {
