@@ -378,7 +378,8 @@ ccz4_status ccz4_features(ccz4_ctx *ctx, const double *Q, const double *HM, floa
 ccz4_status ccz4_mlp_forward(const float *params, const float *norm, const float *feat, int64_t n,
                              float *logits, void *stream);
 
-/* Floats of workspace that ccz4_mlp_grad needs for n rows. */
+/* Floats of workspace that ccz4_mlp_grad asks for with n rows: a partial gradient for every 64 of them (the
+   kernel uses at most 256 of the partials, whatever n). */
 ccz4_status ccz4_mlp_workspace(int64_t n, int64_t *floats);
 
 /* Mean softmax cross-entropy of the logits of n rows against tags in {-1, 0, 1} (COARSEN,
@@ -395,8 +396,8 @@ ccz4_status ccz4_mlp_grad(const float *params, const float *norm, const float *f
 
 /* ccz4_mlp_grad without a workspace, for callers that cannot allocate (code under HIP graph
    capture, tight serving or training loops, harnesses that forbid hipMalloc): the same kernels
-   and the same result, bit for bit, with the per-tile partials in an array that the library
-   holds on each GPU until the process ends (CCZ4_MLP_NOALLOC_MAX_ROWS / 64 tiles of
+   and the same result, bit for bit, with the partial gradients in an array that the library
+   holds on each GPU until the process ends (CCZ4_MLP_NOALLOC_MAX_ROWS / 64 times
    CCZ4_MLP_NPARAM + 1 floats, 2.5 MB).  The call allocates nothing: no hipMalloc, no host or
    device allocation of any library.  n must be 1..CCZ4_MLP_NOALLOC_MAX_ROWS, else EINVAL (use
    ccz4_mlp_grad with a workspace).  Every call on a GPU shares that array: calls that overlap on

@@ -491,7 +491,7 @@ class Context:
         return new, Qn
 
     def autotune(self, Q, precision=PREC_FP64, reps=3, stream=None):
-        """Time the four launch configurations on this mesh and keep the fastest; returns the
+        """Time every launch configuration on this mesh and keep the fastest; returns the
         average stage times in ms (index = configuration)."""
         acc, Qx = self.new_state(0.0), self.new_state(0.0)
         ms = ccz4_autotune(self.h, Q, acc, Qx, precision, reps, stream)
@@ -528,8 +528,7 @@ class Context:
     def rk4_step_fused(self, Qn, dt, bufs, precision=PREC_FP64, stream=None, push=True):
         """One RK4 step in place on Qn with the fused stage kernel; bufs = (Q1, Q2, acc).
         With push (default) the step is ccz4_step_fused: the stages handle the same-level halos
-        themselves, so only Neumann
-        and coarse-fine faces are filled between stages; Qn must enter with all halos filled
+        themselves, so only Neumann and coarse-fine faces are filled between stages; Qn must enter with all halos filled
         (ccz4_fill_halos once after the initial data) and leaves with them filled.  Without push
         every halo is filled before each stage."""
         Q1, Q2, acc = bufs
@@ -586,7 +585,7 @@ class Context:
 
 
 class StepGraph:
-    """ccz4_step_graph_*: one fused RK4 step (push fill) captured once and replayed."""
+    """ccz4_step_graph_*: one fused RK4 step (ccz4_step_fused) captured once and replayed."""
 
     def __init__(self, ctx, Qn, bufs, dt, precision=PREC_FP64):
         Q1, Q2, acc = bufs

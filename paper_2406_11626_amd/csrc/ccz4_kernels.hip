@@ -384,12 +384,12 @@ struct StageSink {
     int64_t pd[3];     // offsets (doubles, from this cell) of its copies in same-level neighbours'
                        // face halos of Q_next along each axis, 0 for none
 
-    // Q_next at element e, and its copies in the neighbours' halos
-    // The copies into the y and z face halos (made only when a step ends) are streamed past the
-    // caches: no stage reads them (the next stage gathers those halos from the neighbours'
-    // interiors) and their rows are partial lines that nothing else writes, so cached they only
-    // wait in L2 as dirty lines for the next launch to evict (2-3 ms per step on 24^3 patches).
-    // The x-face copies stay cached: they complete lines of the neighbour's own rows in L2.
+    // Q_next at element e, and its copies in the neighbours' halos (after every stage: this kernel reads
+    // them there).  Those into the y and z face halos are streamed past the caches: their rows are
+    // partial lines that nothing else writes, and on all but small meshes L2 has evicted them before
+    // the next stage comes to them (a step of 125 / 720 / 4096 leaves 1.52 / 7.19 / 40.1 ms, cached 1.53 /
+    // 7.30 / 40.9 ms; of 27 leaves 0.65 ms, cached 0.55 ms).  The x-face copies stay cached: they
+    // complete lines of the neighbour's own rows in L2.
     __device__ __forceinline__ void out(int64_t e, double val)
     {
         qx[e] = val;
@@ -1271,7 +1271,7 @@ __device__ __forceinline__ void reconstruct_from_lds(const LdsCell<XG> &C, doubl
 // cells of every leaf.  One work-group per z-slab copies the slab's 11 primaries into LDS exactly as
 // the stage kernel stages a slot (the slab's planes with their x and y halos, the interior rows of
 // the three planes below and above), then every lane forms its cell's 33 differences from LDS
-// (110 KB: one work-group per CU; two rounds of six primaries in 60 KB, two work-groups per CU, ran
+// (116 KiB: one work-group per CU; two rounds of six primaries in 63 KiB, two work-groups per CU, ran
 // 5% slower; one thread per cell reading its stencils through the caches ran 30% slower).  The
 // primaries' halos must be filled, except the face halos normal to an axis of gaxes and shared with a
 // same-level leaf, which are read from that leaf's interior.  Every value within

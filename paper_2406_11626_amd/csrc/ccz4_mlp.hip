@@ -24,7 +24,7 @@ constexpr int NIN = MLP_NIN, NINP = 96, NH = MLP_NH, NOUT = MLP_NOUT, NOUTP = 16
 constexpr int OW1 = 0, OB1 = OW1 + NH * NIN, OW2 = OB1 + NH, OB2 = OW2 + NH * NH, OW3 = OB2 + NH,
               OB3 = OW3 + NOUT * NH;
 static_assert(OB3 + NOUT == MLP_NPARAM, "parameter layout");
-constexpr int TILE = 64;  // rows (patches) of four waves, 16 per wave
+constexpr int TILE = 64;  // rows (patches) of a forward work-group's four waves; the unit of the workspace
 
 typedef short bf4_t __attribute__((ext_vector_type(4)));
 typedef float f4_t __attribute__((ext_vector_type(4)));
@@ -580,7 +580,7 @@ __global__ void k_tag_learned_family(const int8_t *__restrict__ pre, const int32
 
 int32_t mlp_tiles(int64_t n) { return (int32_t)((n + TILE - 1) / TILE); }
 
-// Per-tile partial sums of the loss gradient for callers that cannot allocate a workspace: a
+// Partial sums of the loss gradient for callers that cannot allocate a workspace: a
 // file-scope device array, one copy per GPU, held until the process ends.  Its device address is
 // taken once per device with hipGetSymbolAddress (the array's name is not a device address in
 // host code) and kept; kernels receive that address.  Every grad call on a GPU shares the array.
@@ -628,7 +628,7 @@ hipError_t launch_mlp_grad(const float *prm, const float *norm, const float *fea
                            float *work, float *trace, float *grad, float *loss, hipStream_t st)
 {
     const int32_t nt = mlp_tiles(n), nb = std::min((nt + GROWS / TILE - 1) / (GROWS / TILE), MLP_GRAD_BLOCKS);
-    if ((nt + 63) / 64 > 65535) return hipErrorInvalidConfiguration;  // 268 M rows
+    if ((nt + 63) / 64 > 65535) return hipErrorInvalidConfiguration;  // more than 268 M rows are refused
     hipLaunchKernelGGL(k_mlp_grad, dim3(nb), dim3(64 * GWAVES), 0, st, prm, norm, feat, tags, n, work, trace);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

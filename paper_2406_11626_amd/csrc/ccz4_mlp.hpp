@@ -10,8 +10,10 @@ constexpr int MLP_NIN = 81, MLP_NH = 64, MLP_NOUT = 3, MLP_NPARAM = 9603;
 // floats per row of the optional gradient trace: x (81), a1 (64), a2 (64), d3 (3), d2 (64), d1 (64)
 constexpr int MLP_TRACE = MLP_NIN + 4 * MLP_NH + MLP_NOUT;
 
+// the unit of the workspace that callers bring: one partial gradient per 64 rows (the gradient kernel leaves one
+// for every 128 and at most 256 of them)
 int32_t mlp_tiles(int64_t n);
-// the library's own gradient partials (ccz4_mlp_grad_noalloc): room for this many 64-row tiles
+// the library's own gradient partials (ccz4_mlp_grad_noalloc): room for this many
 constexpr int MLP_SCRATCH_TILES = 64;
 // device address of the partials array on the current device (taken once per device)
 hipError_t mlp_scratch(float **out);

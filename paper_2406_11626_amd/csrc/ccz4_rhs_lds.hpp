@@ -524,11 +524,6 @@ __device__ __forceinline__ SlotDeriv stencils(const Cell &c, int b, const double
     return r;
 }
 
-__device__ __forceinline__ double dot3(const double be[3], const double d[3])
-{
-    return be[0] * d[0] + be[1] * d[1] + be[2] * d[2];
-}
-
 // r = v, materialised here: the opaque move keeps the computation of v inside its block of
 // the algebra instead of letting it drift towards the round's output loop.
 __device__ __forceinline__ void keep(double &r, double v)
@@ -637,7 +632,7 @@ __device__ __forceinline__ void rhs_slab_lds(const double *__restrict__ qp, doub
     const T red = p.formulation ? T(0) : T(1);
     // Round 3's Ghat sector shares the Ricci sector's loads and Christoffel symbols when the algebra is
     // FP32 (room in the register file); with FP64 algebra it reloads them in a block of its own, which
-    // keeps the register peak of the Ricci sector below spilling.
+    // keeps the register peak of the Ricci sector down (four to twelve registers of a kernel spill; merged, 74).
     constexpr bool GHAT_IN_RICCI = sizeof(T) == 4;
 
     // carried between rounds

@@ -11,7 +11,7 @@
 namespace ccz4 {
 
 // LDS-staged variants: one work-group per (patch, z-slab), every lane takes part in staging;
-// the 151 KB of LDS leave one work-group per CU, so the waves may use the whole register file.
+// the 158 KiB of LDS leave one work-group per CU, so the waves may use the whole register file.
 template <int XG>
 __device__ __forceinline__ void lds_cell_setup(double *lds, double *ldsb, int sl, const PatchGeom &g, const RhsParams &prm,
                                                const HaloSrc &hs, LdsCell<XG> &C, uint32_t &ob, bool &act)
