@@ -295,7 +295,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     load_vectors(V, prm, norm);  // with a barrier
     const f4_t zero = {0.f, 0.f, 0.f, 0.f};
     const int ot = w >> 1, half = w & 1;
-    f4_t gw1[3] = {zero, zero, zero}, gw2[2] = {zero, zero}, gw3 = zero;
+    // the sums of a pass's two halves of 64 rows apart: half as long, each, as one chain over all of them (which on
+    // 65..190 rows had up to 1.2 times the rounding of sums of 64 rows)
+    f4_t gw1[2][3], gw2[2][2], gw3[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) gw1[h][c] = zero;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) gw2[h][c] = zero;
+        gw3[h] = zero;
+    }
     f4_t gb1[4] = {zero, zero, zero, zero}, gb2[4] = {zero, zero, zero, zero}, gb3 = zero;
     float loss = 0.f;
     const float inv_n = 1.0f / (float)n;
@@ -384,13 +394,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         // gW1 = d1 x^T, gW2 = d2 a1^T, gW3 = d3 a2^T over the pass's rows
 #pragma unroll
         for (int k = 0; k < GROWS; k += 16) {
+            const int h = 2 * k / GROWS;
             const bf4_t p1 = get_block(S.d1, 16 * ot + li, k + 4 * g), p2 = get_block(S.d2, 16 * ot + li, k + 4 * g);
 #pragma unroll
-            for (int c = 0; c < 3; ++c) gw1[c] = mma(p1, get_block(S.x, 16 * (3 * half + c) + li, k + 4 * g), gw1[c]);
+            for (int c = 0; c < 3; ++c)
+                gw1[h][c] = mma(p1, get_block(S.x, 16 * (3 * half + c) + li, k + 4 * g), gw1[h][c]);
 #pragma unroll
-            for (int c = 0; c < 2; ++c) gw2[c] = mma(p2, get_block(S.a1, 16 * (2 * half + c) + li, k + 4 * g), gw2[c]);
+            for (int c = 0; c < 2; ++c)
+                gw2[h][c] = mma(p2, get_block(S.a1, 16 * (2 * half + c) + li, k + 4 * g), gw2[h][c]);
             if (half == 0)
-                gw3 = mma(get_block(S.d3, li, k + 4 * g), get_block(S.a2, 16 * ot + li, k + 4 * g), gw3);
+                gw3[h] = mma(get_block(S.d3, li, k + 4 * g), get_block(S.a2, 16 * ot + li, k + 4 * g), gw3[h]);
         }
         __syncthreads();  // the operands are read before the next pass writes its own
     }
@@ -429,11 +442,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const int i = 16 * (3 * half + c) + li;
-            if (i < NIN) out[OW1 + o * NIN + i] = gw1[c][r];
+            if (i < NIN) out[OW1 + o * NIN + i] = gw1[0][c][r] + gw1[1][c][r];
         }
 #pragma unroll
-        for (int c = 0; c < 2; ++c) out[OW2 + o * NH + 16 * (2 * half + c) + li] = gw2[c][r];
-        if (half == 0 && 4 * g + r < NOUT) out[OW3 + (4 * g + r) * NH + 16 * ot + li] = gw3[r];
+        for (int c = 0; c < 2; ++c) out[OW2 + o * NH + 16 * (2 * half + c) + li] = gw2[0][c][r] + gw2[1][c][r];
+        if (half == 0 && 4 * g + r < NOUT) out[OW3 + (4 * g + r) * NH + 16 * ot + li] = gw3[0][r] + gw3[1][r];
     }
     __syncthreads();
     const int t = threadIdx.x;
