@@ -529,7 +529,8 @@ static hipError_t launch_fills(const ccz4_ctx *c, double *Q, int32_t kinds, int3
 {
     const int32_t t = c->prm.transfer;
     hipError_t e = hipSuccess;
-    if (kinds & CCZ4_FILL_NEUMANN) e = launch_fill(Q, c->d_phn.p, (int32_t)c->ph_neu.size(), t, v0, v1, st);
+    // copies: the kernel of the operators that need few registers, whatever the context's operators are
+    if (kinds & CCZ4_FILL_NEUMANN) e = launch_fill(Q, c->d_phn.p, (int32_t)c->ph_neu.size(), 0, v0, v1, st);
     if (e == hipSuccess && (kinds & CCZ4_FILL_LEVELS)) {
         e = launch_fill(Q, c->d_phr.p, (int32_t)c->ph_res.size(), t, v0, v1, st);
         if (e == hipSuccess) e = launch_fill(Q, c->d_php.p, (int32_t)c->ph_pro.size(), t, v0, v1, st);

@@ -226,12 +226,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HIGHER ? 2 
     int L, t1, t2;
     slab_coords(tk.axis, idx, L, t1, t2);
     double *dst = Q + (int64_t)tk.patch * PS + slab_off(tk.axis, ghost_c(tk.side, L), t1, t2);
-    if (tk.kind == FK_NEUMANN || (HIGHER && tk.kind == FK_RESTRICT)) {
+    if (tk.kind == (HIGHER ? FK_RESTRICT : FK_NEUMANN)) {
         // copies; with the higher-order operators the restriction is one too: coarse ghost c_{2+L}
         // takes the fine cell with the same centre, tangentially the middle of the three fine
         // cells under it, along the normal the fine interior depth 3L - 1
         const int F1 = 3 * t1 + 1, F2 = 3 * t2 + 1;
-        const double *src = tk.kind == FK_RESTRICT
+        const double *src = HIGHER
                                 ? Q + (int64_t)tk.src[(F2 / 9) * 3 + F1 / 9] * PS +
                                       slab_off(tk.axis, depth_c(-tk.side, 3 * L - 1), F1 % 9, F2 % 9)
                                 : Q + (int64_t)tk.patch * PS + slab_off(tk.axis, depth_c(tk.side, 1), t1, t2);
